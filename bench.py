@@ -200,10 +200,10 @@ COUNTER_PASSES = {
 COUNTER_KERNELS = [("k_extend_wave", "k_extend_wave"), ("k_extend<false,", "k_extend"),
                    ("k_shadow<false,", "k_shadow"), ("k_tail<false,", "k_tail"),
                    ("k_shade", "k_shade"), ("k_res_block", "k_res_block"),
-                   ("k_conv3_lds<64, 4, 16, false>", "k_conv3_lds<64,4,16>"),
-                   ("k_conv3_lds<16, 4, 16, false>", "k_conv3_lds<16,4,16>"),
-                   ("k_conv3_lds<8, 4, 16, false>", "k_conv3_lds<8,4,16>"),
-                   ("k_conv3_lds<80, 1, 16, false>", "k_conv3_lds<80,1,16>"),
+                   ("k_conv3_rw<8, 2, 4, false, 0>", "k_conv3_rw<8,2,4>"),
+                   ("k_conv3_lds<16, 4, 16>", "k_conv3_lds<16,4,16>"),
+                   ("k_conv3_lds<8, 4, 16>", "k_conv3_lds<8,4,16>"),
+                   ("k_conv3_lds<80, 1, 16>", "k_conv3_lds<80,1,16>"),
                    ("k_conv<4>", "k_conv<4>")]
 # the closest-hit launches bench.py times as "extend": bounce 0 a wave at a time,
 # the other wavefront bounces lane by lane (k_extend<true, ..> is the counting pass)

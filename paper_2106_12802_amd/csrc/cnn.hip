@@ -26,6 +26,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "mrs_internal.hpp"
@@ -37,11 +38,16 @@ namespace mrs {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Round to nearest even, NaN stays NaN (v_cvt_pk_bf16_f32): one value, and two
+// in one word (a low).
 __device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0u;  // NaN stays NaN
-  u += 0x7fffu + ((u >> 16) & 1u);                      // round to nearest even
-  return (uint16_t)(u >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);
+}
+__device__ __forceinline__ uint32_t f2bf2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
 __device__ __forceinline__ bf16x8 zero8() {
@@ -139,7 +145,10 @@ __device__ __forceinline__ void conv_mainloop(const ConvArgs& p, int M, int m0, 
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int cpt = p.cin_p >> 3;  // 8-channel chunks per tap
-  const uint16_t* wrow = p.w + (size_t)(n0 + li) * p.kp + kq * 8;
+  // packed row by row, or in fragment order: 16 rows x 32 K as 64 lanes x 8
+  const uint16_t* wrow =
+      p.w + (p.frag ? (size_t)n0 * p.kp + lane * 8 : (size_t)(n0 + li) * p.kp + kq * 8);
+  const int wstep = p.frag ? 16 : 1;  // elements from one K index to the next, in steps of 32
   // Operands of K step ks; the next step's loads are issued before this step's
   // MFMAs so that their latency overlaps the matrix work.
   auto load_step = [&](int ks, bf16x8 (&A)[2], bf16x8 (&Bv)[NT]) {
@@ -149,7 +158,7 @@ __device__ __forceinline__ void conv_mainloop(const ConvArgs& p, int M, int m0, 
 #pragma unroll
     for (int r = 0; r < 2; ++r) A[r] = pv[r] ? load_chunk(p, pb[r], py[r], px[r], tap, c) : zero8();
 #pragma unroll
-    for (int j = 0; j < NT; ++j) Bv[j] = ld8(wrow + (size_t)j * 16 * p.kp + ks);
+    for (int j = 0; j < NT; ++j) Bv[j] = ld8(wrow + (size_t)j * 16 * p.kp + ks * wstep);
   };
   bf16x8 A[2], Bv[NT];
   load_step(0, A, Bv);
@@ -273,61 +282,21 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& p, const f32x4 (&a
       }
 }
 
-// 3x3 convolution with its operands staged in LDS (gfx950 gives a workgroup up
-// to 160 KB).  A block of 8 waves owns a 16 x 16 pixel tile of one image: the
-// (16+2) x (16+2) x CINP input tile with its zero halo is gathered through the
-// conv's input view (plain, or shuffle+concat), and the weights of one group
-// of 16 NT output channels (9 CINP x 16 NT BF16) are loaded once per group;
-// then every MFMA operand comes from LDS.  Wave w computes image rows 2w and
-// 2w+1 of the tile (two 16-pixel row tiles) x 16 NT channels with
-// v_mfma_f32_16x16x32_bf16; local K index k = tap CINP + c, so with CINP < 32
-// one K step spans two taps.  Inputs wider than CINP (a multiple of it, CINP =
-// 64: the dense blocks' 128..256-channel convs) are taken CINP channels at a
-// time, tile and weights restaged per channel chunk, the accumulators kept.
+// 3x3 convolution with its operands staged in LDS, for the convs whose input or
+// output is not a multiple of 64 channels (the input and the reconstruction
+// convs).  A block of 8 waves owns a 16 x 16 pixel tile of one image: the (16+2) x
+// (16+2) x CINP input tile with its zero halo is gathered through the conv's
+// input view (plain, or shuffle+concat), and the weights of one group of 16 NT
+// output channels (9 CINP x 16 NT BF16) are loaded once per group; then every
+// MFMA operand comes from LDS.  Wave w computes image rows 2w and 2w+1 of the tile
+// (two 16-pixel row tiles) x 16 NT channels with v_mfma_f32_16x16x32_bf16; K index
+// k = tap CINP + c, so with CINP < 32 one K step spans two taps.
 // LDS layouts are chosen for conflict-free 16-byte accesses: tile pixels
 // padded by 8 channels, weights chunk-major [k / 8][n][8] with one pad chunk
 // per k row.
 constexpr int C3_W = 16;  // tile width: one 16-pixel MFMA row tile
 
-// Epilogue of a data-gradient conv with a plain backward (EPI_PLAIN of
-// k_dgrad): y = scale acc (+ add1 + add2), zero where the ReLU mask is not
-// positive, stored FP32 and/or BF16 (times out_h_scale).  Loads first, then
-// stores, as in conv_epilogue.
 __device__ __forceinline__ bool pos_bf(uint16_t h) { return h != 0 && !(h & 0x8000u); }
-
-template <int NT>
-__device__ __forceinline__ void dgrad_epilogue_plain(const BwdEpi& e, int cout,
-                                                     const f32x4 (&acc)[2][NT],
-                                                     const int64_t (&m)[2][4], int n0, int li) {
-  float y[2][NT][4];
-  bool keep[2][NT][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int n = n0 + j * 16 + li;
-        keep[r][j][v] = m[r][v] >= 0 && n < cout;
-        const size_t idx = keep[r][j][v] ? (size_t)m[r][v] * e.stride + n : 0;
-        float t = acc[r][j][v] * e.scale;
-        if (e.add1 && keep[r][j][v]) t += e.add1[idx];
-        if (e.add2 && keep[r][j][v]) t += e.add2[idx];
-        if (e.mask && keep[r][j][v] && !pos_bf(e.mask[idx])) t = 0.0f;
-        y[r][j][v] = t;
-      }
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        if (!keep[r][j][v]) continue;
-        const size_t idx = (size_t)m[r][v] * e.stride + n0 + j * 16 + li;
-        if (e.out_f) e.out_f[idx] = y[r][j][v];
-        if (e.out_h) e.out_h[idx] = f2bf(y[r][j][v] * e.out_h_scale);
-      }
-}
 
 // LDS pitch of a tile pixel (BF16 channels): 16-byte reads of 8 consecutive
 // lanes (pixels) at this stride hit distinct banks; a multiple of 32 channels
@@ -353,9 +322,9 @@ constexpr int c3_min_waves() {
          (TH / 8 > 0 ? TH / 8 : 1);
 }
 
-template <int CINP, int NT, int TH, bool DG = false>
+template <int CINP, int NT, int TH>
 __global__ __launch_bounds__(32 * TH, (c3_min_waves<CINP, NT, TH>())) void k_conv3_lds(
-    ConvArgs p, int cout_p, int nsplit, BwdEpi be) {
+    ConvArgs p, int cout_p) {
   constexpr int THREADS = 32 * TH;  // TH / 2 waves, two tile rows each
   constexpr int TILE = (TH + 2) * (C3_W + 2);
   constexpr int PITCH = c3_pitch<CINP>();
@@ -369,9 +338,7 @@ __global__ __launch_bounds__(32 * TH, (c3_min_waves<CINP, NT, TH>())) void k_con
   const int lane = tid & 63, wave = tid >> 6;
   const int kq = lane >> 4, li = lane & 15;
   const int x0 = blockIdx.x * C3_W, y0 = blockIdx.y * TH;
-  const int b = blockIdx.z / nsplit, part = blockIdx.z - b * nsplit;
-  const int nper = cout_p / nsplit;  // output channels of this block (a multiple of NG)
-  const int nchunk = p.cin_p / CINP;
+  const int b = blockIdx.z;
   // Loads are issued in batches (C3_BATCH_T tile chunks, C3_BATCH_W weight
   // chunks per thread) before their LDS stores, so that their latencies
   // overlap instead of adding up.
@@ -381,72 +348,67 @@ __global__ __launch_bounds__(32 * TH, (c3_min_waves<CINP, NT, TH>())) void k_con
   // weight chunks in flight per thread; otherwise 3 and 3.
   constexpr int C3_BATCH_T = LDS_ALL > 80 * 1024 ? 6 : 3;
   constexpr int C3_BATCH_W = LDS_ALL > 80 * 1024 ? 9 : 3;
-  for (int n0 = part * nper; n0 < (part + 1) * nper; n0 += NG) {
+  for (int n0 = 0; n0 < cout_p; n0 += NG) {
     f32x4 acc[2][NT];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
       for (int j = 0; j < NT; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int ch = 0; ch < nchunk; ++ch) {
-      const int cbase = ch * CINP;
-      const bool first = n0 == part * nper && ch == 0;
-      if (!first) __syncthreads();  // the LDS operands are no longer read
-      if (nchunk > 1 || first) {
-        auto tile_load = [&](int i) -> bf16x8 {
-          const int px = i / (CINP / 8), c = (i - px * (CINP / 8)) * 8;
-          const int ty = px / (C3_W + 2), tx = px - ty * (C3_W + 2);
-          return i < TCH ? view_chunk(p, b, y0 - 1 + ty, x0 - 1 + tx, cbase + c) : zero8();
-        };
-        auto tile_store = [&](int i, bf16x8 v) {
-          const int px = i / (CINP / 8), c = (i - px * (CINP / 8)) * 8;
-          if (i < TCH) *reinterpret_cast<bf16x8*>(tile + px * PITCH + c) = v;
-        };
-        for (int i = tid; i < TCH; i += C3_BATCH_T * THREADS) {
-          bf16x8 v[C3_BATCH_T];
-#pragma unroll
-          for (int u = 0; u < C3_BATCH_T; ++u) v[u] = tile_load(i + u * THREADS);
-#pragma unroll
-          for (int u = 0; u < C3_BATCH_T; ++u) tile_store(i + u * THREADS, v[u]);
-        }
-      }
-      // local k = tap CINP + c holds packed column tap cin_p + cbase + c
-      auto w_load = [&](int i) -> uint4 {
-        const int n = i / (KP / 8), kc = i - n * (KP / 8);
-        const int k = kc * 8, tap = k / CINP;
-        const int kg = tap * p.cin_p + cbase + (k - tap * CINP);
-        return i < WCH ? *reinterpret_cast<const uint4*>(p.w + (size_t)(n0 + n) * p.kp + kg)
-                       : make_uint4(0u, 0u, 0u, 0u);
+    if (n0) {
+      __syncthreads();  // the weights in LDS are no longer read
+    } else {
+      auto tile_load = [&](int i) -> bf16x8 {
+        const int px = i / (CINP / 8), c = (i - px * (CINP / 8)) * 8;
+        const int ty = px / (C3_W + 2), tx = px - ty * (C3_W + 2);
+        return i < TCH ? view_chunk(p, b, y0 - 1 + ty, x0 - 1 + tx, c) : zero8();
       };
-      auto w_store = [&](int i, uint4 v) {
-        const int n = i / (KP / 8), kc = i - n * (KP / 8);
-        if (i < WCH) *reinterpret_cast<uint4*>(wts + (kc * WPITCH + n) * 8) = v;
+      auto tile_store = [&](int i, bf16x8 v) {
+        const int px = i / (CINP / 8), c = (i - px * (CINP / 8)) * 8;
+        if (i < TCH) *reinterpret_cast<bf16x8*>(tile + px * PITCH + c) = v;
       };
-      for (int i = tid; i < WCH; i += C3_BATCH_W * THREADS) {
-        uint4 v[C3_BATCH_W];
+      for (int i = tid; i < TCH; i += C3_BATCH_T * THREADS) {
+        bf16x8 v[C3_BATCH_T];
 #pragma unroll
-        for (int u = 0; u < C3_BATCH_W; ++u) v[u] = w_load(i + u * THREADS);
+        for (int u = 0; u < C3_BATCH_T; ++u) v[u] = tile_load(i + u * THREADS);
 #pragma unroll
-        for (int u = 0; u < C3_BATCH_W; ++u) w_store(i + u * THREADS, v[u]);
+        for (int u = 0; u < C3_BATCH_T; ++u) tile_store(i + u * THREADS, v[u]);
       }
-      __syncthreads();
-      for (int ks = 0; ks < KP; ks += 32) {
-        const int k = ks + kq * 8;
-        const int tap = k / CINP, c = k - tap * CINP;
-        const int dy = tap / 3, dx = tap - dy * 3;
-        bf16x8 A[2], Bv[NT];
+    }
+    // K index k = tap CINP + c, as packed
+    auto w_load = [&](int i) -> uint4 {
+      const int n = i / (KP / 8), kc = i - n * (KP / 8);
+      return i < WCH ? *reinterpret_cast<const uint4*>(p.w + (size_t)(n0 + n) * p.kp + kc * 8)
+                     : make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto w_store = [&](int i, uint4 v) {
+      const int n = i / (KP / 8), kc = i - n * (KP / 8);
+      if (i < WCH) *reinterpret_cast<uint4*>(wts + (kc * WPITCH + n) * 8) = v;
+    };
+    for (int i = tid; i < WCH; i += C3_BATCH_W * THREADS) {
+      uint4 v[C3_BATCH_W];
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
-          A[r] = tap < 9 ? ld8(tile + ((2 * wave + r + dy) * (C3_W + 2) + li + dx) * PITCH + c)
-                         : zero8();
+      for (int u = 0; u < C3_BATCH_W; ++u) v[u] = w_load(i + u * THREADS);
+#pragma unroll
+      for (int u = 0; u < C3_BATCH_W; ++u) w_store(i + u * THREADS, v[u]);
+    }
+    __syncthreads();
+    for (int ks = 0; ks < KP; ks += 32) {
+      const int k = ks + kq * 8;
+      const int tap = k / CINP, c = k - tap * CINP;
+      const int dy = tap / 3, dx = tap - dy * 3;
+      bf16x8 A[2], Bv[NT];
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        A[r] = tap < 9 ? ld8(tile + ((2 * wave + r + dy) * (C3_W + 2) + li + dx) * PITCH + c)
+                       : zero8();
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        Bv[j] = ld8(wts + (((ks >> 3) + kq) * WPITCH + j * 16 + li) * 8);
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
-          Bv[j] = ld8(wts + (((ks >> 3) + kq) * WPITCH + j * 16 + li) * 8);
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-          for (int j = 0; j < NT; ++j)
-            acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[r], Bv[j], acc[r][j], 0, 0, 0);
-      }
+          acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[r], Bv[j], acc[r][j], 0, 0, 0);
     }
     int64_t m[2][4];
 #pragma unroll
@@ -456,14 +418,399 @@ __global__ __launch_bounds__(32 * TH, (c3_min_waves<CINP, NT, TH>())) void k_con
         const int y = y0 + 2 * wave + r, x = x0 + kq * 4 + v;
         m[r][v] = (y < p.H && x < p.W) ? ((int64_t)b * p.H + y) * p.W + x : -1;
       }
-    if (DG) {
-      dgrad_epilogue_plain<NT>(be, p.cout, acc, m, n0, li);
-    } else {
-      EpiIn<NT> in;
-      epi_load<NT>(p, m, n0, li, in);
-      conv_epilogue<NT>(p, acc, m, n0, li, in);
+    EpiIn<NT> in;
+    epi_load<NT>(p, m, n0, li, in);
+    conv_epilogue<NT>(p, acc, m, n0, li, in);
+  }
+}
+
+// Row (channel) and K index of element e of a layer packed in fragment order:
+// 16-row tiles, each as K steps of 32, each as the 64 lanes' 8 weights in the
+// order of the MFMA's A operand (lane l: row l % 16, K 8 (l / 16) ..).
+__device__ __forceinline__ void frag_order(int e, int kp, int& row, int& k) {
+  const int t = e / (16 * kp), f = e - t * 16 * kp;
+  const int ks = f >> 9, lane = (f >> 3) & 63;
+  row = t * 16 + (lane & 15);
+  k = ks * 32 + (lane >> 4) * 8 + (f & 7);
+}
+
+// 3x3 convolution of 64-channel slices (cin_p a multiple of 64) with its weights
+// held in registers.  A block owns a tile of 16 columns x WR R rows of one image
+// and 16 WN output channels; wave (wr, wn) computes R rows x 16 channels.  The
+// input tile with its halo is staged in LDS, 64 channels at a time; the 18 K
+// steps' weights of a slice stay in the wave's registers and the wave sweeps the
+// R + 2 input rows once: a row's operands are read from LDS for the outer two tap
+// columns, shifted between lanes for the middle one, and feed the three output
+// rows that use them (taps dy = 0, 1, 2).  That is 0.28 LDS reads per MFMA (R = 8);
+// reading both operands for every product took 0.75 and made LDS bandwidth the
+// bound.  The weights are the MFMA's A operand (rows = output channels), the
+// pixels its B operand, so a lane ends up with 4 consecutive channels of one
+// pixel and the epilogue moves 8 and 16 bytes at a time.  The next slice's
+// weights are loaded as the last rows release the registers, and the next tile
+// goes through registers into the other LDS buffer.  The weights are packed in
+// fragment order (frag_order): row-major ones cost 16 half-used lines a load
+// and 7 us a launch.
+// Every output sums its K in the order slice, tap, channel, whatever the plan.
+// Measured (720p LR image, 64 / 128 / 256 input channels, one launch after the
+// other): 8.6 / 11.7 / 24.0 us (with FP32 residual in and out), 494 / 725 / 708
+// TFLOP/s; the 2-wave-per-SIMD MFMA time is 1.9 us for 64 channels, the LDS reads
+// 1.1, a launch 2.5, the first loads 1.7, the stores 2.  As data gradients of the
+// dense blocks (16384 pixels) 43-50 us by the direct conv, 5-8 now.
+template <int R, int WR>
+constexpr int rw_tile_px() {
+  return (WR * R + 2) * (C3_W + 2);
+}
+constexpr int RW_PITCH = 64 + 8;  // BF16 per tile pixel: 16-byte reads of 8 lanes hit all banks
+
+// What the epilogue of a conv adds and where it stores: y = relu?(acc + bias),
+// y = a1 + s1 y, y += a2, y += a3, zero where mask <= 0, to out_f (FP32) and
+// out_h (BF16 of y out_h_scale).  Pointers are to channel 0 of the block's group
+// of channels at pixel 0, with a stride in channels per pixel each.
+struct RwEpi {
+  const float *a1, *a2, *a3;
+  const uint16_t* mask;
+  float* out_f;
+  uint16_t* out_h;
+  int st1, st2, st3, stm, stf, sth;
+  float s1, out_h_scale;
+};
+
+enum RwMode { RW_FWD = 0, RW_DG = 1 };
+
+template <int MODE>
+__device__ __forceinline__ RwEpi rw_epi(const ConvArgs& p, const BwdEpi& e, int n0) {
+  RwEpi o;
+  o.a1 = o.a2 = o.a3 = nullptr;
+  o.mask = nullptr;
+  o.out_f = nullptr;
+  o.out_h = nullptr;
+  o.st1 = o.st2 = o.st3 = o.stm = o.stf = o.sth = NET_FEAT;
+  o.s1 = 1.0f;
+  o.out_h_scale = 1.0f;
+  if (MODE == RW_FWD) {
+    o.a1 = p.res ? p.res + n0 : nullptr;
+    o.a2 = p.res2 ? p.res2 + n0 : nullptr;
+    o.a3 = p.res3 ? p.res3 + n0 : nullptr;
+    o.st1 = o.st2 = o.st3 = p.cout;
+    o.s1 = p.res_scale;
+    o.out_f = p.out_f ? p.out_f + n0 : nullptr;
+    o.stf = p.out_f_stride;
+    o.out_h = p.out_h ? p.out_h + n0 : nullptr;
+    o.sth = p.out_h_stride;
+  } else if (e.mode == EPI_PLAIN) {
+    o.a1 = e.add1 ? e.add1 + n0 : nullptr;
+    o.a2 = e.add2 ? e.add2 + n0 : nullptr;
+    o.mask = e.mask ? e.mask + n0 : nullptr;
+    o.out_f = e.out_f ? e.out_f + n0 : nullptr;
+    o.out_h = e.out_h ? e.out_h + n0 : nullptr;
+    o.st1 = o.st2 = o.stm = o.stf = o.sth = e.stride;
+    o.out_h_scale = e.out_h_scale;
+  } else {  // EPI_DENSE: input slice n0 / 64 of a residual dense block
+    const int sl = n0 >> 6, ch = n0 & 63;
+    if (e.k == 1) {  // x_0 complete: the gradient of the block input
+      o.a1 = e.ga + n0;
+      o.st1 = RDG_DENSE;
+      o.a2 = e.add1 ? e.add1 + ch : nullptr;
+      o.a3 = e.add2 ? e.add2 + ch : nullptr;
+      o.mask = e.mask0 ? e.dense + n0 : nullptr;
+      o.stm = RDG_DENSE;
+      o.out_f = e.out_f ? e.out_f + ch : nullptr;
+      o.out_h = e.out_h + ch;
+    } else if (sl == e.k - 1) {  // x_{k-1} complete: through its ReLU
+      o.a1 = e.fusing ? nullptr : e.ga + n0;
+      o.st1 = RDG_DENSE;
+      o.mask = e.dense + n0;
+      o.stm = RDG_DENSE;
+      o.out_h = e.dy_next + ch;
+    } else {  // a running slice gradient; the block's last conv starts it
+      if (e.fusing) {
+        o.a1 = sl == 0 ? e.ds + ch : nullptr;
+      } else {
+        o.a1 = e.ga + n0;
+        o.st1 = RDG_DENSE;
+      }
+      o.out_f = e.ga + n0;
+      o.stf = RDG_DENSE;
     }
   }
+  return o;
+}
+
+// Buffer accesses: a uniform base, a 32-bit lane offset in bytes and a scalar
+// offset in one instruction.  A lane whose offset is not below `bytes` loads
+// zeros and stores nothing (the buffer's range check), so a lane outside the
+// image gets the offset BUF_OUT and needs no branch; in-image offsets stay
+// below 2^31 (at most 18 rows of 16384 pixels of 256 FP32 channels).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t BUF_OUT = 0x80000000u, BUF_MAX = 0x7fffffffu;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* base, uint32_t bytes = BUF_MAX) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 buf_ld16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t s = 0) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)s, 0);
+}
+__device__ __forceinline__ u32x2 buf_ld8(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+}
+__device__ __forceinline__ void buf_st16(__amdgpu_buffer_rsrc_t r, uint32_t off, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 0);
+}
+__device__ __forceinline__ void buf_st8(__amdgpu_buffer_rsrc_t r, uint32_t off, u32x2 v) {
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, 0);
+}
+
+// The operands of the middle tap column (pixel li + 1 in lane li) from those of
+// the outer two (pixels li and li + 2): lanes 1..15 of a row take the next
+// column's operand of the lane before, lane 0 this column's of the lane after.
+__device__ __forceinline__ bf16x8 rw_middle(bf16x8 left, bf16x8 right) {
+  const uint4 l = __builtin_bit_cast(uint4, left), r = __builtin_bit_cast(uint4, right);
+  auto one = [](uint32_t a, uint32_t c) {
+    const int first = __builtin_amdgcn_update_dpp(0, (int)a, 0x101, 0xf, 0xf, false);  // row_shl:1
+    return (uint32_t)__builtin_amdgcn_update_dpp(first, (int)c, 0x111, 0xf, 0xf, false);  // row_shr:1
+  };
+  return __builtin_bit_cast(bf16x8,
+                            make_uint4(one(l.x, r.x), one(l.y, r.y), one(l.z, r.z), one(l.w, r.w)));
+}
+
+template <int R, int WR, int WN, bool MULTI, int MODE>
+__global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_p, int nsplit,
+                                                           BwdEpi be) {
+  constexpr int THREADS = 64 * WR * WN, TH = WR * R, TILE = rw_tile_px<R, WR>();
+  constexpr int TCH = TILE * 8, CNT = (TCH + THREADS - 1) / THREADS;
+  constexpr int BN = WN * 16;
+  __shared__ __attribute__((aligned(16))) uint16_t tile[MULTI ? 2 : 1][TILE * RW_PITCH];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kq = lane >> 4, li = lane & 15;
+  const int wr = wave % WR, wn = wave / WR;
+  const int x0 = blockIdx.x * C3_W, y0 = blockIdx.y * TH;
+  const int b = blockIdx.z / nsplit, part = blockIdx.z - b * nsplit;
+  const int nper = cout_p / nsplit;  // output channels of this block (a multiple of BN)
+  const int nchunk = MULTI ? p.cin_p >> 6 : 1;
+  // this thread's chunks (8 channels of a pixel) of the input tile: byte offsets
+  // from the tile's first pixel inside the image (BUF_OUT: outside, zeros)
+  const int vs = p.mode == VIEW_PLAIN ? 0 : 1;  // log2 of the view's shuffle
+  const int yb = max(y0 - 1, 0) >> vs, xb = max(x0 - 1, 0) >> vs;
+  const auto src = buf(p.a + (((size_t)b * (p.H >> vs) + yb) * (p.W >> vs) + xb) * p.ca);
+  uint32_t off[CNT];
+#pragma unroll
+  for (int u = 0; u < CNT; ++u) {
+    const int i = tid + u * THREADS, px = i >> 3;
+    const int ty = px / (C3_W + 2), tx = px - ty * (C3_W + 2);
+    const int y = y0 - 1 + ty, x = x0 - 1 + tx;
+    int c = (i & 7) * 8;
+    if (vs) c += (2 * (y & 1) + (x & 1)) * 64;  // shuffle: slot of the coarse pixel
+    off[u] = i < TCH && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W
+                 ? (uint32_t)((((y >> vs) - yb) * (p.W >> vs) + ((x >> vs) - xb)) * p.ca + c) * 2u
+                 : BUF_OUT;
+  }
+  auto tile_load = [&](int cbase, u32x4(&v)[CNT]) {
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) v[u] = buf_ld16(src, off[u], cbase * 2);
+  };
+  auto tile_store = [&](int which, const u32x4(&v)[CNT]) {
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) {
+      const int i = tid + u * THREADS;
+      if (i < TCH)
+        *reinterpret_cast<u32x4*>(&tile[which][(i >> 3) * RW_PITCH + (i & 7) * 8]) = v[u];
+    }
+  };
+  // weights in fragment order: one contiguous 1 KB load per K step and M tile
+  bf16x8 W[3][6];
+  const auto wbuf = buf(p.w);
+  auto w_load = [&](int dy, int n0, int ch) {
+#pragma unroll
+      for (int s = 0; s < 6; ++s) {
+        const int ks = (dy * 3 + (s >> 1)) * (p.cin_p >> 5) + ch * 2;
+        W[dy][s] = __builtin_bit_cast(
+            bf16x8, buf_ld16(wbuf, lane * 16 + (s & 1) * 1024,
+                             (n0 + wn * 16) * p.kp * 2 + ks * 1024));
+      }
+  };
+  {
+    u32x4 v[CNT];
+    tile_load(0, v);
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy) w_load(dy, part * nper, 0);
+    tile_store(0, v);
+  }
+  __syncthreads();
+  const int nstep = nper / BN * nchunk;
+  f32x4 acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+ acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // this lane's pixels: column x0 + li, rows yo + r; its channels of a group start
+  // at nw (the wave's) + nl
+  const int yo = y0 + wr * R, nl = kq * 4, nw = wn * 16;
+  const int rows = min(max(p.H - yo, 0), R);  // rows inside the image
+  const size_t mo = ((size_t)b * p.H + min(yo, p.H - 1)) * p.W + x0;
+  const bool xin = x0 + li < p.W;
+  // a tensor of `stride` channels of `sz` bytes from the wave's first pixel and
+  // channel on, ending with its last row in the image, and the lane's offset in it
+  auto tbuf = [&](const void* base, int stride, int sz) {
+    return buf((const char*)base + (mo * stride + nw) * sz, (uint32_t)(rows * p.W * stride) * sz);
+  };
+  auto lane_off = [&](int stride, int sz) {
+    return xin ? (uint32_t)(li * stride + nl) * sz : BUF_OUT;
+  };
+  auto rows4 = [&](const float* a, int stride, f32x4(&v)[R]) {
+    const auto t = tbuf(a, stride, 4);
+    const uint32_t o = lane_off(stride, 4);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      v[r] = __builtin_bit_cast(f32x4, buf_ld16(t, o + r * (p.W * stride * 4)));
+  };
+  int n0 = part * nper, ch = 0;
+  for (int st = 0; st < nstep; ++st) {
+    const bool lastch = !MULTI || ch == nchunk - 1;
+    const bool more = st + 1 < nstep;
+    const int ch1 = lastch ? 0 : ch + 1, n1 = lastch ? n0 + BN : n0;  // the next step's
+    u32x4 v[CNT];
+    if (MULTI && more) tile_load(ch1 * 64, v);
+    // the epilogue's first inputs are on their way during the last slice
+    const RwEpi e = rw_epi<MODE>(p, be, n0);
+    f32x4 r1[R];
+    float bias[4];
+    if (lastch) {
+      if (e.a1) rows4(e.a1, e.st1, r1);
+      if (MODE == RW_FWD) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bias[q] = p.bias[n0 + nw + nl + q];
+      }
+    }
+    const uint16_t* tp = &tile[MULTI ? st & 1 : 0][((wr * R) * (C3_W + 2) + li) * RW_PITCH + kq * 8];
+    // operands of one input row: s = 2 dx + c / 32, the outer columns from LDS
+    bf16x8 P[6], Q[6];
+    auto row_load = [&](int i, bf16x8(&o)[6]) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        o[c] = ld8(tp + i * (C3_W + 2) * RW_PITCH + c * 32);
+        o[4 + c] = ld8(tp + (i * (C3_W + 2) + 2) * RW_PITCH + c * 32);
+      }
+    };
+    row_load(0, P);
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+      if (i + 1 < R + 2) row_load(i + 1, Q);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) P[2 + c] = rw_middle(P[c], P[4 + c]);
+#pragma unroll
+      for (int s = 0; s < 6; ++s)
+#pragma unroll
+        for (int dy = 2; dy >= 0; --dy) {
+          const int r = i - dy;
+          if (r < 0 || r >= R) continue;
+          acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[dy][s], P[s], acc[r], 0, 0, 0);
+        }
+      if (i >= R - 1 && more) w_load(i - (R - 1), n1, ch1);  // tap row i - R + 1 is done with
+#pragma unroll
+      for (int s = 0; s < 6; ++s) P[s] = Q[s];
+      // keep the LDS reads one row ahead: hoisted further they spill
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (MULTI && more) {
+      tile_store((st + 1) & 1, v);
+      __syncthreads();
+    }
+    if (lastch) {
+      // loads before stores: the outputs may alias the inputs for all the compiler knows
+      if (MODE == RW_FWD) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[r][q] += bias[q];
+        if (p.relu) {
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[r][q] = fmaxf(acc[r][q], 0.0f);
+        }
+      }
+      if (e.a1) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[r][q] = r1[r][q] + e.s1 * acc[r][q];
+      }
+#pragma unroll 1
+      for (int k = 0; k < 2; ++k) {
+        const float* a = k ? e.a3 : e.a2;
+        if (!a) continue;
+        f32x4 v2[R];
+        rows4(a, k ? e.st3 : e.st2, v2);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc[r][q] += v2[r][q];
+      }
+      if (MODE != RW_FWD && e.mask) {
+        u32x2 mk[R];
+        const auto t = tbuf(e.mask, e.stm, 2);
+        const uint32_t o = lane_off(e.stm, 2);
+#pragma unroll
+        for (int r = 0; r < R; ++r) mk[r] = buf_ld8(t, o + r * (p.W * e.stm * 2));
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (!pos_bf((uint16_t)(mk[r][q >> 1] >> (16 * (q & 1))))) acc[r][q] = 0.0f;
+      }
+      if (e.out_f) {
+        const auto t = tbuf(e.out_f, e.stf, 4);
+        const uint32_t o = lane_off(e.stf, 4);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          buf_st16(t, o + r * (p.W * e.stf * 4), __builtin_bit_cast(u32x4, acc[r]));
+      }
+      if (e.out_h) {
+        const auto t = tbuf(e.out_h, e.sth, 2);
+        const uint32_t o = lane_off(e.sth, 2);
+        const float sc = MODE == RW_DG ? e.out_h_scale : 1.0f;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          buf_st8(t, o + r * (p.W * e.sth * 2),
+                  u32x2{f2bf2(acc[r][0] * sc, acc[r][1] * sc),
+                        f2bf2(acc[r][2] * sc, acc[r][3] * sc)});
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    n0 = n1;
+    ch = ch1;
+  }
+}
+
+// Runs the conv on k_conv3_rw if it fits: 3x3 over cin_p = 64 n channels of a
+// plain view, or the 64 channels of a shuffle by 2; no padding in K or in the
+// output channels, and channel strides that the epilogue's vectors can take.
+// The output channels are split over nsplit blocks per tile.
+template <int R, int WR, int WN, int MODE>
+bool try_conv3_rw(const ConvArgs& a, int cout_p, int nsplit, hipStream_t st, const BwdEpi* be) {
+  const bool multi = a.cin_p > 64;
+  if (!a.frag || a.taps != 9 || (a.mode == VIEW_PLAIN && a.ca < a.cin_p) || a.cin_p % 64 || a.kp != 9 * a.cin_p ||
+      (a.mode != VIEW_PLAIN && (multi || a.c0 != 64 || a.r != 2)) || a.cout != cout_p ||
+      cout_p % (WN * 16 * nsplit))
+    return false;
+  // a tile's offsets fit 31 bits (images up to about 116,000 pixels wide)
+  if ((int64_t)(WR * R + 2) * a.W * RDG_DENSE * 4 >= (int64_t)BUF_OUT) return false;
+  if (MODE == RW_FWD && ((a.out_f && a.out_f_stride % 4) || (a.out_h && a.out_h_stride % 8)))
+    return false;
+  if (be && be->scale != 1.0f) return false;
+  if (MODE == RW_DG &&
+      (be->mode == EPI_PLAIN ? be->stride % 8 != 0 : be->mode != EPI_DENSE))
+    return false;
+  BwdEpi e;
+  if (be) e = *be;
+  else std::memset(&e, 0, sizeof e);
+  const dim3 grid((a.W + C3_W - 1) / C3_W, (a.H + WR * R - 1) / (WR * R), a.B * nsplit);
+  if (multi)
+    k_conv3_rw<R, WR, WN, true, MODE><<<grid, 64 * WR * WN, 0, st>>>(a, cout_p, nsplit, e);
+  else
+    k_conv3_rw<R, WR, WN, false, MODE><<<grid, 64 * WR * WN, 0, st>>>(a, cout_p, nsplit, e);
+  return true;
 }
 
 // One residual block of the trunk in one launch: for a 16 x 16 output tile,
@@ -511,14 +858,14 @@ __global__ __launch_bounds__(RB_THREADS) void k_res_block(ConvArgs pa, ConvArgs 
       if (ii < TCH) *reinterpret_cast<bf16x8*>(tile + (ii >> 3) * RB_PITCH + (ii & 7) * 8) = v[u];
     }
   }
-  // weights of chunk i: row n = i / (KP / 8), 16-byte chunk kc; LDS [kc][n][8]
+  // weights of chunk i (16 bytes, fragment order): row n, K chunk kc; LDS [kc][n][8]
   auto w_load = [&](const ConvArgs& p, int i) -> uint4 {
-    const int n = i / (RB_KP / 8), kc = i - n * (RB_KP / 8);
-    return *reinterpret_cast<const uint4*>(p.w + (size_t)n * p.kp + kc * 8);
+    return *reinterpret_cast<const uint4*>(p.w + (size_t)i * 8);
   };
   auto w_store = [&](int i, uint4 v) {
-    const int n = i / (RB_KP / 8), kc = i - n * (RB_KP / 8);
-    *reinterpret_cast<uint4*>(wts + (kc * RB_WPITCH + n) * 8) = v;
+    int n, k;
+    frag_order(i * 8, RB_KP, n, k);
+    *reinterpret_cast<uint4*>(wts + ((k >> 3) * RB_WPITCH + n) * 8) = v;
   };
   {
     uint4 v[WPT];
@@ -628,22 +975,13 @@ __global__ __launch_bounds__(RB_THREADS) void k_res_block(ConvArgs pa, ConvArgs 
 }
 
 // Runs the conv on k_conv3_lds<CINP, NT, TH> if its shape fits: cin_p == CINP,
-// or (CINP = 64) a multiple of it taken in chunks; packed K = 9 cin_p rounded up
-// to 32; cout_p a multiple of nsplit channel groups of 16 NT.  The output
-// channels are split over nsplit blocks per tile.
-template <int CINP, int NT, int TH, bool DG = false>
-bool try_conv3_lds(const ConvArgs& a, int cout_p, int nsplit, hipStream_t st,
-                   const BwdEpi* be = nullptr) {
-  const bool chunked = CINP == 64 && a.cin_p > CINP && a.cin_p % CINP == 0;
-  if ((a.cin_p != CINP && !chunked) || a.kp != (9 * a.cin_p + 31) / 32 * 32 ||
-      cout_p % (16 * NT * nsplit))
+// packed K = 9 cin_p rounded up to 32, cout_p a multiple of 16 NT.
+template <int CINP, int NT, int TH>
+bool try_conv3_lds(const ConvArgs& a, int cout_p, hipStream_t st) {
+  if (a.frag || a.cin_p != CINP || a.kp != (9 * a.cin_p + 31) / 32 * 32 || cout_p % (16 * NT))
     return false;
-  BwdEpi e;
-  if (be) e = *be;
-  else std::memset(&e, 0, sizeof e);
-  k_conv3_lds<CINP, NT, TH, DG><<<dim3((a.W + C3_W - 1) / C3_W, (a.H + TH - 1) / TH,
-                                       a.B * nsplit),
-                                  32 * TH, 0, st>>>(a, cout_p, nsplit, e);
+  k_conv3_lds<CINP, NT, TH><<<dim3((a.W + C3_W - 1) / C3_W, (a.H + TH - 1) / TH, a.B), 32 * TH, 0,
+                              st>>>(a, cout_p);
   return true;
 }
 
@@ -832,6 +1170,7 @@ __global__ __launch_bounds__(256) void k_prep_layers(int64_t nhr, int64_t nlr,
 // t = 0: wp[n][tap cin_p + c] = W[n][c][tap], the forward convs' B operand.
 // t = 1: wt[c][tap' cinp_t + n] = W[n][c][taps - 1 - tap'], the data-gradient
 // conv (flipped taps, input and output channels swapped).  Padding is zero.
+// Layers that run on k_conv3_rw are stored in fragment order, the others row by row.
 __global__ __launch_bounds__(256) void k_pack_all(const float* __restrict__ wm,
                                                   const PackJob* __restrict__ jobs, int njobs,
                                                   int64_t total, uint16_t* __restrict__ packed,
@@ -846,7 +1185,8 @@ __global__ __launch_bounds__(256) void k_pack_all(const float* __restrict__ wm,
   }
   const PackJob& J = jobs[lo];
   const int64_t e = i - J.begin;
-  const int row = (int)(e / J.kp), k = (int)(e % J.kp);
+  int row = (int)(e / J.kp), k = (int)(e % J.kp);
+  if (J.frag) frag_order((int)e, J.kp, row, k);
   const int tap = k / J.cinp, col = k % J.cinp;
   const int taps = J.ksz * J.ksz;
   const float* w = wm + J.w_off;
@@ -1220,15 +1560,12 @@ inline void count_conv(int kind) { g_conv_launches[kind].fetch_add(1, std::memor
 }  // namespace
 
 void launch_dgrad(const ConvArgs& a, const BwdEpi& e, int cout_p, hipStream_t st) {
-  // 3x3 data gradients with a plain backward on the LDS conv (the same tile
-  // plans as the forward convs)
-  if (e.mode == EPI_PLAIN && a.taps == 9 && a.mode == VIEW_PLAIN && a.ca >= a.cin_p &&
-      cout_p >= 64 && a.cin_p % 64 == 0) {
-    const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
-    if (tiles < conv_small_tiles() && try_conv3_lds<64, 2, 8, true>(a, cout_p, cout_p / 32, st, &e))
-      return count_conv(8);
-    if (try_conv3_lds<64, 4, 16, true>(a, cout_p, 1, st, &e)) return count_conv(9);
-  }
+  // 3x3 data gradients of 64-channel slices: the same kernel and tile plans as
+  // the forward convs
+  const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
+  if (tiles < conv_small_tiles() && try_conv3_rw<4, 2, 2, RW_DG>(a, cout_p, cout_p / 32, st, &e))
+    return count_conv(8);
+  if (try_conv3_rw<8, 2, 4, RW_DG>(a, cout_p, 1, st, &e)) return count_conv(9);
   const int64_t M = (int64_t)a.B * a.H * a.W;
   const unsigned gx = cdiv64(M, 128);
   if (cout_p >= 64) {
@@ -1298,14 +1635,15 @@ void launch_adam(float* w, const float* g, float* m, float* v, int64_t n, float 
   k_adam<<<cdiv64(n, 256), 256, 0, st>>>(w, g, m, v, n, lr, b1, b2, eps, c1, c2);
 }
 
-// Tile plan of a 3x3 conv on k_conv3_lds: 16 x 16 tiles of 8 waves with all
-// output channels per block; when such tiles are fewer than
-// mrs_tuning.conv_small_tiles (default 128: half of the 256 CUs), 16 x 8 tiles
-// of 4 waves with the output channels split over blocks of 32 (two fit a CU at
-// once).  Both plans sum every output in the same K order, so the choice
-// changes speed only.  Measured: the 720p LR trunk (240 tiles) is 18% faster
-// on the large tiles, the x8 network on a 1024 x 1024 image (64 tiles) 19%
-// faster on the small ones.
+// Tile plan of a 3x3 conv on k_conv3_rw: 16 x 16 tiles of 8 waves with 64 output
+// channels at a time; when such tiles are fewer than mrs_tuning.conv_small_tiles
+// (default 128: half of the 256 CUs), 16 x 8 tiles of 4 waves with the output
+// channels split over blocks of 32 (two fit a CU at once).  Both plans sum every
+// output in the same K order, so the choice changes speed only.  Measured, small
+// against large plan, 64 / 128 / 256 input channels: 40 tiles 4.8 / 6.4 / 10.1
+// against 7.7 / 10.7 / 19.7 us, 120 tiles 6.1 / 8.9 / 15.9 against 7.9 / 11.0 /
+// 21.4, 160 tiles 7.1 / 13.2 / 23.2 against 8.0 / 11.2 / 22.5, 240 tiles (the 720p
+// LR image) 10.3 / 16.6 / 29.7 against 8.5 / 11.8 / 24.2.
 
 void conv_launch_counts(int64_t* out, bool reset) {
   for (int i = 0; i < MRS_NUM_CONV_KINDS; ++i)
@@ -1330,16 +1668,16 @@ void launch_conv(const ConvArgs& a, int cout_p, hipStream_t st) {
   if (a.taps == 9 && a.mode != VIEW_CONCAT_UNSHUFFLE &&
       (a.mode != VIEW_PLAIN || a.ca >= a.cin_p)) {
     const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
-    if (cout_p >= 64 && a.cin_p % 64 == 0 && tiles < conv_small_tiles() &&
-        try_conv3_lds<64, 2, 8>(a, cout_p, cout_p / 32, st))
+    if (tiles < conv_small_tiles() &&
+        try_conv3_rw<4, 2, 2, RW_FWD>(a, cout_p, cout_p / 32, st, nullptr))
       return count_conv(0);
     if (cout_p >= 64) {
-      if (try_conv3_lds<64, 4, 16>(a, cout_p, 1, st)) return count_conv(1);
-      if (try_conv3_lds<16, 4, 16>(a, cout_p, 1, st)) return count_conv(2);
-      if (try_conv3_lds<8, 4, 16>(a, cout_p, 1, st)) return count_conv(3);
+      if (try_conv3_rw<8, 2, 4, RW_FWD>(a, cout_p, 1, st, nullptr)) return count_conv(1);
+      if (try_conv3_lds<16, 4, 16>(a, cout_p, st)) return count_conv(2);
+      if (try_conv3_lds<8, 4, 16>(a, cout_p, st)) return count_conv(3);
     } else {
-      if (try_conv3_lds<80, 1, 16>(a, cout_p, 1, st)) return count_conv(4);
-      if (try_conv3_lds<64, 1, 16>(a, cout_p, 1, st)) return count_conv(5);
+      if (try_conv3_lds<80, 1, 16>(a, cout_p, st)) return count_conv(4);
+      if (try_conv3_lds<64, 1, 16>(a, cout_p, st)) return count_conv(5);
     }
   }
   const int64_t M = (int64_t)a.B * a.H * a.W;

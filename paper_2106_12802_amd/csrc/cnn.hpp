@@ -30,7 +30,8 @@ struct ConvArgs {
   int cin_p;    // channels per tap as laid out in K (multiple of 8)
   int taps;     // 1 or 9
   int kp;       // padded K (multiple of 32)
-  const uint16_t* w;  // packed BF16 [cout_p][kp]
+  const uint16_t* w;  // packed BF16 [cout_p][kp] (row by row, or in fragment order)
+  int frag;           // the weights are in fragment order
   const float* bias;  // [cout]
   int cout;
   int relu;
@@ -110,6 +111,9 @@ struct NetLayer {
   // data-gradient conv: inputs dY (cinp_t channels stored), outputs cin channels
   int cinp_t, kp_t, coutp_t;
   int64_t pkt_off;       // offset in the packed transposed weights (-1: none)
+  // packed in fragment order: 3x3 convs from and to multiples of 64 channels
+  bool frag() const { return k == 3 && cin_p % 64 == 0 && cout % 64 == 0; }
+  bool frag_t() const { return k == 3 && cinp_t > 0 && cinp_t % 64 == 0 && cin % 64 == 0; }
 };
 
 // One layer's BF16 packing job of k_pack_all: the forward layout (t = 0) or
@@ -121,6 +125,7 @@ struct PackJob {
   int cout, cin, ksz;
   int cinp, kp, coutp;  // padded layout of the output
   int t;
+  int frag;  // fragment order
 };
 
 constexpr int NET_FEAT = 64;

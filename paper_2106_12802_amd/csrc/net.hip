@@ -195,6 +195,7 @@ ConvArgs base_args(const mrs_net* net, const NetLayer& L, int B, int H, int W) {
   a.taps = L.k * L.k;
   a.kp = L.kp;
   a.w = net->d_packed + L.pk_off;
+  a.frag = L.frag();
   a.bias = net->d_master + L.b_off;
   a.cout = L.cout;
   a.res_scale = 1.0f;
@@ -337,6 +338,7 @@ mrs_status ensure_pack_jobs(mrs_net* net) {
       j.kp = t ? L.kp_t : L.kp;
       j.coutp = t ? L.coutp_t : L.cout_p;
       j.t = t;
+      j.frag = t ? L.frag_t() : L.frag();
       jobs.push_back(j);
       at += (int64_t)j.coutp * j.kp;
     }
@@ -430,6 +432,7 @@ ConvArgs tconv_args(const mrs_net* net, const NetLayer& L, int B, int H, int W,
   a.taps = L.k * L.k;
   a.kp = L.kp_t;
   a.w = net->d_packed_t + L.pkt_off;
+  a.frag = L.frag_t();
   a.bias = net->d_master + L.b_off;  // unused by the data-gradient epilogue
   a.cout = L.cin;
   a.res_scale = 1.0f;
