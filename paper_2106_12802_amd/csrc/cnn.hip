@@ -22,6 +22,7 @@
 // loads the 8 consecutive input channels (one 16-byte load) of pixel l%16 of
 // each row tile for K chunk l/16, and the matching 8 weights of output channel
 // l%16 of each column tile.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -574,6 +575,162 @@ __device__ __forceinline__ bf16x8 rw_middle(bf16x8 left, bf16x8 right) {
                             make_uint4(one(l.x, r.x), one(l.y, r.y), one(l.z, r.z), one(l.w, r.w)));
 }
 
+// One wave's sweep over R + 2 rows of an LDS tile TW pixels wide (tp: this lane's
+// operand at the first row): acc[r] gets rows r .. r + 2 through the weights W[dy],
+// s = 2 dx + c / 32.  after_row(i) runs when input row i is done with.
+template <int R, int TW, class F>
+__device__ __forceinline__ void rw_sweep(const uint16_t* tp, bf16x8 (&W)[3][6], f32x4 (&acc)[R],
+                                         F after_row) {
+  bf16x8 P[6], Q[6];
+  auto row_load = [&](int i, bf16x8(&o)[6]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      o[c] = ld8(tp + i * TW * RW_PITCH + c * 32);
+      o[4 + c] = ld8(tp + (i * TW + 2) * RW_PITCH + c * 32);
+    }
+  };
+  row_load(0, P);
+#pragma unroll
+  for (int i = 0; i < R + 2; ++i) {
+    if (i + 1 < R + 2) row_load(i + 1, Q);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) P[2 + c] = rw_middle(P[c], P[4 + c]);
+#pragma unroll
+    for (int s = 0; s < 6; ++s)
+#pragma unroll
+      for (int dy = 2; dy >= 0; --dy) {
+        const int r = i - dy;
+        if (r < 0 || r >= R) continue;
+        acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[dy][s], P[s], acc[r], 0, 0, 0);
+      }
+    after_row(i);
+#pragma unroll
+    for (int s = 0; s < 6; ++s) P[s] = Q[s];
+    // keep the LDS reads one row ahead: hoisted further they spill
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Weights of tap row dy of channel slice ch (64 channels) for the 16 output
+// channels from n on.
+__device__ __forceinline__ void rw_weights(const ConvArgs& p, int dy, int n, int ch, int lane,
+                                           bf16x8 (&W)[6]) {
+  const auto w = buf(p.w);
+#pragma unroll
+  for (int s = 0; s < 6; ++s) {
+    const int ks = (dy * 3 + (s >> 1)) * (p.cin_p >> 5) + ch * 2;
+    W[s] = __builtin_bit_cast(bf16x8,
+                              buf_ld16(w, lane * 16 + (s & 1) * 1024, n * p.kp * 2 + ks * 1024));
+  }
+}
+
+// The part of a conv's output that one wave holds: R rows of 16 pixels from
+// (x0, yo) of image b, lane (li, kq) with 4 channels from nw + 4 kq of pixel li.
+template <int R>
+struct RwOut {
+  size_t mo;   // the wave's first pixel
+  int W, nw, rows, li, kq;
+  bool xin;
+  __device__ __forceinline__ RwOut(const ConvArgs& p, int b, int yo, int x0, int nw_, int li_,
+                                   int kq_)
+      : W(p.W), nw(nw_), li(li_), kq(kq_) {
+    rows = min(max(p.H - yo, 0), R);  // rows inside the image
+    mo = ((size_t)b * p.H + min(yo, p.H - 1)) * p.W + x0;
+    xin = x0 + li < p.W;
+  }
+  // a tensor of `stride` channels of `sz` bytes from the wave's first pixel and
+  // channel on, ending with its last row in the image, and the lane's offset in it
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t tbuf(const void* base, int stride,
+                                                         int sz) const {
+    return buf((const char*)base + (mo * stride + nw) * sz, (uint32_t)(rows * W * stride) * sz);
+  }
+  __device__ __forceinline__ uint32_t off(int stride, int sz) const {
+    return xin ? (uint32_t)(li * stride + kq * 4) * sz : BUF_OUT;
+  }
+  __device__ __forceinline__ void load(const float* a, int stride, f32x4 (&v)[R]) const {
+    const auto t = tbuf(a, stride, 4);
+    const uint32_t o = off(stride, 4);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      v[r] = __builtin_bit_cast(f32x4, buf_ld16(t, o + r * (W * stride * 4)));
+  }
+};
+
+// The epilogue's first inputs, loaded ahead: the first tensor to add and the bias.
+template <int R, int MODE>
+__device__ __forceinline__ void rw_epi_load(const ConvArgs& p, const RwEpi& e, const RwOut<R>& o,
+                                            int n0, f32x4 (&r1)[R], float (&bias)[4]) {
+  if (e.a1) o.load(e.a1, e.st1, r1);
+  if (MODE == RW_FWD) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bias[q] = p.bias[n0 + o.nw + o.kq * 4 + q];
+  }
+}
+
+// Loads before stores: the outputs may alias the inputs for all the compiler knows.
+template <int R, int MODE>
+__device__ __forceinline__ void rw_epilogue(const ConvArgs& p, const RwEpi& e, const RwOut<R>& o,
+                                            const f32x4 (&r1)[R], const float (&bias)[4],
+                                            f32x4 (&acc)[R]) {
+  if (MODE == RW_FWD) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[r][q] += bias[q];
+    if (p.relu) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[r][q] = fmaxf(acc[r][q], 0.0f);
+    }
+  }
+  if (e.a1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[r][q] = r1[r][q] + e.s1 * acc[r][q];
+  }
+#pragma unroll 1
+  for (int k = 0; k < 2; ++k) {
+    const float* a = k ? e.a3 : e.a2;
+    if (!a) continue;
+    f32x4 v[R];
+    o.load(a, k ? e.st3 : e.st2, v);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[r][q] += v[r][q];
+  }
+  if (MODE != RW_FWD && e.mask) {
+    u32x2 mk[R];
+    const auto t = o.tbuf(e.mask, e.stm, 2);
+    const uint32_t lo = o.off(e.stm, 2);
+#pragma unroll
+    for (int r = 0; r < R; ++r) mk[r] = buf_ld8(t, lo + r * (o.W * e.stm * 2));
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (!pos_bf((uint16_t)(mk[r][q >> 1] >> (16 * (q & 1))))) acc[r][q] = 0.0f;
+  }
+  if (e.out_f) {
+    const auto t = o.tbuf(e.out_f, e.stf, 4);
+    const uint32_t lo = o.off(e.stf, 4);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      buf_st16(t, lo + r * (o.W * e.stf * 4), __builtin_bit_cast(u32x4, acc[r]));
+  }
+  if (e.out_h) {
+    const auto t = o.tbuf(e.out_h, e.sth, 2);
+    const uint32_t lo = o.off(e.sth, 2);
+    const float sc = MODE == RW_DG ? e.out_h_scale : 1.0f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      buf_st8(t, lo + r * (o.W * e.sth * 2), u32x2{f2bf2(acc[r][0] * sc, acc[r][1] * sc),
+                                                   f2bf2(acc[r][2] * sc, acc[r][3] * sc)});
+  }
+}
+
 template <int R, int WR, int WN, bool MULTI, int MODE>
 __global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_p, int nsplit,
                                                            BwdEpi be) {
@@ -617,52 +774,21 @@ __global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_
         *reinterpret_cast<u32x4*>(&tile[which][(i >> 3) * RW_PITCH + (i & 7) * 8]) = v[u];
     }
   };
-  // weights in fragment order: one contiguous 1 KB load per K step and M tile
   bf16x8 W[3][6];
-  const auto wbuf = buf(p.w);
-  auto w_load = [&](int dy, int n0, int ch) {
-#pragma unroll
-      for (int s = 0; s < 6; ++s) {
-        const int ks = (dy * 3 + (s >> 1)) * (p.cin_p >> 5) + ch * 2;
-        W[dy][s] = __builtin_bit_cast(
-            bf16x8, buf_ld16(wbuf, lane * 16 + (s & 1) * 1024,
-                             (n0 + wn * 16) * p.kp * 2 + ks * 1024));
-      }
-  };
+  const int nw = wn * 16;  // the wave's channels within a group of BN
   {
     u32x4 v[CNT];
     tile_load(0, v);
 #pragma unroll
-    for (int dy = 0; dy < 3; ++dy) w_load(dy, part * nper, 0);
+    for (int dy = 0; dy < 3; ++dy) rw_weights(p, dy, part * nper + nw, 0, lane, W[dy]);
     tile_store(0, v);
   }
   __syncthreads();
   const int nstep = nper / BN * nchunk;
   f32x4 acc[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
- acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // this lane's pixels: column x0 + li, rows yo + r; its channels of a group start
-  // at nw (the wave's) + nl
-  const int yo = y0 + wr * R, nl = kq * 4, nw = wn * 16;
-  const int rows = min(max(p.H - yo, 0), R);  // rows inside the image
-  const size_t mo = ((size_t)b * p.H + min(yo, p.H - 1)) * p.W + x0;
-  const bool xin = x0 + li < p.W;
-  // a tensor of `stride` channels of `sz` bytes from the wave's first pixel and
-  // channel on, ending with its last row in the image, and the lane's offset in it
-  auto tbuf = [&](const void* base, int stride, int sz) {
-    return buf((const char*)base + (mo * stride + nw) * sz, (uint32_t)(rows * p.W * stride) * sz);
-  };
-  auto lane_off = [&](int stride, int sz) {
-    return xin ? (uint32_t)(li * stride + nl) * sz : BUF_OUT;
-  };
-  auto rows4 = [&](const float* a, int stride, f32x4(&v)[R]) {
-    const auto t = tbuf(a, stride, 4);
-    const uint32_t o = lane_off(stride, 4);
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      v[r] = __builtin_bit_cast(f32x4, buf_ld16(t, o + r * (p.W * stride * 4)));
-  };
+  for (int r = 0; r < R; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const RwOut<R> out(p, b, y0 + wr * R, x0, nw, li, kq);
   int n0 = part * nper, ch = 0;
   for (int st = 0; st < nstep; ++st) {
     const bool lastch = !MULTI || ch == nchunk - 1;
@@ -674,107 +800,18 @@ __global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_
     const RwEpi e = rw_epi<MODE>(p, be, n0);
     f32x4 r1[R];
     float bias[4];
-    if (lastch) {
-      if (e.a1) rows4(e.a1, e.st1, r1);
-      if (MODE == RW_FWD) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bias[q] = p.bias[n0 + nw + nl + q];
-      }
-    }
-    const uint16_t* tp = &tile[MULTI ? st & 1 : 0][((wr * R) * (C3_W + 2) + li) * RW_PITCH + kq * 8];
-    // operands of one input row: s = 2 dx + c / 32, the outer columns from LDS
-    bf16x8 P[6], Q[6];
-    auto row_load = [&](int i, bf16x8(&o)[6]) {
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        o[c] = ld8(tp + i * (C3_W + 2) * RW_PITCH + c * 32);
-        o[4 + c] = ld8(tp + (i * (C3_W + 2) + 2) * RW_PITCH + c * 32);
-      }
-    };
-    row_load(0, P);
-#pragma unroll
-    for (int i = 0; i < R + 2; ++i) {
-      if (i + 1 < R + 2) row_load(i + 1, Q);
-#pragma unroll
-      for (int c = 0; c < 2; ++c) P[2 + c] = rw_middle(P[c], P[4 + c]);
-#pragma unroll
-      for (int s = 0; s < 6; ++s)
-#pragma unroll
-        for (int dy = 2; dy >= 0; --dy) {
-          const int r = i - dy;
-          if (r < 0 || r >= R) continue;
-          acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[dy][s], P[s], acc[r], 0, 0, 0);
-        }
-      if (i >= R - 1 && more) w_load(i - (R - 1), n1, ch1);  // tap row i - R + 1 is done with
-#pragma unroll
-      for (int s = 0; s < 6; ++s) P[s] = Q[s];
-      // keep the LDS reads one row ahead: hoisted further they spill
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    if (lastch) rw_epi_load<R, MODE>(p, e, out, n0, r1, bias);
+    rw_sweep<R, C3_W + 2>(
+        &tile[MULTI ? st & 1 : 0][((wr * R) * (C3_W + 2) + li) * RW_PITCH + kq * 8], W, acc,
+        [&](int i) {  // tap row i - R + 1 is done with: the next step's weights
+          if (i >= R - 1 && more) rw_weights(p, i - (R - 1), n1 + nw, ch1, lane, W[i - (R - 1)]);
+        });
     if (MULTI && more) {
       tile_store((st + 1) & 1, v);
       __syncthreads();
     }
     if (lastch) {
-      // loads before stores: the outputs may alias the inputs for all the compiler knows
-      if (MODE == RW_FWD) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[r][q] += bias[q];
-        if (p.relu) {
-#pragma unroll
-          for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[r][q] = fmaxf(acc[r][q], 0.0f);
-        }
-      }
-      if (e.a1) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[r][q] = r1[r][q] + e.s1 * acc[r][q];
-      }
-#pragma unroll 1
-      for (int k = 0; k < 2; ++k) {
-        const float* a = k ? e.a3 : e.a2;
-        if (!a) continue;
-        f32x4 v2[R];
-        rows4(a, k ? e.st3 : e.st2, v2);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[r][q] += v2[r][q];
-      }
-      if (MODE != RW_FWD && e.mask) {
-        u32x2 mk[R];
-        const auto t = tbuf(e.mask, e.stm, 2);
-        const uint32_t o = lane_off(e.stm, 2);
-#pragma unroll
-        for (int r = 0; r < R; ++r) mk[r] = buf_ld8(t, o + r * (p.W * e.stm * 2));
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (!pos_bf((uint16_t)(mk[r][q >> 1] >> (16 * (q & 1))))) acc[r][q] = 0.0f;
-      }
-      if (e.out_f) {
-        const auto t = tbuf(e.out_f, e.stf, 4);
-        const uint32_t o = lane_off(e.stf, 4);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          buf_st16(t, o + r * (p.W * e.stf * 4), __builtin_bit_cast(u32x4, acc[r]));
-      }
-      if (e.out_h) {
-        const auto t = tbuf(e.out_h, e.sth, 2);
-        const uint32_t o = lane_off(e.sth, 2);
-        const float sc = MODE == RW_DG ? e.out_h_scale : 1.0f;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-          buf_st8(t, o + r * (p.W * e.sth * 2),
-                  u32x2{f2bf2(acc[r][0] * sc, acc[r][1] * sc),
-                        f2bf2(acc[r][2] * sc, acc[r][3] * sc)});
-      }
+      rw_epilogue<R, MODE>(p, e, out, r1, bias, acc);
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -815,163 +852,112 @@ bool try_conv3_rw(const ConvArgs& a, int cout_p, int nsplit, hipStream_t st, con
 
 // One residual block of the trunk in one launch: for a 16 x 16 output tile,
 // y = res + res_scale convB(ReLU(convA(x))) (+ res2), convA and convB 3x3 convs
-// of 64 channels.  The block stages x with a halo of 2, computes convA on the
-// 18 x 18 pixels convB needs (halo recompute: 21 M tiles of 16 pixels instead
-// of 16), keeps ReLU(convA) as BF16 in LDS -- zero outside the image, which is
-// convB's zero padding -- and runs convB on it; convB's weights are loaded into
-// registers during convA.  The intermediate is rounded to BF16 as the two-conv
-// path stores it and every output element sums its K in the same order, so the
-// result is bitwise that of convA then convB as two k_conv3_lds launches, less
-// one launch and the intermediate's round trip through memory.
+// of 64 channels, both as in k_conv3_rw (weights in registers, 8 waves of 8 or 9
+// rows x 16 channels).  The block stages x with a halo of 2 and computes convA on
+// the 18 x 18 pixels convB needs: 16 columns of them by the row sweep, the last
+// two as pixel groups of 8 rows x 2 columns (19 M tiles in place of 16), whose
+// MFMAs run between the sweep's.  ReLU(convA) goes to LDS as BF16 -- zero outside
+// the image, which is convB's zero padding.  ConvB's weights are loaded as convA's
+// last rows release the registers, the FP32 residual during convB.  The
+// intermediate is rounded to BF16 as the two-conv path stores it and every output
+// element sums its K in the same order, so the result is bitwise that of convA
+// then convB as two launches, less one launch and the intermediate's round trip.
+// Measured (720p LR image, 240 tiles): 27.0 -> 19.9 us a launch (with both operands
+// of every MFMA read from LDS: 0.75 reads each); the MFMA time is 4.7 us.
 constexpr int RB_T = 16;          // output tile
 constexpr int RB_IN = RB_T + 4;   // input tile rows / columns (halo of both convs)
 constexpr int RB_MID = RB_T + 2;  // convA outputs = convB's input tile
 constexpr int RB_C = 64;          // channels in and out of both convs
-constexpr int RB_PITCH = RB_C + 8;
 constexpr int RB_KP = 9 * RB_C;
-constexpr int RB_WPITCH = RB_C + 1;  // 16-byte chunks per weight row
-constexpr int RB_MIDT = (RB_MID * RB_MID + 15) / 16;  // convA's M tiles (21)
-constexpr int RB_THREADS = 512;                      // 8 waves
-constexpr int RB_MQ = (RB_MIDT + 7) / 8;             // convA M tiles per wave (3)
+constexpr int RB_THREADS = 512;   // 8 waves: 2 halves of the rows x 4 channel tiles
+constexpr int RB_RA = RB_MID / 2, RB_RB = RB_T / 2;  // rows per wave of convA and convB
 
 __global__ __launch_bounds__(RB_THREADS) void k_res_block(ConvArgs pa, ConvArgs pb) {
-  __shared__ __attribute__((aligned(16))) uint16_t tile[RB_IN * RB_IN * RB_PITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t wts[(RB_KP / 8) * RB_WPITCH * 8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __attribute__((aligned(16))) uint16_t tile[RB_IN * RB_IN * RW_PITCH];
+  __shared__ __attribute__((aligned(16))) uint16_t mid[RB_MID * RB_MID * RW_PITCH];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kq = lane >> 4, li = lane & 15;
+  const int wr = wave & 1, nw = (wave >> 1) * 16;
   const int x0 = blockIdx.x * RB_T, y0 = blockIdx.y * RB_T, b = blockIdx.z;
-  constexpr int TCH = RB_IN * RB_IN * (RB_C / 8), WCH = RB_C * (RB_KP / 8);
-  constexpr int WPT = WCH / RB_THREADS;  // weight chunks per thread (9)
-  static_assert(WCH % RB_THREADS == 0, "weights split evenly over the threads");
-  // input tile, 4 chunks in flight per thread
-  for (int i = tid; i < TCH; i += 4 * RB_THREADS) {
-    bf16x8 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int ii = i + u * RB_THREADS, px = ii >> 3, c = (ii & 7) * 8;
-      const int ty = px / RB_IN, tx = px - ty * RB_IN;
-      v[u] = ii < TCH ? view_chunk(pa, b, y0 - 2 + ty, x0 - 2 + tx, c) : zero8();
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int ii = i + u * RB_THREADS;
-      if (ii < TCH) *reinterpret_cast<bf16x8*>(tile + (ii >> 3) * RB_PITCH + (ii & 7) * 8) = v[u];
-    }
-  }
-  // weights of chunk i (16 bytes, fragment order): row n, K chunk kc; LDS [kc][n][8]
-  auto w_load = [&](const ConvArgs& p, int i) -> uint4 {
-    return *reinterpret_cast<const uint4*>(p.w + (size_t)i * 8);
-  };
-  auto w_store = [&](int i, uint4 v) {
-    int n, k;
-    frag_order(i * 8, RB_KP, n, k);
-    *reinterpret_cast<uint4*>(wts + ((k >> 3) * RB_WPITCH + n) * 8) = v;
-  };
+  constexpr int TCH = RB_IN * RB_IN * (RB_C / 8), CNT = (TCH + RB_THREADS - 1) / RB_THREADS;
+  bf16x8 W[3][6];
   {
-    uint4 v[WPT];
+    const int yb = max(y0 - 2, 0), xb = max(x0 - 2, 0);
+    const auto src = buf(pa.a + (((size_t)b * pa.H + yb) * pa.W + xb) * pa.ca);
+    u32x4 v[CNT];
 #pragma unroll
-    for (int u = 0; u < WPT; ++u) v[u] = w_load(pa, tid + u * RB_THREADS);
+    for (int u = 0; u < CNT; ++u) {
+      const int i = tid + u * RB_THREADS, px = i >> 3;
+      const int ty = px / RB_IN, tx = px - ty * RB_IN;
+      const int y = y0 - 2 + ty, x = x0 - 2 + tx;
+      v[u] = buf_ld16(src, i < TCH && (unsigned)y < (unsigned)pa.H && (unsigned)x < (unsigned)pa.W
+                               ? (uint32_t)(((y - yb) * pa.W + (x - xb)) * pa.ca + (i & 7) * 8) * 2u
+                               : BUF_OUT);
+    }
 #pragma unroll
-    for (int u = 0; u < WPT; ++u) w_store(tid + u * RB_THREADS, v[u]);
+    for (int dy = 0; dy < 3; ++dy) rw_weights(pa, dy, nw, 0, lane, W[dy]);
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) {
+      const int i = tid + u * RB_THREADS;
+      if (i < TCH) *reinterpret_cast<u32x4*>(tile + (i >> 3) * RW_PITCH + (i & 7) * 8) = v[u];
+    }
+  }
+  float bias[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) bias[q] = pa.bias[nw + kq * 4 + q];
+  __syncthreads();
+  {
+    // convA.  Columns 16 and 17: lane li holds pixel (er + li / 2, 16 + li % 2) of
+    // group g; half wr takes rows 8 wr .. 8 wr + 7 (g = 0), half 1 also rows 16, 17
+    f32x4 acc[RB_RA], ex[2];
+#pragma unroll
+    for (int r = 0; r < RB_RA; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    ex[0] = ex[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int er0 = 8 * wr + (li >> 1), er1 = RB_T + ((li >> 1) & 1), ec = RB_T + (li & 1);
+    const uint16_t* e0 = tile + (er0 * RB_IN + ec) * RW_PITCH + kq * 8;
+    const uint16_t* e1 = tile + (er1 * RB_IN + ec) * RW_PITCH + kq * 8;
+    rw_sweep<RB_RA, RB_IN>(
+        tile + (wr * RB_RA * RB_IN + li) * RW_PITCH + kq * 8, W, acc, [&](int i) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {  // K steps 2 i and 2 i + 1 of the last two columns
+            const int t = (2 * i + h) / 2, c = h;  // tap, channel half
+            if (t >= 9) continue;
+            const int dy = t / 3, dx = t - dy * 3, o = (dy * RB_IN + dx) * RW_PITCH + c * 32;
+            ex[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[dy][2 * dx + c], ld8(e0 + o), ex[0],
+                                                            0, 0, 0);
+            if (wr)
+              ex[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[dy][2 * dx + c], ld8(e1 + o),
+                                                              ex[1], 0, 0, 0);
+          }
+          if (i >= RB_RA - 1) rw_weights(pb, i - (RB_RA - 1), nw, 0, lane, W[i - (RB_RA - 1)]);
+        });
+    // ReLU(convA + bias) as BF16, zero outside the image
+    auto put = [&](const f32x4& a, int iy, int ix) {
+      const int y = y0 - 1 + iy, x = x0 - 1 + ix;
+      const bool in = (unsigned)y < (unsigned)pa.H && (unsigned)x < (unsigned)pa.W;
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = in ? fmaxf(a[q] + bias[q], 0.0f) : 0.0f;
+      *reinterpret_cast<u32x2*>(mid + (iy * RB_MID + ix) * RW_PITCH + nw + kq * 4) =
+          u32x2{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
+    };
+#pragma unroll
+    for (int r = 0; r < RB_RA; ++r) put(acc[r], wr * RB_RA + r, li);
+    put(ex[0], er0, ec);
+    if (wr && li < 4) put(ex[1], er1, ec);
   }
   __syncthreads();
-  // convB's weights, in flight while convA runs
-  uint4 wb[WPT];
+  // convB on the 16 x 16 tile
+  f32x4 acc[RB_RB], r1[RB_RB];
 #pragma unroll
-  for (int u = 0; u < WPT; ++u) wb[u] = w_load(pb, tid + u * RB_THREADS);
-  // convA: wave w takes M tiles w, w + 8, w + 16 of the 18 x 18 intermediate
-  // pixels in row-major order; lane li holds pixel 16 t + li of the A operand
-  f32x4 acc[RB_MQ][4];
-  int pofs[RB_MQ];
-#pragma unroll
-  for (int q = 0; q < RB_MQ; ++q) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[q][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int pix = 16 * (wave + 8 * q) + li;
-    const int iy = pix / RB_MID, ix = pix - iy * RB_MID;
-    pofs[q] = pix < RB_MID * RB_MID ? (iy * RB_IN + ix) * RB_PITCH : -1;
-  }
-  for (int ks = 0; ks < RB_KP; ks += 32) {
-    const int k = ks + kq * 8;
-    const int tap = k / RB_C, c = k - tap * RB_C;
-    const int dy = tap / 3, dx = tap - dy * 3;
-    const int tofs = (dy * RB_IN + dx) * RB_PITCH + c;
-    bf16x8 Bv[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Bv[j] = ld8(wts + (((ks >> 3) + kq) * RB_WPITCH + j * 16 + li) * 8);
-#pragma unroll
-    for (int q = 0; q < RB_MQ; ++q) {
-      if (wave + 8 * q >= RB_MIDT) continue;  // wave-uniform
-      const bf16x8 A = pofs[q] >= 0 ? ld8(tile + pofs[q] + tofs) : zero8();
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Bv[j], acc[q][j], 0, 0, 0);
-    }
-  }
-  // ReLU(convA + bias) as BF16, zero outside the image and past the 18 x 18
-  uint16_t hv[RB_MQ][4][4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float bias = pa.bias[j * 16 + li];
-#pragma unroll
-    for (int q = 0; q < RB_MQ; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int pix = 16 * (wave + 8 * q) + kq * 4 + v;
-        const int iy = pix / RB_MID, ix = pix - iy * RB_MID;
-        const int y = y0 - 1 + iy, x = x0 - 1 + ix;
-        const bool in = pix < RB_MID * RB_MID && y >= 0 && y < pa.H && x >= 0 && x < pa.W;
-        hv[q][j][v] = in ? f2bf(fmaxf(acc[q][j][v] + bias, 0.0f)) : (uint16_t)0;
-      }
-  }
-  __syncthreads();  // convA's operands are no longer read
-#pragma unroll
-  for (int q = 0; q < RB_MQ; ++q) {
-    if (wave + 8 * q >= RB_MIDT) continue;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int pix = 16 * (wave + 8 * q) + kq * 4 + v;
-      if (pix >= RB_MID * RB_MID) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) tile[pix * RB_PITCH + j * 16 + li] = hv[q][j][v];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < WPT; ++u) w_store(tid + u * RB_THREADS, wb[u]);
-  __syncthreads();
-  // convB on the 16 x 16 tile: wave w computes rows 2w and 2w + 1
-  f32x4 acc2[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc2[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int ks = 0; ks < RB_KP; ks += 32) {
-    const int k = ks + kq * 8;
-    const int tap = k / RB_C, c = k - tap * RB_C;
-    const int dy = tap / 3, dx = tap - dy * 3;
-    bf16x8 A[2], Bv[4];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-      A[r] = ld8(tile + ((2 * wave + r + dy) * RB_MID + li + dx) * RB_PITCH + c);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Bv[j] = ld8(wts + (((ks >> 3) + kq) * RB_WPITCH + j * 16 + li) * 8);
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc2[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[r], Bv[j], acc2[r][j], 0, 0, 0);
-  }
-  int64_t m[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int y = y0 + 2 * wave + r, x = x0 + kq * 4 + v;
-      m[r][v] = (y < pb.H && x < pb.W) ? ((int64_t)b * pb.H + y) * pb.W + x : -1;
-    }
-  EpiIn<4> in;
-  epi_load<4>(pb, m, 0, li, in);
-  conv_epilogue<4>(pb, acc2, m, 0, li, in);
+  for (int r = 0; r < RB_RB; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  BwdEpi none;
+  const RwEpi e = rw_epi<RW_FWD>(pb, none, 0);
+  const RwOut<RB_RB> out(pb, b, y0 + wr * RB_RB, x0, nw, li, kq);
+  rw_epi_load<RB_RB, RW_FWD>(pb, e, out, 0, r1, bias);
+  rw_sweep<RB_RB, RB_MID>(mid + (wr * RB_RB * RB_MID + li) * RW_PITCH + kq * 8, W, acc,
+                          [](int) {});
+  rw_epilogue<RB_RB, RW_FWD>(pb, e, out, r1, bias, acc);
 }
 
 // Runs the conv on k_conv3_lds<CINP, NT, TH> if its shape fits: cin_p == CINP,
@@ -1653,7 +1639,9 @@ void conv_launch_counts(int64_t* out, bool reset) {
 bool launch_res_block(const ConvArgs& a, const ConvArgs& b, hipStream_t st) {
   const auto fits = [](const ConvArgs& p) {
     return p.mode == VIEW_PLAIN && p.taps == 9 && p.cin_p == RB_C && p.kp == RB_KP &&
-           p.cout == RB_C;
+           p.cout == RB_C && p.frag && (!p.out_f || p.out_f_stride % 4 == 0) &&
+           (!p.out_h || p.out_h_stride % 8 == 0) &&
+           (int64_t)RB_IN * p.W * std::max(p.ca, RDG_DENSE) * 4 < (int64_t)BUF_OUT;
   };
   if (!fits(a) || !fits(b) || a.ca < RB_C || !a.relu || a.B != b.B || a.H != b.H ||
       a.W != b.W)
