@@ -201,8 +201,7 @@ COUNTER_KERNELS = [("k_extend_wave", "k_extend_wave"), ("k_extend<false,", "k_ex
                    ("k_shadow<false,", "k_shadow"), ("k_tail<false,", "k_tail"),
                    ("k_shade", "k_shade"), ("k_res_block", "k_res_block"),
                    ("k_conv3_rw<8, 2, 4, false, 0>", "k_conv3_rw<8,2,4>"),
-                   ("k_conv3_lds<16, 4, 16>", "k_conv3_lds<16,4,16>"),
-                   ("k_conv3_lds<8, 4, 16>", "k_conv3_lds<8,4,16>"),
+                   ("k_input<false>", "k_input"),
                    ("k_conv3_lds<80, 1, 16>", "k_conv3_lds<80,1,16>"),
                    ("k_conv<4>", "k_conv<4>")]
 # the closest-hit launches bench.py times as "extend": bounce 0 a wave at a time,
@@ -1109,7 +1108,7 @@ def main():
     torch.cuda.synchronize()
     prof_cnn = R.profile_read()
     R.profile_enable(False)
-    cnn_ms = sum(prof_cnn.get(k, (0.0, 0))[0] for k in ("cnn_prep", "cnn_hr_in", "cnn_lr",
+    cnn_ms = sum(prof_cnn.get(k, (0.0, 0))[0] for k in ("cnn_hr_in", "cnn_lr",
                                                          "cnn_hr_out")) / args.steps
     cnn_roof = {"bound": "mfma", "achieved": round(CNN_FLOP_720P / (cnn_ms / 1e3) / 1e12, 2)
                 if cnn_ms > 0 else 0.0, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",

@@ -307,8 +307,8 @@ mrs_status mrs_set_count_work(int32_t on);
 /* Kernel timing with HIP events recorded on the launch stream around every
  * launch of the library's kernels, by kernel id:
  * 0 generate, 1 extend (closest hit), 2 shade, 3 shadow (any hit),
- * 4 accumulate, 5 resolve, 6 network input preparation, 7 network HR input conv,
- * 8 network LR convs (lrhs, fuse, trunk, up), 9 network HR output conv,
+ * 4 accumulate, 5 resolve, 6 reserved, 7 network input preparation and input convs,
+ * 8 network LR convs (fuse, trunk, up), 9 network HR output conv,
  * 10 training forward, 11 training backward, 12 Adam + weight refresh,
  * 13 path tail (bounces from mrs_tuning.tail_bounce on), 14..15 reserved.
  * mrs_profile_enable(1) clears the totals and starts recording;
@@ -576,15 +576,15 @@ mrs_status mrs_debug_net_activation(const mrs_net* net, int32_t which, float* ou
                                     int64_t count);
 
 /* Launches of each network conv kernel since the last reset, counted on the
- * host when enqueued (so a captured graph counts once): [0] 3x3 LDS conv on
- * 16x8 tiles, 64-channel input chunks, output channels split over blocks;
- * [1] 3x3 LDS conv on 16x16 tiles, 64-channel chunks; [2] / [3] the same with
- * 16 / 8 input channels (the HR and LR input convs); [4] / [5] 3x3 LDS convs
+ * host when enqueued (so a captured graph counts once): [0] 3x3 conv of
+ * 64-channel slices on 16x8 tiles, output channels split over blocks; [1] the
+ * same on 16x16 tiles; [2] / [3] the HR and LR input convs (one launch with
+ * their preprocessing, counted in both); [4] / [5] 3x3 LDS convs
  * with fewer than 64 output channels (80 / 64 input channels: the
  * reconstruction convs); [6] / [7] the direct implicit-GEMM conv (64 / 16
- * output channels per block: the 1x1 fuse conv and shapes the LDS kernels do
- * not take); [8] / [9] the data-gradient convs of training on the LDS conv
- * (16x8 / 16x16 tiles; the others run a direct implicit GEMM, not counted);
+ * output channels per block: the 1x1 fuse conv and shapes the other kernels do
+ * not take); [8] / [9] the data-gradient convs of training on the kernel of
+ * [0] / [1] (the others run a direct implicit GEMM, not counted);
  * [10] a residual block of the trunk as one kernel (two 3x3 convs, counted
  * once).  reset != 0 clears the counts after reading them. */
 #define MRS_NUM_CONV_KINDS 11

@@ -1080,74 +1080,183 @@ __global__ __launch_bounds__(256) void k_dgrad(ConvArgs p, BwdEpi e) {
   }
 }
 
-// Network inputs: HRLS -> 16 BF16 channels (log1p of clipped RGB, albedo,
-// normal, log1p depth, 6 zeros); LRHS -> 8 channels (log1p RGB, 5 zeros).
-__global__ __launch_bounds__(256) void k_prep(int64_t nhr, int64_t nlr,
-                                              const float* __restrict__ hr,
-                                              const float* __restrict__ aux,
-                                              const float* __restrict__ lr,
-                                              uint16_t* __restrict__ xh,
-                                              uint16_t* __restrict__ xl) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < nhr) {
+// Network input channels of one HRLS pixel: 16 BF16 values (log1p of clipped RGB,
+// albedo, normal, log1p depth, 6 zeros; with the render layers instead of the
+// depth: log1p of the clipped diffuse and glossy layers, log1p of the per-sample
+// variance averaged over RGB, clamped to [0, 1e4]).
+__device__ __forceinline__ float tone(float v) { return log1pf(fminf(fmaxf(v, 0.0f), 100.0f)); }
+
+template <bool LAYERS>
+struct HrPixel {  // loaded before any is used
+  float rgb[3], aux[LAYERS ? 6 : 7], lay[LAYERS ? 6 : 1], sq[LAYERS ? 3 : 1];
+  __device__ __forceinline__ void load(const InputArgs& p, int64_t i) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rgb[c] = p.hr[3 * i + c];
+#pragma unroll
+    for (int c = 0; c < (LAYERS ? 6 : 7); ++c) aux[c] = p.aux[7 * i + c];
+    if (LAYERS) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) lay[c] = p.layers[9 * i + 3 + c];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sq[c] = p.sumsq[3 * i + c];
+    }
+  }
+  __device__ __forceinline__ void pack(const InputArgs& p, u32x4 (&o)[2]) const {
     float v[16];
-    for (int c = 0; c < 3; ++c) v[c] = log1pf(fminf(fmaxf(hr[3 * i + c], 0.0f), 100.0f));
-    for (int c = 0; c < 6; ++c) v[3 + c] = aux[7 * i + c];
-    v[9] = log1pf(fmaxf(aux[7 * i + 6], 0.0f));
-    for (int c = 10; c < 16; ++c) v[c] = 0.0f;
-    uint32_t w[8];
-    for (int k = 0; k < 8; ++k) w[k] = (uint32_t)f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
-    uint4* o = reinterpret_cast<uint4*>(xh + 16 * i);
-    o[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    o[1] = make_uint4(w[4], w[5], w[6], w[7]);
-  } else if (i < nhr + nlr) {
-    const int64_t j = i - nhr;
-    float v[8];
-    for (int c = 0; c < 3; ++c) v[c] = log1pf(fminf(fmaxf(lr[3 * j + c], 0.0f), 100.0f));
-    for (int c = 3; c < 8; ++c) v[c] = 0.0f;
-    uint32_t w[4];
-    for (int k = 0; k < 4; ++k) w[k] = (uint32_t)f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
-    *reinterpret_cast<uint4*>(xl + 8 * j) = make_uint4(w[0], w[1], w[2], w[3]);
+    float var = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      v[c] = tone(rgb[c]);
+      if (LAYERS) var += sq[c] * p.inv_spp - rgb[c] * rgb[c];
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[3 + c] = aux[c];
+    if (LAYERS) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) v[9 + c] = tone(lay[c]);
+      v[15] = log1pf(fminf(fmaxf(var * (1.0f / 3.0f), 0.0f), 1.0e4f));
+    } else {
+      v[9] = log1pf(fmaxf(aux[LAYERS ? 0 : 6], 0.0f));
+#pragma unroll
+      for (int c = 10; c < 16; ++c) v[c] = 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      o[k] = u32x4{f2bf2(v[8 * k], v[8 * k + 1]), f2bf2(v[8 * k + 2], v[8 * k + 3]),
+                   f2bf2(v[8 * k + 4], v[8 * k + 5]), f2bf2(v[8 * k + 6], v[8 * k + 7])};
+  }
+};
+
+// The two input convs and what precedes them in one launch: blocks 0 .. nhr - 1
+// preprocess and convolve tiles of the HRLS image (16 channels), the others tiles
+// of the LRHS image (log1p RGB and 5 zeros: 8 channels), each to 64 channels with
+// bias and ReLU.  A block of 4 waves owns 32 x 16 pixels: the preprocessed tile with
+// its zero halo goes to LDS (pitch 24 channels for 16: 16-byte reads of 8 lanes
+// hit all banks), each wave computes 4 rows x 2 column tiles x 64 channels with
+// all weights in registers (5 or 3 K steps; K index tap CIN + c, a K step spans 2
+// or 4 taps).  Row i of M tile j holds channel 16 (i / 4) + 4 j + i % 4, so that
+// a lane has 16 consecutive channels of a pixel: 16-byte stores.
+// Writing the 64-channel result bounds it (118 MB at 720p, 25 us at the rate of
+// a copy).  A preprocessing pass, then one conv launch per image, both operands
+// of every MFMA from LDS, took 17 + 99 + 8 us; one launch takes 50.
+// xh / xl: also store the preprocessed images (training reads them again).
+constexpr int IN_W = 32, IN_H = 16, IN_TW = IN_W + 2, IN_PX = IN_TW * (IN_H + 2);
+constexpr int IN_CNT = (IN_PX + 255) / 256;
+
+template <int CIN>
+__device__ __forceinline__ void input_conv(const uint16_t* tile, const uint16_t* w,
+                                           const float* bias, uint16_t* out, int b, int H, int W,
+                                           int x0, int y0) {
+  constexpr int KS = (9 * CIN + 31) / 32, PITCH = CIN == 16 ? 24 : CIN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kq = lane >> 4, li = lane & 15;
+  bf16x8 Wt[KS][4];
+  const auto wb = buf(w);
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)  // row li / 4 of 16 channels, 4 j + li % 4 within
+      Wt[s][j] = __builtin_bit_cast(
+          bf16x8, buf_ld16(wb, ((li >> 2) * KS * 64 + kq * 16 + 4 * j + (li & 3)) * 16 + s * 1024));
+  float bs[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) bs[q] = bias[16 * kq + q];
+  // offset of this lane's operand of K step s: tap (32 s + 8 kq) / CIN
+  int to[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const int k = 32 * s + 8 * kq, tap = min(k / CIN, 8), c = k & (CIN - 1);
+    const int dy = tap / 3, dx = tap - dy * 3;
+    to[s] = (dy * IN_TW + dx + li) * PITCH + c;
+  }
+  const bool pad = 32 * (KS - 1) + 8 * kq >= 9 * CIN;  // the last K step's zero padding
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const int row = 4 * wave + (t >> 1), col = 16 * (t & 1);
+    const uint16_t* tp = tile + (row * IN_TW + col) * PITCH;
+    f32x4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      bf16x8 P = ld8(tp + to[s]);
+      if (s == KS - 1 && pad) P = zero8();
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Wt[s][j], P, acc[j], 0, 0, 0);
+    }
+    const int y = y0 + row, x = x0 + col + li;
+    if (y < H && x < W) {
+      uint32_t h[8];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          h[2 * j + q] = f2bf2(fmaxf(acc[j][2 * q] + bs[4 * j + 2 * q], 0.0f),
+                               fmaxf(acc[j][2 * q + 1] + bs[4 * j + 2 * q + 1], 0.0f));
+      u32x4* o = reinterpret_cast<u32x4*>(out + (((size_t)b * H + y) * W + x) * NET_FEAT + 16 * kq);
+      o[0] = u32x4{h[0], h[1], h[2], h[3]};
+      o[1] = u32x4{h[4], h[5], h[6], h[7]};
+    }
   }
 }
 
-// Network inputs with the HRLS render layers: HRLS -> 16 BF16 channels (log1p
-// of clipped RGB, albedo, normal, log1p of the clipped diffuse and glossy
-// layers, log1p of the per-sample variance averaged over RGB, clamped to
-// [0, 1e4]); LRHS as in k_prep.
-__global__ __launch_bounds__(256) void k_prep_layers(int64_t nhr, int64_t nlr,
-                                                     const float* __restrict__ hr,
-                                                     const float* __restrict__ aux,
-                                                     const float* __restrict__ lay,
-                                                     const float* __restrict__ sq, float inv_spp,
-                                                     const float* __restrict__ lr,
-                                                     uint16_t* __restrict__ xh,
-                                                     uint16_t* __restrict__ xl) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < nhr) {
-    float v[16];
-    float var = 0.0f;
-    for (int c = 0; c < 3; ++c) {
-      const float m = hr[3 * i + c];
-      v[c] = log1pf(fminf(fmaxf(m, 0.0f), 100.0f));
-      var += sq[3 * i + c] * inv_spp - m * m;
+template <bool LAYERS>
+__global__ __launch_bounds__(256) void k_input(InputArgs p) {
+  __shared__ __attribute__((aligned(16))) uint16_t tile[IN_PX * 24];
+  const bool hr = (int)blockIdx.x < p.nhr;
+  const int W = hr ? p.W : p.w, H = hr ? p.H : p.h;
+  const int tx = (W + IN_W - 1) / IN_W, ty = (H + IN_H - 1) / IN_H;
+  int t = hr ? blockIdx.x : blockIdx.x - p.nhr;
+  const int x0 = t % tx * IN_W;
+  t /= tx;
+  const int y0 = t % ty * IN_H, b = t / ty;
+  int64_t at[IN_CNT];  // the pixel's index in its image batch, -1 outside
+  bool own[IN_CNT];    // inside the block's own tile
+#pragma unroll
+  for (int u = 0; u < IN_CNT; ++u) {
+    const int i = threadIdx.x + u * 256, r = i / IN_TW, c = i - r * IN_TW;
+    const int y = y0 - 1 + r, x = x0 - 1 + c;
+    const bool in = i < IN_PX && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+    at[u] = in ? ((int64_t)b * H + y) * W + x : -1;
+    own[u] = in && r >= 1 && r <= IN_H && c >= 1 && c <= IN_W;
+  }
+  if (hr) {
+    HrPixel<LAYERS> px[IN_CNT];
+#pragma unroll
+    for (int u = 0; u < IN_CNT; ++u)
+      if (at[u] >= 0) px[u].load(p, at[u]);
+#pragma unroll
+    for (int u = 0; u < IN_CNT; ++u) {
+      const int i = threadIdx.x + u * 256;
+      u32x4 o[2] = {u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0}};
+      if (at[u] >= 0) px[u].pack(p, o);
+      if (i < IN_PX) {
+        u32x4* d = reinterpret_cast<u32x4*>(tile + i * 24);
+        d[0] = o[0];
+        d[1] = o[1];
+      }
+      if (p.xh && own[u]) {
+        u32x4* d = reinterpret_cast<u32x4*>(p.xh + 16 * at[u]);
+        d[0] = o[0];
+        d[1] = o[1];
+      }
     }
-    for (int c = 0; c < 6; ++c) v[3 + c] = aux[7 * i + c];
-    for (int c = 0; c < 6; ++c) v[9 + c] = log1pf(fminf(fmaxf(lay[9 * i + 3 + c], 0.0f), 100.0f));
-    v[15] = log1pf(fminf(fmaxf(var * (1.0f / 3.0f), 0.0f), 1.0e4f));
-    uint32_t w[8];
-    for (int k = 0; k < 8; ++k) w[k] = (uint32_t)f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
-    uint4* o = reinterpret_cast<uint4*>(xh + 16 * i);
-    o[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    o[1] = make_uint4(w[4], w[5], w[6], w[7]);
-  } else if (i < nhr + nlr) {
-    const int64_t j = i - nhr;
-    float v[8];
-    for (int c = 0; c < 3; ++c) v[c] = log1pf(fminf(fmaxf(lr[3 * j + c], 0.0f), 100.0f));
-    for (int c = 3; c < 8; ++c) v[c] = 0.0f;
-    uint32_t w[4];
-    for (int k = 0; k < 4; ++k) w[k] = (uint32_t)f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
-    *reinterpret_cast<uint4*>(xl + 8 * j) = make_uint4(w[0], w[1], w[2], w[3]);
+    input_conv<16>(tile, p.wh, p.bh, p.h0, b, H, W, x0, y0);
+  } else {
+#pragma unroll
+    for (int u = 0; u < IN_CNT; ++u) {
+      const int i = threadIdx.x + u * 256;
+      u32x4 o = u32x4{0, 0, 0, 0};
+      if (at[u] >= 0) {
+        const float* s = p.lr + 3 * at[u];
+        o = u32x4{f2bf2(tone(s[0]), tone(s[1])), f2bf2(tone(s[2]), 0.0f), 0, 0};
+      }
+      if (i < IN_PX) *reinterpret_cast<u32x4*>(tile + i * 8) = o;
+      if (p.xl && own[u]) *reinterpret_cast<u32x4*>(p.xl + 8 * at[u]) = o;
+    }
+    input_conv<8>(tile, p.wl, p.bl, p.fl, b, H, W, x0, y0);
   }
 }
 
@@ -1661,8 +1770,6 @@ void launch_conv(const ConvArgs& a, int cout_p, hipStream_t st) {
       return count_conv(0);
     if (cout_p >= 64) {
       if (try_conv3_rw<8, 2, 4, RW_FWD>(a, cout_p, 1, st, nullptr)) return count_conv(1);
-      if (try_conv3_lds<16, 4, 16>(a, cout_p, st)) return count_conv(2);
-      if (try_conv3_lds<8, 4, 16>(a, cout_p, st)) return count_conv(3);
     } else {
       if (try_conv3_lds<80, 1, 16>(a, cout_p, st)) return count_conv(4);
       if (try_conv3_lds<64, 1, 16>(a, cout_p, st)) return count_conv(5);
@@ -1679,13 +1786,39 @@ void launch_conv(const ConvArgs& a, int cout_p, hipStream_t st) {
   }
 }
 
-void launch_prep(const mrs_net* net, int64_t nhr, int64_t nlr, const float* hr, const float* aux,
-                 const float* lr, uint16_t* xh, uint16_t* xl, hipStream_t st) {
-  if (arch_has_layers(net->arch))
-    k_prep_layers<<<cdiv64(nhr + nlr, 256), 256, 0, st>>>(
-        nhr, nlr, hr, aux, net->in_layers, net->in_sumsq, 1.0f / (float)net->in_spp, lr, xh, xl);
-  else
-    k_prep<<<cdiv64(nhr + nlr, 256), 256, 0, st>>>(nhr, nlr, hr, aux, lr, xh, xl);
+void launch_input(const mrs_net* net, int B, int H, int W, const float* hr, const float* aux,
+                  const float* lr, uint16_t* xh, uint16_t* xl, uint16_t* h0, uint16_t* fl,
+                  hipStream_t st) {
+  const NetLayer &Lh = net->layers[0], &Ll = net->layers[1];
+  const int s = arch_scale(net->arch);
+  InputArgs a;
+  a.hr = hr;
+  a.aux = aux;
+  a.lr = lr;
+  a.layers = net->in_layers;
+  a.sumsq = net->in_sumsq;
+  a.inv_spp = net->in_spp ? 1.0f / (float)net->in_spp : 0.0f;
+  a.H = H;
+  a.W = W;
+  a.h = H / s;
+  a.w = W / s;
+  a.wh = net->d_packed + Lh.pk_off;
+  a.wl = net->d_packed + Ll.pk_off;
+  a.bh = net->d_master + Lh.b_off;
+  a.bl = net->d_master + Ll.b_off;
+  a.xh = xh;
+  a.xl = xl;
+  a.h0 = h0;
+  a.fl = fl;
+  const auto tiles = [B](int h, int w) {
+    return (int64_t)B * ((h + IN_H - 1) / IN_H) * ((w + IN_W - 1) / IN_W);
+  };
+  a.nhr = (int)tiles(H, W);
+  const unsigned grid = (unsigned)(a.nhr + tiles(a.h, a.w));
+  if (arch_has_layers(net->arch)) k_input<true><<<grid, 256, 0, st>>>(a);
+  else k_input<false><<<grid, 256, 0, st>>>(a);
+  count_conv(2);
+  count_conv(3);
 }
 
 void launch_pack_all(const float* wm, const PackJob* jobs, int njobs, int64_t total,

@@ -77,6 +77,18 @@ struct BwdEpi {
   // k == 1: dL/dx_0 = ga + acc + add1 + add2 -> out_f (FP32 [M][64], optional), out_h (BF16)
 };
 
+// Arguments of k_input.
+struct InputArgs {
+  const float *hr, *aux, *lr;      // HRLS rgb and features, LRHS rgb (FP32)
+  const float *layers, *sumsq;     // HRLS render layers (layered networks)
+  float inv_spp;
+  int H, W, h, w;                  // HR and LR size
+  int nhr;                         // blocks of the HR image
+  const uint16_t *wh, *wl;         // packed weights of the two convs
+  const float *bh, *bl;
+  uint16_t *xh, *xl, *h0, *fl;
+};
+
 struct WgradArgs {
   ConvArgs x;            // view of the conv input (mode, tensors, B, H, W, cin_p, taps, kp)
   const uint16_t* dy;    // output gradient, NHWC BF16, dy_stride channels per pixel
@@ -111,8 +123,8 @@ struct NetLayer {
   // data-gradient conv: inputs dY (cinp_t channels stored), outputs cin channels
   int cinp_t, kp_t, coutp_t;
   int64_t pkt_off;       // offset in the packed transposed weights (-1: none)
-  // packed in fragment order: 3x3 convs from and to multiples of 64 channels
-  bool frag() const { return k == 3 && cin_p % 64 == 0 && cout % 64 == 0; }
+  // packed in fragment order: 3x3 convs to multiples of 64 channels
+  bool frag() const { return k == 3 && cout % 64 == 0; }
   bool frag_t() const { return k == 3 && cinp_t > 0 && cinp_t % 64 == 0 && cin % 64 == 0; }
 };
 
@@ -177,8 +189,12 @@ void launch_conv(const ConvArgs& a, int cout_p, hipStream_t st);
 // convs over the same plain BF16 input grid and a has the ReLU; false (nothing
 // launched) otherwise.
 bool launch_res_block(const ConvArgs& a, const ConvArgs& b, hipStream_t st);
-void launch_prep(const mrs_net* net, int64_t nhr, int64_t nlr, const float* hr, const float* aux,
-                 const float* lr, uint16_t* xh, uint16_t* xl, hipStream_t st);
+// Preprocessing and the two input convs (with bias and ReLU): h0 B*H*W*64, fl at
+// the LR size; the preprocessed images too where xh (16 channels) and xl (8) are
+// given.
+void launch_input(const mrs_net* net, int B, int H, int W, const float* hr, const float* aux,
+                  const float* lr, uint16_t* xh, uint16_t* xl, uint16_t* h0, uint16_t* fl,
+                  hipStream_t st);
 void launch_init(float* dst, const NetLayer& L, uint64_t seed, hipStream_t st);
 void launch_dgrad(const ConvArgs& a, const BwdEpi& e, int cout_p, hipStream_t st);
 void launch_wgrad(const WgradArgs& a, int splits, hipStream_t st);

@@ -167,14 +167,14 @@ mrs_status arena_carve(char*& base, size_t& cap, std::vector<std::pair<void**, s
 namespace {
 
 struct Arena {
-  uint16_t *xh, *xl, *h0, *fl, *f0h, *rh[2], *th, *U;
+  uint16_t *h0, *fl, *f0h, *rh[2], *th, *U;
   float *f0f, *rf[2];
 };
 
 mrs_status ensure_arena(mrs_net* net, int B, int H, int W, Arena& A) {
   const size_t P = (size_t)B * H * W, p = P / 16;
   std::vector<std::pair<void**, size_t>> plan = {
-      {(void**)&A.xh, P * 16 * 2},   {(void**)&A.xl, p * 8 * 2},    {(void**)&A.h0, P * 64 * 2},
+      {(void**)&A.h0, P * 64 * 2},
       {(void**)&A.fl, p * 64 * 2},   {(void**)&A.f0f, p * 64 * 4},  {(void**)&A.f0h, p * 64 * 2},
       {(void**)&A.rf[0], p * 64 * 4}, {(void**)&A.rf[1], p * 64 * 4},
       {(void**)&A.rh[0], p * 64 * 2}, {(void**)&A.rh[1], p * 64 * 2},
@@ -209,31 +209,10 @@ mrs_status net_forward(mrs_net* net, int B, int H, int W, const float* hr, const
   if (rc != MRS_OK) return rc;
   const std::vector<NetLayer>& Ls = net->layers;
   const int h = H / NET_SCALE, w = W / NET_SCALE;
-  const int64_t P = (int64_t)B * H * W, p = P / 16;
-  prof_begin(KID_CNN_PREP, st);
-  launch_prep(net, P, p, hr, aux, lr, A.xh, A.xl, st);
-  prof_end(KID_CNN_PREP, st);
-  prof_begin(KID_CNN_HR, st);
-  {  // h0 = ReLU(conv(xh))
-    ConvArgs a = base_args(net, Ls[0], B, H, W);
-    a.a = A.xh;
-    a.ca = 16;
-    a.relu = 1;
-    a.out_h = A.h0;
-    a.out_h_stride = NET_FEAT;
-    launch_conv(a, Ls[0].cout_p, st);
-  }
+  prof_begin(KID_CNN_HR, st);  // h0 = ReLU(conv(xh)), fl = ReLU(conv(xl))
+  launch_input(net, B, H, W, hr, aux, lr, nullptr, nullptr, A.h0, A.fl, st);
   prof_end(KID_CNN_HR, st);
   prof_begin(KID_CNN_LR, st);
-  {  // fl = ReLU(conv(xl))
-    ConvArgs a = base_args(net, Ls[1], B, h, w);
-    a.a = A.xl;
-    a.ca = 8;
-    a.relu = 1;
-    a.out_h = A.fl;
-    a.out_h_stride = NET_FEAT;
-    launch_conv(a, Ls[1].cout_p, st);
-  }
   {  // F0 = ReLU(conv1x1([fl, unshuffle(h0)]))
     ConvArgs a = base_args(net, Ls[2], B, h, w);
     a.mode = VIEW_CONCAT_UNSHUFFLE;
@@ -517,23 +496,8 @@ void forward_train(mrs_net* net, const TrainArena& A, int B, int H, int W, const
                    const float* aux, const float* lr, hipStream_t st) {
   const std::vector<NetLayer>& Ls = net->layers;
   const int h = H / NET_SCALE, w = W / NET_SCALE;
-  const int64_t P = (int64_t)B * H * W, p = P / 16;
-  launch_prep(net, P, p, hr, aux, lr, A.xh, A.xl, st);
-  ConvArgs a = base_args(net, Ls[0], B, H, W);
-  a.a = A.xh;
-  a.ca = 16;
-  a.relu = 1;
-  a.out_h = A.h0;
-  a.out_h_stride = NET_FEAT;
-  launch_conv(a, Ls[0].cout_p, st);
-  a = base_args(net, Ls[1], B, h, w);
-  a.a = A.xl;
-  a.ca = 8;
-  a.relu = 1;
-  a.out_h = A.fl;
-  a.out_h_stride = NET_FEAT;
-  launch_conv(a, Ls[1].cout_p, st);
-  a = base_args(net, Ls[2], B, h, w);
+  launch_input(net, B, H, W, hr, aux, lr, A.xh, A.xl, A.h0, A.fl, st);
+  ConvArgs a = base_args(net, Ls[2], B, h, w);
   a.mode = VIEW_CONCAT_UNSHUFFLE;
   a.a = A.fl;
   a.ca = NET_FEAT;

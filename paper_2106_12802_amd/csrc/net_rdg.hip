@@ -47,11 +47,13 @@ struct RdgActs {
 size_t lr_pixels(size_t P, int D) { return P >> (2 * D); }
 
 void plan_acts(std::vector<std::pair<void**, size_t>>& plan, RdgActs& A, size_t P, int D,
-               int ndense, bool out) {
+               int ndense, bool keep) {
   const size_t p = lr_pixels(P, D);
   auto add = [&](void** ptr, size_t bytes) { plan.push_back({ptr, bytes}); };
-  add((void**)&A.xh, P * 16 * 2);
-  add((void**)&A.xl, p * 8 * 2);
+  if (keep) {  // the weight gradients of the input convs read them
+    add((void**)&A.xh, P * 16 * 2);
+    add((void**)&A.xl, p * 8 * 2);
+  }
   add((void**)&A.h0, P * NET_FEAT * 2);
   add((void**)&A.fl, p * NET_FEAT * 2);
   add((void**)&A.fdfh, p * NET_FEAT * 2);
@@ -61,7 +63,7 @@ void plan_acts(std::vector<std::pair<void**, size_t>>& plan, RdgActs& A, size_t 
   for (int i = 0; i < 2; ++i) add((void**)&A.S[i], p * NET_FEAT * 4);
   for (int i = 0; i < 2; ++i) add((void**)&A.F[i], p * NET_FEAT * 4);
   add((void**)&A.fdf, p * NET_FEAT * 4);
-  if (out) add((void**)&A.out, P * 3 * 4);
+  if (keep) add((void**)&A.out, P * 3 * 4);
 }
 
 // The whole forward.  `keep`: one dense tensor per block (training); else the
@@ -71,31 +73,10 @@ void forward(mrs_net* net, const RdgActs& A, bool keep, int B, int H, int W, con
   const std::vector<NetLayer>& Ls = net->layers;
   const int Dn = arch_dsf(net->arch), sc = 1 << Dn;
   const int h = H / sc, w = W / sc;
-  const int64_t P = (int64_t)B * H * W, p = (int64_t)lr_pixels(P, Dn);
-  prof_begin(KID_CNN_PREP, st);
-  launch_prep(net, P, p, hr, aux, lr, A.xh, A.xl, st);
-  prof_end(KID_CNN_PREP, st);
-  prof_begin(KID_CNN_HR, st);
-  {  // F^0_HRLS
-    ConvArgs a = base_args(net, Ls[0], B, H, W);
-    a.a = A.xh;
-    a.ca = 16;
-    a.relu = 1;
-    a.out_h = A.h0;
-    a.out_h_stride = NET_FEAT;
-    launch_conv(a, Ls[0].cout_p, st);
-  }
+  prof_begin(KID_CNN_HR, st);  // F^0_HRLS and F_LRHS
+  launch_input(net, B, H, W, hr, aux, lr, A.xh, A.xl, A.h0, A.fl, st);
   prof_end(KID_CNN_HR, st);
   prof_begin(KID_CNN_LR, st);
-  {  // F_LRHS
-    ConvArgs a = base_args(net, Ls[1], B, h, w);
-    a.a = A.xl;
-    a.ca = 8;
-    a.relu = 1;
-    a.out_h = A.fl;
-    a.out_h_stride = NET_FEAT;
-    launch_conv(a, Ls[1].cout_p, st);
-  }
   {  // F0 = ReLU(fuse [F_LRHS, DSF^D(F^0_HRLS)]) -> FP32 and slot 0 of the first block
     ConvArgs a = base_args(net, Ls[2], B, h, w);
     a.mode = VIEW_CONCAT_UNSHUFFLE;
