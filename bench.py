@@ -202,8 +202,7 @@ COUNTER_KERNELS = [("k_extend_wave", "k_extend_wave"), ("k_extend<false,", "k_ex
                    ("k_shade", "k_shade"), ("k_res_block", "k_res_block"),
                    ("k_conv3_rw<8, 2, 4, false, 0>", "k_conv3_rw<8,2,4>"),
                    ("k_input<false>", "k_input"),
-                   ("k_conv3_lds<80, 1, 16>", "k_conv3_lds<80,1,16>"),
-                   ("k_conv<4>", "k_conv<4>")]
+                   ("k_rec<16, 64, 4>", "k_rec"), ("k_fuse", "k_fuse")]
 # the closest-hit launches bench.py times as "extend": bounce 0 a wave at a time,
 # the other wavefront bounces lane by lane (k_extend<true, ..> is the counting pass)
 EXTEND_KERNELS = ("k_extend_wave", "k_extend<false,")
@@ -1119,7 +1118,8 @@ def main():
     roofline["counters"] = None if ctr is None else {
         k: ctr[k] for k in ("k_extend_wave", "k_extend", "k_shadow", "k_tail") if k in ctr}
     cnn_roof["counters"] = None if ctr is None else {
-        k: ctr[k] for k in ctr if k.startswith("k_conv") or k == "k_res_block"}
+        k: ctr[k] for k in ctr
+        if k.startswith("k_conv") or k in ("k_res_block", "k_input", "k_rec", "k_fuse")}
     kernel_ms = {k: round(v[0] / args.steps, 4) for k, v in prof.items()}
     result = {
         "metric": METRIC, "value": round(value, 3), "unit": "Mpaths/s", "n_gpus": 1,

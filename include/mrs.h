@@ -579,11 +579,10 @@ mrs_status mrs_debug_net_activation(const mrs_net* net, int32_t which, float* ou
  * host when enqueued (so a captured graph counts once): [0] 3x3 conv of
  * 64-channel slices on 16x8 tiles, output channels split over blocks; [1] the
  * same on 16x16 tiles; [2] / [3] the HR and LR input convs (one launch with
- * their preprocessing, counted in both); [4] / [5] 3x3 LDS convs
- * with fewer than 64 output channels (80 / 64 input channels: the
- * reconstruction convs); [6] / [7] the direct implicit-GEMM conv (64 / 16
- * output channels per block: the 1x1 fuse conv and shapes the other kernels do
- * not take); [8] / [9] the data-gradient convs of training on the kernel of
+ * their preprocessing, counted in both); [4] / [5] the
+ * reconstruction convs of 80 / 64 input channels; [6] / [7] the 1x1 fuse conv
+ * and the direct implicit-GEMM conv (64 / 16 output channels per block) that
+ * takes the shapes the other kernels do not take; [8] / [9] the data-gradient convs of training on the kernel of
  * [0] / [1] (the others run a direct implicit GEMM, not counted);
  * [10] a residual block of the trunk as one kernel (two 3x3 convs, counted
  * once).  reset != 0 clears the counts after reading them. */

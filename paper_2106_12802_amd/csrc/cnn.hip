@@ -283,147 +283,9 @@ __device__ __forceinline__ void conv_epilogue(const ConvArgs& p, const f32x4 (&a
       }
 }
 
-// 3x3 convolution with its operands staged in LDS, for the convs whose input or
-// output is not a multiple of 64 channels (the input and the reconstruction
-// convs).  A block of 8 waves owns a 16 x 16 pixel tile of one image: the (16+2) x
-// (16+2) x CINP input tile with its zero halo is gathered through the conv's
-// input view (plain, or shuffle+concat), and the weights of one group of 16 NT
-// output channels (9 CINP x 16 NT BF16) are loaded once per group; then every
-// MFMA operand comes from LDS.  Wave w computes image rows 2w and 2w+1 of the tile
-// (two 16-pixel row tiles) x 16 NT channels with v_mfma_f32_16x16x32_bf16; K index
-// k = tap CINP + c, so with CINP < 32 one K step spans two taps.
-// LDS layouts are chosen for conflict-free 16-byte accesses: tile pixels
-// padded by 8 channels, weights chunk-major [k / 8][n][8] with one pad chunk
-// per k row.
 constexpr int C3_W = 16;  // tile width: one 16-pixel MFMA row tile
 
 __device__ __forceinline__ bool pos_bf(uint16_t h) { return h != 0 && !(h & 0x8000u); }
-
-// LDS pitch of a tile pixel (BF16 channels): 16-byte reads of 8 consecutive
-// lanes (pixels) at this stride hit distinct banks; a multiple of 32 channels
-// needs 8 more (64: 72), other widths do not (80: 80, 16: 16, 8: 8).
-template <int CINP>
-constexpr int c3_pitch() {
-  return CINP % 32 == 0 ? CINP + 8 : CINP;
-}
-// LDS bytes of a k_conv3_lds instance (input tile and weights).
-template <int CINP, int NT, int TH>
-constexpr int c3_lds_bytes() {
-  constexpr int KP = (9 * CINP + 31) / 32 * 32;
-  return 2 * ((TH + 2) * (C3_W + 2) * c3_pitch<CINP>() + (KP / 8) * (16 * NT + 1) * 8);
-}
-// Waves per SIMD the compiler must leave registers for (a block of TH / 2
-// waves puts TH / 8 on each SIMD): two blocks per CU for the narrow convs (16
-// output channels: the reconstruction convs) when the LDS allows it -- they fit
-// in 128 VGPRs --, one block otherwise (the 64-channel instances need more
-// registers than two blocks leave them, and spill when forced).
-template <int CINP, int NT, int TH>
-constexpr int c3_min_waves() {
-  return (NT == 1 && c3_lds_bytes<CINP, NT, TH>() <= 80 * 1024 ? 2 : 1) *
-         (TH / 8 > 0 ? TH / 8 : 1);
-}
-
-template <int CINP, int NT, int TH>
-__global__ __launch_bounds__(32 * TH, (c3_min_waves<CINP, NT, TH>())) void k_conv3_lds(
-    ConvArgs p, int cout_p) {
-  constexpr int THREADS = 32 * TH;  // TH / 2 waves, two tile rows each
-  constexpr int TILE = (TH + 2) * (C3_W + 2);
-  constexpr int PITCH = c3_pitch<CINP>();
-  constexpr int KP = (9 * CINP + 31) / 32 * 32;
-  constexpr int NG = 16 * NT;
-  constexpr int WPITCH = NG + 1;  // 16-byte chunks per weight row (pad: conflict-free stores)
-  constexpr int LDS_ALL = c3_lds_bytes<CINP, NT, TH>();
-  __shared__ __attribute__((aligned(16))) uint16_t tile[TILE * PITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t wts[(KP / 8) * WPITCH * 8];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int kq = lane >> 4, li = lane & 15;
-  const int x0 = blockIdx.x * C3_W, y0 = blockIdx.y * TH;
-  const int b = blockIdx.z;
-  // Loads are issued in batches (C3_BATCH_T tile chunks, C3_BATCH_W weight
-  // chunks per thread) before their LDS stores, so that their latencies
-  // overlap instead of adding up.
-  constexpr int TCH = TILE * (CINP / 8), WCH = NG * (KP / 8);
-  // A block whose LDS leaves room for no second block on its CU (more than
-  // 80 KB) has 2 waves per SIMD, so registers are plentiful: 6 tile and 9
-  // weight chunks in flight per thread; otherwise 3 and 3.
-  constexpr int C3_BATCH_T = LDS_ALL > 80 * 1024 ? 6 : 3;
-  constexpr int C3_BATCH_W = LDS_ALL > 80 * 1024 ? 9 : 3;
-  for (int n0 = 0; n0 < cout_p; n0 += NG) {
-    f32x4 acc[2][NT];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (n0) {
-      __syncthreads();  // the weights in LDS are no longer read
-    } else {
-      auto tile_load = [&](int i) -> bf16x8 {
-        const int px = i / (CINP / 8), c = (i - px * (CINP / 8)) * 8;
-        const int ty = px / (C3_W + 2), tx = px - ty * (C3_W + 2);
-        return i < TCH ? view_chunk(p, b, y0 - 1 + ty, x0 - 1 + tx, c) : zero8();
-      };
-      auto tile_store = [&](int i, bf16x8 v) {
-        const int px = i / (CINP / 8), c = (i - px * (CINP / 8)) * 8;
-        if (i < TCH) *reinterpret_cast<bf16x8*>(tile + px * PITCH + c) = v;
-      };
-      for (int i = tid; i < TCH; i += C3_BATCH_T * THREADS) {
-        bf16x8 v[C3_BATCH_T];
-#pragma unroll
-        for (int u = 0; u < C3_BATCH_T; ++u) v[u] = tile_load(i + u * THREADS);
-#pragma unroll
-        for (int u = 0; u < C3_BATCH_T; ++u) tile_store(i + u * THREADS, v[u]);
-      }
-    }
-    // K index k = tap CINP + c, as packed
-    auto w_load = [&](int i) -> uint4 {
-      const int n = i / (KP / 8), kc = i - n * (KP / 8);
-      return i < WCH ? *reinterpret_cast<const uint4*>(p.w + (size_t)(n0 + n) * p.kp + kc * 8)
-                     : make_uint4(0u, 0u, 0u, 0u);
-    };
-    auto w_store = [&](int i, uint4 v) {
-      const int n = i / (KP / 8), kc = i - n * (KP / 8);
-      if (i < WCH) *reinterpret_cast<uint4*>(wts + (kc * WPITCH + n) * 8) = v;
-    };
-    for (int i = tid; i < WCH; i += C3_BATCH_W * THREADS) {
-      uint4 v[C3_BATCH_W];
-#pragma unroll
-      for (int u = 0; u < C3_BATCH_W; ++u) v[u] = w_load(i + u * THREADS);
-#pragma unroll
-      for (int u = 0; u < C3_BATCH_W; ++u) w_store(i + u * THREADS, v[u]);
-    }
-    __syncthreads();
-    for (int ks = 0; ks < KP; ks += 32) {
-      const int k = ks + kq * 8;
-      const int tap = k / CINP, c = k - tap * CINP;
-      const int dy = tap / 3, dx = tap - dy * 3;
-      bf16x8 A[2], Bv[NT];
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-        A[r] = tap < 9 ? ld8(tile + ((2 * wave + r + dy) * (C3_W + 2) + li + dx) * PITCH + c)
-                       : zero8();
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        Bv[j] = ld8(wts + (((ks >> 3) + kq) * WPITCH + j * 16 + li) * 8);
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[r], Bv[j], acc[r][j], 0, 0, 0);
-    }
-    int64_t m[2][4];
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int y = y0 + 2 * wave + r, x = x0 + kq * 4 + v;
-        m[r][v] = (y < p.H && x < p.W) ? ((int64_t)b * p.H + y) * p.W + x : -1;
-      }
-    EpiIn<NT> in;
-    epi_load<NT>(p, m, n0, li, in);
-    conv_epilogue<NT>(p, acc, m, n0, li, in);
-  }
-}
 
 // Row (channel) and K index of element e of a layer packed in fragment order:
 // 16-row tiles, each as K steps of 32, each as the 64 lanes' 8 weights in the
@@ -960,14 +822,199 @@ __global__ __launch_bounds__(RB_THREADS) void k_res_block(ConvArgs pa, ConvArgs 
   rw_epilogue<RB_RB, RW_FWD>(pb, e, out, r1, bias, acc);
 }
 
-// Runs the conv on k_conv3_lds<CINP, NT, TH> if its shape fits: cin_p == CINP,
-// packed K = 9 cin_p rounded up to 32, cout_p a multiple of 16 NT.
-template <int CINP, int NT, int TH>
-bool try_conv3_lds(const ConvArgs& a, int cout_p, hipStream_t st) {
-  if (a.frag || a.cin_p != CINP || a.kp != (9 * a.cin_p + 31) / 32 * 32 || cout_p % (16 * NT))
+// The 1x1 fuse conv [a, unshuffle(b)] -> 64 channels.  Its K is the LR image's 64
+// channels and then 64 for each of the r^2 pixels of the HR block: reading the HR
+// features once is what bounds it.  A block of 8 waves stages the weights of
+// FU_KS K steps in LDS (48 KB, two blocks per CU); each wave owns 16 LR pixels x 64
+// channels and has the operands of all these K steps in flight at once, straight
+// from memory into registers (a K step is 32 channels of one HR pixel per LR
+// pixel, so its place in the block is uniform).  K steps ascend, as in k_conv.
+constexpr int FU_KS = 12, FU_WAVES = 8;
+
+__global__ __launch_bounds__(64 * FU_WAVES, 4) void k_fuse(ConvArgs p) {
+  __shared__ __attribute__((aligned(16))) uint16_t wts[FU_KS * 4 * 512];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kq = lane >> 4, li = lane & 15;
+  const int64_t M = (int64_t)p.B * p.H * p.W, m0 = ((int64_t)blockIdx.x * FU_WAVES + wave) * 16;
+  const int ks_all = p.kp >> 5;
+  // this lane's pixel and its operands' offsets from the wave's first pixel's
+  const int64_t mf = m0 < M ? m0 : M - 1, m = m0 + li;
+  const int64_t tf = mf / p.W, t = (m < M ? m : M - 1) / p.W;
+  const int Xf = (int)(mf - tf * p.W), X = (int)((m < M ? m : M - 1) - t * p.W);
+  const int wr = p.W * p.r;
+  const auto fa = buf(p.a + mf * NET_FEAT);
+  const auto fb = buf(p.b + (tf * p.r * wr + (int64_t)Xf * p.r) * NET_FEAT);
+  const uint32_t oa = m < M ? (uint32_t)(li * NET_FEAT + kq * 8) * 2u : BUF_OUT;
+  const uint32_t ob = m < M ? (uint32_t)(((int)(t - tf) * p.r * wr + (X - Xf) * p.r) * NET_FEAT +
+                                         kq * 8) * 2u
+                            : BUF_OUT;
+  f32x4 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const auto wb = buf(p.w);
+  for (int k0 = 0; k0 < ks_all; k0 += FU_KS) {
+    // weights [K step][16-channel tile][lane], packed as [tile][K step][lane]
+    constexpr int WCH = FU_KS * 4 * 64, CNT = (WCH + 64 * FU_WAVES - 1) / (64 * FU_WAVES);
+    u32x4 v[CNT];
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) {
+      const int i = tid + u * 64 * FU_WAVES, ks = k0 + (i >> 8), j = (i >> 6) & 3;
+      v[u] = buf_ld16(wb, i < WCH && ks < ks_all
+                              ? (uint32_t)((j * ks_all + ks) * 64 + (i & 63)) * 16u
+                              : BUF_OUT);
+    }
+    bf16x8 P[FU_KS];
+#pragma unroll
+    for (int u = 0; u < FU_KS; ++u) {
+      const int ks = k0 + u;
+      if (ks >= ks_all) continue;  // uniform
+      if (ks < 2) {
+        P[u] = __builtin_bit_cast(bf16x8, buf_ld16(fa, oa, ks * 64));
+      } else {
+        int I, J;
+        unshuffle_slot((ks - 2) >> 1, p.r, p.dsf, I, J);
+        P[u] = __builtin_bit_cast(
+            bf16x8, buf_ld16(fb, ob, (uint32_t)((I * wr + J) * NET_FEAT + (ks & 1) * 32) * 2u));
+      }
+    }
+    if (k0) __syncthreads();  // the previous steps' weights are no longer read
+#pragma unroll
+    for (int u = 0; u < CNT; ++u) {
+      const int i = tid + u * 64 * FU_WAVES;
+      if (i < WCH) *reinterpret_cast<u32x4*>(wts + (size_t)i * 8) = v[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < FU_KS; ++u) {
+      if (k0 + u >= ks_all) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld8(wts + ((u * 4 + j) * 64 + lane) * 8),
+                                                         P[u], acc[j], 0, 0, 0);
+    }
+  }
+  if (m >= M) return;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int n = j * 16 + kq * 4;
+    f32x4 y;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      y[q] = acc[j][q] + p.bias[n + q];
+      y[q] = p.relu ? fmaxf(y[q], 0.0f) : y[q];
+    }
+    if (p.out_f) *reinterpret_cast<f32x4*>(p.out_f + (size_t)m * p.out_f_stride + n) = y;
+    if (p.out_h)
+      *reinterpret_cast<u32x2*>(p.out_h + (size_t)m * p.out_h_stride + n) =
+          u32x2{f2bf2(y[0], y[1]), f2bf2(y[2], y[3])};
+  }
+}
+
+bool try_fuse(const ConvArgs& a, int cout_p, hipStream_t st) {
+  if (a.mode != VIEW_CONCAT_UNSHUFFLE || a.taps != 1 || !a.frag || cout_p != 64 || a.cout != 64 ||
+      a.ca != NET_FEAT || a.cb != NET_FEAT || a.kp != NET_FEAT * (1 + a.r * a.r) || a.res ||
+      (a.out_f && a.out_f_stride % 4) || (a.out_h && a.out_h_stride % 4) ||
+      // offsets within two rows of HR blocks fit 31 bits
+      (int64_t)2 * a.r * a.r * a.W * NET_FEAT * 2 >= (int64_t)BUF_OUT)
     return false;
-  k_conv3_lds<CINP, NT, TH><<<dim3((a.W + C3_W - 1) / C3_W, (a.H + TH - 1) / TH, a.B), 32 * TH, 0,
-                              st>>>(a, cout_p);
+  const int64_t M = (int64_t)a.B * a.H * a.W;
+  k_fuse<<<(unsigned)((M + 16 * FU_WAVES - 1) / (16 * FU_WAVES)), 64 * FU_WAVES, 0, st>>>(a);
+  return true;
+}
+
+// The reconstruction conv: 3x3 over [shuffle_r(a) (C0 channels), b (CB)] to 3
+// channels in FP32.  A block of 4 waves stages the (16 + 2)^2 pixels of its tile in
+// LDS (every load in flight at once), wave w computes rows 4 w .. 4 w + 3 with all
+// weights in registers (only the 3 rows of the MFMA's A operand that hold output
+// channels are read from memory).  Bound by reading its input (147 MB at 720p,
+// 31 us at the rate of a copy).  K index tap (C0 + CB) + c: a K step may span taps.
+template <int C0, int CB, int RS>
+__global__ __launch_bounds__(256, 3) void k_rec(ConvArgs p) {
+  constexpr int CIN = C0 + CB, KS = (9 * CIN + 31) / 32, TW = C3_W + 2, NPX = TW * TW;
+  constexpr int PITCH = CIN % 32 == 0 ? CIN + 8 : CIN;  // 16-byte reads of 8 lanes hit all banks
+  __shared__ __attribute__((aligned(16))) uint16_t tile[NPX * PITCH];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kq = lane >> 4, li = lane & 15;
+  const int x0 = blockIdx.x * C3_W, y0 = blockIdx.y * C3_W, b = blockIdx.z;
+  // byte offsets from the tile's first pixel in the image (coarse pixel for a)
+  const int yf = max(y0 - 1, 0), xf = max(x0 - 1, 0);
+  const int hh = p.H / RS, ww = p.W / RS;
+  const auto sa = buf(p.a + (((size_t)b * hh + yf / RS) * ww + xf / RS) * (C0 * RS * RS));
+  const auto sb = buf(p.b + (((size_t)b * p.H + yf) * p.W + xf) * CB);
+  constexpr int CA8 = C0 / 8, CB8 = CB / 8;
+  constexpr int NA = (NPX * CA8 + 255) / 256, NB = (NPX * CB8 + 255) / 256;
+  u32x4 va[NA], vb[NB > 0 ? NB : 1];
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int i = tid + u * 256, px = i / CA8, c = i - px * CA8;
+    const int r = px / TW, y = y0 - 1 + r, x = x0 - 1 + px - r * TW;
+    const bool in = px < NPX && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
+    const int Y = y / RS, X = x / RS;
+    va[u] = buf_ld16(sa, in ? (uint32_t)(((Y - yf / RS) * ww + X - xf / RS) * (C0 * RS * RS) +
+                                         ((y - Y * RS) * RS + x - X * RS) * C0 + c * 8) * 2u
+                            : BUF_OUT);
+  }
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int i = tid + u * 256, px = i / (CB8 > 0 ? CB8 : 1), c = i - px * CB8;
+    const int r = px / TW, y = y0 - 1 + r, x = x0 - 1 + px - r * TW;
+    const bool in = px < NPX && (unsigned)y < (unsigned)p.H && (unsigned)x < (unsigned)p.W;
+    vb[u] = buf_ld16(sb, in ? (uint32_t)(((y - yf) * p.W + x - xf) * CB + c * 8) * 2u : BUF_OUT);
+  }
+  bf16x8 Wt[KS];
+  const auto wb = buf(p.w);
+  const uint32_t wo = li < p.cout ? (uint32_t)(li * p.kp + kq * 8) * 2u : BUF_OUT;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) Wt[s] = __builtin_bit_cast(bf16x8, buf_ld16(wb, wo, s * 64));
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int i = tid + u * 256, px = i / CA8, c = i - px * CA8;
+    if (px < NPX) *reinterpret_cast<u32x4*>(tile + px * PITCH + c * 8) = va[u];
+  }
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int i = tid + u * 256, px = i / (CB8 > 0 ? CB8 : 1), c = i - px * CB8;
+    if (px < NPX) *reinterpret_cast<u32x4*>(tile + px * PITCH + C0 + c * 8) = vb[u];
+  }
+  __syncthreads();
+  f32x4 acc[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint16_t* tp = tile + ((4 * wave) * TW + li) * PITCH;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const int k = 32 * s + 8 * kq, tap = k / CIN, c = k - tap * CIN;
+    const bool pad = 32 * (s + 1) > 9 * CIN && tap >= 9;  // the last K step's zero padding
+    const int dy = tap / 3, dx = tap - dy * 3;
+    const uint16_t* o = tp + (pad ? 0 : (dy * TW + dx) * PITCH + c);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      bf16x8 P = ld8(o + r * TW * PITCH);
+      if (pad) P = zero8();
+      acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Wt[s], P, acc[r], 0, 0, 0);
+    }
+  }
+  const int x = x0 + li;
+  if (kq == 0 && x < p.W) {  // rows 0 .. 2 of the result
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int y = y0 + 4 * wave + r;
+      if (y >= p.H) continue;
+      float* o = p.out_f + (((size_t)b * p.H + y) * p.W + x) * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) o[c] = acc[r][c] + p.bias[c];
+    }
+  }
+}
+
+template <int C0, int CB, int RS>
+bool try_rec(const ConvArgs& a, hipStream_t st) {
+  if (a.mode != VIEW_SHUFFLE_CONCAT || a.taps != 9 || a.frag || a.cout != 3 || a.r != RS ||
+      a.c0 != C0 || a.ca != C0 * RS * RS || a.cb != CB || a.cin_p != C0 + CB ||
+      a.kp != (9 * a.cin_p + 31) / 32 * 32 || a.relu || a.res || a.res2 || a.out_h ||
+      a.out_f_stride != 3 || (int64_t)(C3_W + 2) * a.W * 64 * 2 * RS >= (int64_t)BUF_OUT)
+    return false;
+  k_rec<C0, CB, RS><<<dim3((a.W + C3_W - 1) / C3_W, (a.H + C3_W - 1) / C3_W, a.B), 256, 0, st>>>(a);
   return true;
 }
 
@@ -1762,19 +1809,14 @@ bool launch_res_block(const ConvArgs& a, const ConvArgs& b, hipStream_t st) {
 }
 
 void launch_conv(const ConvArgs& a, int cout_p, hipStream_t st) {
-  if (a.taps == 9 && a.mode != VIEW_CONCAT_UNSHUFFLE &&
-      (a.mode != VIEW_PLAIN || a.ca >= a.cin_p)) {
-    const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
-    if (tiles < conv_small_tiles() &&
-        try_conv3_rw<4, 2, 2, RW_FWD>(a, cout_p, cout_p / 32, st, nullptr))
-      return count_conv(0);
-    if (cout_p >= 64) {
-      if (try_conv3_rw<8, 2, 4, RW_FWD>(a, cout_p, 1, st, nullptr)) return count_conv(1);
-    } else {
-      if (try_conv3_lds<80, 1, 16>(a, cout_p, st)) return count_conv(4);
-      if (try_conv3_lds<64, 1, 16>(a, cout_p, st)) return count_conv(5);
-    }
-  }
+  const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
+  if (tiles < conv_small_tiles() &&
+      try_conv3_rw<4, 2, 2, RW_FWD>(a, cout_p, cout_p / 32, st, nullptr))
+    return count_conv(0);
+  if (try_conv3_rw<8, 2, 4, RW_FWD>(a, cout_p, 1, st, nullptr)) return count_conv(1);
+  if (try_rec<16, 64, 4>(a, st)) return count_conv(4);
+  if (try_rec<64, 0, 2>(a, st)) return count_conv(5);
+  if (try_fuse(a, cout_p, st)) return count_conv(6);
   const int64_t M = (int64_t)a.B * a.H * a.W;
   const unsigned gx = cdiv64(M, 128);
   if (cout_p >= 64) {

@@ -123,8 +123,8 @@ struct NetLayer {
   // data-gradient conv: inputs dY (cinp_t channels stored), outputs cin channels
   int cinp_t, kp_t, coutp_t;
   int64_t pkt_off;       // offset in the packed transposed weights (-1: none)
-  // packed in fragment order: 3x3 convs to multiples of 64 channels
-  bool frag() const { return k == 3 && cout % 64 == 0; }
+  // packed in fragment order: convs to multiples of 64 channels
+  bool frag() const { return cout % 64 == 0; }
   bool frag_t() const { return k == 3 && cinp_t > 0 && cinp_t % 64 == 0 && cin % 64 == 0; }
 };
 
