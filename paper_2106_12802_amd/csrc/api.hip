@@ -81,8 +81,8 @@ void free_scene(mrs_scene* s) {
   dfree(s->d_prim_n);
   dfree(s->d_leaf_tri);
   dfree(s->d_nodes);
-  dfree(s->d_nodes4);
-  dfree(s->d_nodes4q);
+  dfree(s->d_nodes4);  // and the quantized copies behind them
+  s->d_nodes4q = nullptr;
   dfree(s->d_morton);
   dfree(s->d_leaf_prim);
   dfree(s->d_mats);
