@@ -800,6 +800,12 @@ __global__ __launch_bounds__(256) void k_reset(uint32_t* q, uint32_t n) {
   for (int i = threadIdx.x; i < Q_WORDS; i += blockDim.x) q[i] = (i == Q_RAYS) ? n : 0u;
 }
 
+// k_store_job and k_reset in one launch.
+__global__ __launch_bounds__(256) void k_begin(DevJob j, DevJob* dst, uint32_t* q, uint32_t n) {
+  if (threadIdx.x == 0) *dst = j;
+  for (int i = threadIdx.x; i < Q_WORDS; i += blockDim.x) q[i] = (i == Q_RAYS) ? n : 0u;
+}
+
 // The camera ray of global path g: its job j, origin o and direction d.
 // k_generate stores it; the bounce-0 kernels that skip the stored queue
 // (wave traversal and shading, when generation is fused into them) call the
@@ -1457,33 +1463,89 @@ __global__ __launch_bounds__(TB) void k_tail(const DevJob* __restrict__ jobs, in
   if (COUNT && wc.max_steps) atomicMax(stats + 10, (unsigned long long)wc.max_steps);
 }
 
-// Per pixel of every job overlapping the chunk [g0, g0 + n): add its samples of
-// the chunk (consecutive slots from slot0 + s_lo), in sample order, to the
-// pixel's sums (FP32 or FP64 per job).
-template <typename T>
-__device__ __forceinline__ void accumulate_pixel(const DevJob& J, char* acc_base, uint32_t pl,
+// ------------------------------------------------------------ per-pixel sums
+//
+// A pixel's samples are consecutive path slots and are added in sample order
+// (FP32 or FP64 per job), whatever the split into sub-chunks.  DIRECT: every
+// path of the render is resident at once, so the launch of the sub-chunk that
+// holds a pixel's last sample adds all its samples -- those of an earlier
+// sub-chunk too, whose slots lie just before and whose launches the stream has
+// already waited for -- and writes the means to the outputs: no sums in memory,
+// none to clear and no resolve launch.  Otherwise each launch adds the samples
+// of its sub-chunk to sums in memory, and k_resolve writes the outputs at the end.
+struct SumArgs {
+  const DevJob* __restrict__ jobs;
+  int njobs;
+  int64_t g0;      // path of slot 0 (first path of the super-chunk)
+  int64_t lo;      // the sub-chunk's paths: lo .. lo + n - 1
+  uint32_t n;
+  int64_t pix_lo, pix_hi;  // its pixels, in path order
+  const float4* __restrict__ L_buf;
+  const float4* __restrict__ aux_buf;
+  const float4* __restrict__ lay_buf;
+  char* __restrict__ acc_base;
+  unsigned long long* __restrict__ stats;
+  const uint32_t* __restrict__ qc;
+  int nb;          // wavefront bounces
+  int first;       // the sub-chunk's first launch: counts its rays and paths
+};
+
+__device__ __forceinline__ void count_chunk(const SumArgs& a) {
+  // the chunk's ray counts, once (bounces 0 .. nb-1; the path tail counts its own)
+  if (!a.first || blockIdx.x != 0 || threadIdx.x != 0) return;
+  unsigned long long r = 0, s = 0;
+  for (int b = 0; b < a.nb; ++b) {
+    r += a.qc[Q_RAYS + b];
+    s += a.qc[Q_SHADOW + b];
+  }
+  atomicAdd(a.stats + 1, r);
+  atomicAdd(a.stats + 2, s);
+  atomicAdd(a.stats + 4, (unsigned long long)a.n);
+}
+
+// The samples s_lo .. s_hi that a launch adds for pixel q (path order) of job J;
+// false: none.
+template <bool DIRECT>
+__device__ __forceinline__ bool pixel_samples(const SumArgs& a, const DevJob& J, uint32_t q,
+                                              int64_t& s_lo, int64_t& s_hi, int64_t& slot0) {
+  const int64_t base = J.first + (int64_t)q * J.spp;
+  slot0 = base - a.g0;
+  if (DIRECT) {
+    s_lo = 0;
+    s_hi = J.spp - 1;
+    const int64_t last = base + s_hi;
+    return last >= a.lo && last < a.lo + (int64_t)a.n;
+  }
+  // samples s with path first + q spp + s in [lo, lo + n)
+  s_lo = a.lo > base ? a.lo - base : 0;
+  s_hi = std::min<int64_t>(J.spp - 1, a.lo + a.n - 1 - base);
+  return s_lo <= s_hi;
+}
+
+// One thread per pixel.
+template <typename T, bool DIRECT>
+__device__ __forceinline__ void accumulate_pixel(const SumArgs& A, const DevJob& J, uint32_t pl,
                                                  int64_t s_lo, int64_t s_hi, int64_t slot0,
-                                                 int64_t npix, const float4* __restrict__ L_buf,
-                                                 const float4* __restrict__ aux_buf,
-                                                 const float4* __restrict__ lay_buf,
-                                                 uint32_t& bad) {
-  T* acc = reinterpret_cast<T*>(acc_base + J.acc_off);
+                                                 int64_t npix, uint32_t& bad) {
+  T* acc = reinterpret_cast<T*>(A.acc_base + J.acc_off);
   T* a_rgb = acc + 3 * (int64_t)pl;
   T* a_aux = acc + 3 * npix + 7 * (int64_t)pl;
   T* a_sq = acc + 10 * npix + 3 * (int64_t)pl;
   const bool feats = J.out_aux != nullptr;  // features are only traced for jobs that output them
   const bool lays = J.out_layers != nullptr;
   T* a_lay = acc + 13 * npix + 9 * (int64_t)pl;
-  T r = a_rgb[0], gg = a_rgb[1], bb = a_rgb[2];
-  T sr = a_sq[0], sg = a_sq[1], sb = a_sq[2];
-  T a[7];
-  for (int c = 0; c < 7; ++c) a[c] = feats ? a_aux[c] : (T)0;
-  T ly[9];
-  for (int c = 0; c < 9; ++c) ly[c] = lays ? a_lay[c] : (T)0;
+  T r = 0, gg = 0, bb = 0, sr = 0, sg = 0, sb = 0;
+  T a[7] = {}, ly[9] = {};
+  if (!DIRECT) {
+    r = a_rgb[0], gg = a_rgb[1], bb = a_rgb[2];
+    sr = a_sq[0], sg = a_sq[1], sb = a_sq[2];
+    for (int c = 0; c < 7; ++c) a[c] = feats ? a_aux[c] : (T)0;
+    for (int c = 0; c < 9; ++c) ly[c] = lays ? a_lay[c] : (T)0;
+  }
   for (int64_t s = s_lo; s <= s_hi; ++s) {
     const int64_t slot = slot0 + s;
-    float4 Lv = L_buf[slot];
-    float4 E = lays ? lay_buf[slot] : make_float4(0, 0, 0, 0);
+    float4 Lv = A.L_buf[slot];
+    float4 E = lays ? A.lay_buf[slot] : make_float4(0, 0, 0, 0);
     if (!(isfinite(Lv.x) && isfinite(Lv.y) && isfinite(Lv.z))) {
       Lv = make_float4(0, 0, 0, 0);
       E = make_float4(0, 0, 0, E.w);
@@ -1508,14 +1570,28 @@ __device__ __forceinline__ void accumulate_pixel(const DevJob& J, char* acc_base
     r += (T)Lv.x;
     gg += (T)Lv.y;
     bb += (T)Lv.z;
-    sr += (T)Lv.x * (T)Lv.x;
-    sg += (T)Lv.y * (T)Lv.y;
-    sb += (T)Lv.z * (T)Lv.z;
+    sr = fma((T)Lv.x, (T)Lv.x, sr);
+    sg = fma((T)Lv.y, (T)Lv.y, sg);
+    sb = fma((T)Lv.z, (T)Lv.z, sb);
     if (feats) {
-      const float4 A0 = aux_buf[2 * slot], A1 = aux_buf[2 * slot + 1];
+      const float4 A0 = A.aux_buf[2 * slot], A1 = A.aux_buf[2 * slot + 1];
       a[0] += (T)A0.x; a[1] += (T)A0.y; a[2] += (T)A0.z; a[3] += (T)A0.w;
       a[4] += (T)A1.x; a[5] += (T)A1.y; a[6] += (T)A1.z;
     }
+  }
+  if (DIRECT) {
+    const T inv = (T)1 / (T)J.spp;
+    float* o = J.out_rgb + 3 * (int64_t)pl;
+    o[0] = (float)(r * inv); o[1] = (float)(gg * inv); o[2] = (float)(bb * inv);
+    if (feats)
+      for (int c = 0; c < 7; ++c) J.out_aux[7 * (int64_t)pl + c] = (float)(a[c] * inv);
+    if (J.out_sq) {
+      float* q = J.out_sq + 3 * (int64_t)pl;
+      q[0] = (float)sr; q[1] = (float)sg; q[2] = (float)sb;
+    }
+    if (lays)
+      for (int c = 0; c < 9; ++c) J.out_layers[9 * (int64_t)pl + c] = (float)(ly[c] * inv);
+    return;
   }
   a_rgb[0] = r; a_rgb[1] = gg; a_rgb[2] = bb;
   a_sq[0] = sr; a_sq[1] = sg; a_sq[2] = sb;
@@ -1525,50 +1601,135 @@ __device__ __forceinline__ void accumulate_pixel(const DevJob& J, char* acc_base
     for (int c = 0; c < 9; ++c) a_lay[c] = ly[c];
 }
 
-__global__ __launch_bounds__(256) void k_accumulate(const DevJob* __restrict__ jobs, int njobs,
-                                                    int64_t g0, uint32_t n, int64_t pix_lo,
-                                                    int64_t pix_hi,
-                                                    const float4* __restrict__ L_buf,
-                                                    const float4* __restrict__ aux_buf,
-                                                    const float4* __restrict__ lay_buf,
-                                                    char* __restrict__ acc_base,
-                                                    unsigned long long* __restrict__ stats,
-                                                    const uint32_t* __restrict__ qc, int nb) {
-  // the chunk's ray counts, once (bounces 0 .. nb-1; the path tail counts its own)
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    unsigned long long r = 0, s = 0;
-    for (int b = 0; b < nb; ++b) {
-      r += qc[Q_RAYS + b];
-      s += qc[Q_SHADOW + b];
-    }
-    atomicAdd(stats + 1, r);
-    atomicAdd(stats + 2, s);
-    atomicAdd(stats + 4, (unsigned long long)n);
-  }
+template <bool DIRECT>
+__global__ __launch_bounds__(256) void k_accumulate(SumArgs A) {
+  count_chunk(A);
   // i runs over pixels in path order (the chunk's pixels are one range of it)
-  const int64_t i = pix_lo + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= pix_hi) return;
-  const uint32_t j = find_job_pix(jobs, njobs, i);
-  const DevJob& J = jobs[j];
+  const int64_t i = A.pix_lo + (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= A.pix_hi) return;
+  const uint32_t j = find_job_pix(A.jobs, A.njobs, i);
+  const DevJob& J = A.jobs[j];
   const int64_t npix = (int64_t)J.ww * J.wh;
   const uint32_t q = (uint32_t)(i - J.pix_first);  // path order of the pixel
+  int64_t s_lo, s_hi, slot0;
+  if (!pixel_samples<DIRECT>(A, J, q, s_lo, s_hi, slot0)) return;
   uint32_t wx, wy;
   tile_pixel(J, q, wx, wy);
   const uint32_t pl = wy * (uint32_t)J.ww + wx;  // row-major window pixel (outputs)
-  // samples s with g = first + q spp + s in [g0, g0 + n)
-  const int64_t base = J.first + (int64_t)q * J.spp;
-  const int64_t s_lo = g0 > base ? g0 - base : 0;
-  const int64_t s_hi = std::min<int64_t>(J.spp - 1, g0 + n - 1 - base);
-  if (s_lo > s_hi) return;
-  const int64_t slot0 = base - g0;
   uint32_t bad = 0;
-  if (J.fp64)
-    accumulate_pixel<double>(J, acc_base, pl, s_lo, s_hi, slot0, npix, L_buf, aux_buf, lay_buf,
-                             bad);
-  else
-    accumulate_pixel<float>(J, acc_base, pl, s_lo, s_hi, slot0, npix, L_buf, aux_buf, lay_buf,
-                            bad);
-  if (bad) atomicAdd(stats + 0, (unsigned long long)bad);
+  if (J.fp64) accumulate_pixel<double, DIRECT>(A, J, pl, s_lo, s_hi, slot0, npix, bad);
+  else accumulate_pixel<float, DIRECT>(A, J, pl, s_lo, s_hi, slot0, npix, bad);
+  if (bad) atomicAdd(A.stats + 0, (unsigned long long)bad);
+}
+
+// The same sums with 16 lanes per pixel (all jobs of a launch of one FP width T): the
+// lanes load 16 consecutive samples at once (256 bytes of radiance) into LDS, then each
+// lane adds them, in order, to the one or two channels that it holds.  With a thread
+// per pixel, a lane's loads are a pixel apart and few pixels leave the chip idle: 2.8 M
+// paths at 1024 spp are 2730 pixels, 11 blocks of one thread a pixel, 275 us; this
+// kernel, bound by the serial adds of a pixel, takes 35.  The lines (sum_class): with
+// features or layers to sum (thread per pixel / 16 lanes, us) 8 spp 10.6 / 14.8, 16 spp
+// 21 / 15, 32 spp 26 / 21 at 57,600 pixels; radiance alone 16 spp 6.5 / 7.4, 32 spp
+// 10.0 / 9.2, 64 spp 17 / 13 at 16,384 pixels (1,024 pixels: 16 lanes ahead from 16 on;
+// 77,000 pixels at 16 spp: 9.8 / 21).
+constexpr int WIDE_SPP = 16;             // with features or layers
+constexpr int WIDE_SPP_RGB = 32;         // radiance alone
+constexpr int WIDE_PIX = 16;             // pixels per block
+constexpr int WIDE_ROWS = 16 * 4 + 4;    // float4 per pixel: 16 samples x 4, and padding
+
+// Orders a wave's LDS accesses before and after it, across its lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename T, bool DIRECT>
+__global__ __launch_bounds__(256) void k_accumulate_wide(SumArgs A) {
+  __shared__ float4 lds[WIDE_PIX * WIDE_ROWS];
+  count_chunk(A);
+  const int c = threadIdx.x & 15;
+  float4* rows = lds + (threadIdx.x >> 4) * WIDE_ROWS;
+  const int64_t i = A.pix_lo + (int64_t)blockIdx.x * WIDE_PIX + (threadIdx.x >> 4);
+  int64_t s_lo = 0, s_hi = -1, slot0 = 0;
+  bool live = i < A.pix_hi;
+  const DevJob& J = A.jobs[find_job_pix(A.jobs, A.njobs, live ? i : A.pix_lo)];
+  const uint32_t q = live ? (uint32_t)(i - J.pix_first) : 0u;
+  live = live && pixel_samples<DIRECT>(A, J, q, s_lo, s_hi, slot0);
+  uint32_t wx, wy;
+  tile_pixel(J, q, wx, wy);
+  const int64_t pl = wy * (uint32_t)J.ww + wx, npix = (int64_t)J.ww * J.wh;
+  const bool feats = J.out_aux != nullptr, lays = J.out_layers != nullptr;
+  // the lane's channels: radiance 0-2, squares 3-5, features 6-12; layers 0-8
+  const int word = c < 3 ? c : c < 6 ? c - 3 : min(c - 2, 10), c3 = c % 3;
+  const bool square = c >= 3 && c < 6;
+  const bool ch1 = live && (c < 6 || (feats && c < 13)), ch2 = live && lays && c < 9;
+  T* acc = reinterpret_cast<T*>(A.acc_base + J.acc_off);
+  T* p1 = c < 3 ? acc + 3 * pl + c : c < 6 ? acc + 10 * npix + 3 * pl + c - 3
+                                           : acc + 3 * npix + 7 * pl + c - 6;
+  T* p2 = acc + 13 * npix + 9 * pl + c;
+  T a1 = 0, a2 = 0;
+  if (!DIRECT && ch1) a1 = *p1;
+  if (!DIRECT && ch2) a2 = *p2;
+  const int cnt = live ? (int)(s_hi - s_lo + 1) : 0;
+  int most = max(cnt, __shfl_xor(cnt, 16));
+  most = max(most, __shfl_xor(most, 32));
+  most = __builtin_amdgcn_readfirstlane(most);
+  const int64_t first = slot0 + s_lo + c;
+  const float4 zero = make_float4(0, 0, 0, 0);
+  float4 Lv, A0, A1, E;
+  auto load = [&](int k0) {
+    const bool in = k0 + c < cnt;
+    const int64_t slot = first + k0;
+    Lv = in ? A.L_buf[slot] : zero;
+    A0 = in && feats ? A.aux_buf[2 * slot] : zero;
+    A1 = in && feats ? A.aux_buf[2 * slot + 1] : zero;
+    E = in && lays ? A.lay_buf[slot] : zero;
+  };
+  uint32_t bad = 0;
+  load(0);
+  for (int k0 = 0; k0 < most; k0 += 16) {
+    if (!(isfinite(Lv.x) && isfinite(Lv.y) && isfinite(Lv.z))) {
+      Lv = zero;
+      E = make_float4(0, 0, 0, E.w);
+      ++bad;
+    }
+    rows[4 * c] = make_float4(Lv.x, Lv.y, Lv.z, E.w);
+    rows[4 * c + 1] = A0;
+    rows[4 * c + 2] = A1;
+    rows[4 * c + 3] = E;
+    wave_lds_sync();  // a pixel's rows are its wave's own
+    if (k0 + 16 < most) load(k0 + 16);
+    const float* w = reinterpret_cast<const float*>(rows);
+    const int m = min(16, cnt - k0);
+    if (ch1) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const T v = (T)w[16 * k + word];
+        if (k < m) a1 = fma(v, square ? v : (T)1, a1);
+      }
+    }
+    if (ch2) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int lobe = (int)w[16 * k + 3];
+        const T e = (T)w[16 * k + 12 + c3], l = (T)w[16 * k + c3];
+        if (k < m && (c < 3 || lobe == c / 3)) a2 += c < 3 ? e : l - e;
+      }
+    }
+    wave_lds_sync();
+  }
+  if (DIRECT) {
+    const T inv = (T)1 / (T)J.spp;
+    if (ch1 && c < 3) J.out_rgb[3 * pl + c] = (float)(a1 * inv);
+    if (ch1 && square && J.out_sq) J.out_sq[3 * pl + c - 3] = (float)a1;
+    if (ch1 && c >= 6) J.out_aux[7 * pl + c - 6] = (float)(a1 * inv);
+    if (ch2) J.out_layers[9 * pl + c] = (float)(a2 * inv);
+  } else {
+    if (ch1) *p1 = a1;
+    if (ch2) *p2 = a2;
+  }
+  if (bad) atomicAdd(A.stats + 0, (unsigned long long)bad);
 }
 
 __global__ __launch_bounds__(256) void k_zero_words(uint32_t* p, size_t n) {
@@ -1684,6 +1845,7 @@ struct Pending {
   hipStream_t st = nullptr;
   int used = 0;
   int nwave = 0;
+  bool direct = false;  // the sums go straight to the outputs
   Sub sub[MAX_SUB];
 };
 
@@ -1881,26 +2043,53 @@ size_t acc_bytes_of(int64_t npix, bool fp64, bool layers) {
   return ((size_t)npix * (layers ? 22 : 13) * (fp64 ? 8 : 4) + 255) & ~(size_t)255;
 }
 
+// The kernel class of a job's per-pixel sums: 0 a thread per pixel, 1 and 2 sixteen
+// lanes per pixel with FP32 and FP64 sums.
+int sum_class(const DevJob& J) {
+  const bool more = J.out_aux || J.out_layers;
+  return J.spp < (more ? WIDE_SPP : WIDE_SPP_RGB) ? 0 : J.fp64 ? 2 : 1;
+}
+
 // Per-pixel sums of one super-chunk, in sample order: each sub-chunk, in path
-// order, on the caller's stream once that sub-chunk is done (its join event).
+// order, on the caller's stream once that sub-chunk is done (its join event);
+// one launch per run of jobs of one kernel class.
 mrs_status sum_chunk(Workspace& ws, const DevJob* d_jobs, const std::vector<DevJob>& jobs,
-                     const Sub* sub, int used, int nwave, char* acc, hipStream_t st) {
+                     const Sub* sub, int used, int nwave, bool direct, char* acc,
+                     hipStream_t st) {
   const int nj = (int)jobs.size();
   for (int k = 0; k < used; ++k) {
     const Sub& u = sub[k];
     if (u.s != st) MRS_TRY_HIP(hipStreamWaitEvent(st, ws.ev_join[k], 0));
     // the chunk's pixels in path order: from the pixel of its first path to
     // the pixel of its last
+    const int64_t end = u.lo + (int64_t)u.n;
     int jlo = 0, jhi = nj - 1;
     while (jlo < nj - 1 && jobs[jlo + 1].first <= u.lo) ++jlo;
-    while (jhi > 0 && jobs[jhi].first >= u.lo + (int64_t)u.n) --jhi;
-    const int64_t pix_lo = jobs[jlo].pix_first + (u.lo - jobs[jlo].first) / jobs[jlo].spp;
-    const int64_t pix_hi =
-        jobs[jhi].pix_first + (u.lo + (int64_t)u.n - 1 - jobs[jhi].first) / jobs[jhi].spp + 1;
-    prof_begin(KID_ACCUMULATE, st);
-    k_accumulate<<<cdiv((size_t)(pix_hi - pix_lo), 256), 256, 0, st>>>(
-        d_jobs, nj, u.lo, u.n, pix_lo, pix_hi, u.L, u.aux, u.lay, acc, ws.stats, u.q, nwave);
-    prof_end(KID_ACCUMULATE, st);
+    while (jhi > 0 && jobs[jhi].first >= end) --jhi;
+    for (int ja = jlo; ja <= jhi;) {
+      const int cls = sum_class(jobs[ja]);
+      int jb = ja;
+      while (jb < jhi && sum_class(jobs[jb + 1]) == cls) ++jb;
+      const DevJob &Ja = jobs[ja], &Jb = jobs[jb];
+      const int64_t a = std::max(u.lo, Ja.first);
+      const int64_t z = jb < jhi ? jobs[jb + 1].first : end;
+      SumArgs A{d_jobs, nj, sub[0].lo, u.lo, u.n,
+                Ja.pix_first + (a - Ja.first) / Ja.spp,
+                Jb.pix_first + (z - 1 - Jb.first) / Jb.spp + 1,
+                ws.L, ws.aux, ws.lay, acc, ws.stats, u.q, nwave, ja == jlo};
+      const unsigned blocks = cdiv((size_t)(A.pix_hi - A.pix_lo), cls ? WIDE_PIX : 256);
+      auto kern = cls == 0 ? (direct ? k_accumulate<true> : k_accumulate<false>)
+                  : cls == 1 ? (direct ? k_accumulate_wide<float, true> : k_accumulate_wide<float, false>)
+                             : (direct ? k_accumulate_wide<double, true> : k_accumulate_wide<double, false>);
+      // the launch that writes the render's last outputs is its resolve as well
+      const bool last = direct && k == used - 1 && jb == jhi;
+      prof_begin(KID_ACCUMULATE, st);
+      if (last) prof_begin(KID_RESOLVE, st);
+      kern<<<blocks, 256, 0, st>>>(A);
+      if (last) prof_end(KID_RESOLVE, st);
+      prof_end(KID_ACCUMULATE, st);
+      ja = jb + 1;
+    }
   }
   // the next super-chunk (or render) reuses the slices once these sums have read them
   if (used > 0 && sub[0].s != st) MRS_TRY_HIP(hipEventRecord(ws.ev_fork, st));
@@ -1925,7 +2114,7 @@ auto shadow_kernel(int sched) {
 // which end_batch enqueues (render_batch does both).
 mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs,
                        const std::vector<DevJob>& jobs, char* acc, size_t acc_bytes,
-                       hipStream_t st) {
+                       hipStream_t st, DevJob* store = nullptr) {
   const int nj = (int)jobs.size();
   int64_t total = 0;
   int max_depth = 0;
@@ -1946,9 +2135,12 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
   const size_t spill_k = (size_t)P.blocks_k * TB * (MAX_STACK4 - LDS_STACK);
   const bool forked = ws.forked && ws.fork_st == st;
   ws.forked = false;
+  const bool direct = total <= P.K * P.Cs;  // every path resident: no sums in memory
+  if (store && P.K > 1) k_store_job<<<1, 64, 0, st>>>(jobs[0], store);
   if (!forked) {
-    k_zero_words<<<std::min(4096u, cdiv(acc_bytes / 4, 256)), 256, 0, st>>>((uint32_t*)acc,
-                                                                            acc_bytes / 4);
+    if (!direct)
+      k_zero_words<<<std::min(4096u, cdiv(acc_bytes / 4, 256)), 256, 0, st>>>((uint32_t*)acc,
+                                                                              acc_bytes / 4);
     if (P.K > 1) MRS_TRY_HIP(hipEventRecord(ws.ev_fork, st));
   }
   for (int64_t g0 = 0; g0 < total; g0 += P.K * P.Cs) {
@@ -1977,7 +2169,8 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
     for (int k = 0; k < used; ++k) {
       Sub& u = sub[k];
       if (P.K > 1) MRS_TRY_HIP(hipStreamWaitEvent(u.s, ws.ev_fork, 0));
-      k_reset<<<1, 256, 0, u.s>>>(u.q, u.n);
+      if (store && P.K == 1 && g0 == 0) k_begin<<<1, 256, 0, st>>>(jobs[0], store, u.q, u.n);
+      else k_reset<<<1, 256, 0, u.s>>>(u.q, u.n);
       if (!gen_fused) {
         prof_begin(KID_GENERATE, u.s);
         k_generate<<<cdiv(u.n, 256), 256, 0, u.s>>>(d_jobs, nj, u.lo, u.n, u.rays[0]);
@@ -2038,12 +2231,13 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
     if (P.K > 1)
       for (int k = 0; k < used; ++k) MRS_TRY_HIP(hipEventRecord(ws.ev_join[k], sub[k].s));
     if (g0 + P.K * P.Cs < total) {
-      MRS_TRY_STATUS(sum_chunk(ws, d_jobs, jobs, sub, used, nwave, acc, st));
+      MRS_TRY_STATUS(sum_chunk(ws, d_jobs, jobs, sub, used, nwave, false, acc, st));
     } else {
       ws.pend.active = true;
       ws.pend.st = st;
       ws.pend.used = used;
       ws.pend.nwave = nwave;
+      ws.pend.direct = direct;
       for (int k = 0; k < used; ++k) ws.pend.sub[k] = sub[k];
     }
   }
@@ -2059,7 +2253,12 @@ mrs_status end_batch(Workspace& ws, const DevJob* d_jobs, const std::vector<DevJ
   int64_t total_pix = 0;
   for (const DevJob& J : jobs) total_pix += (int64_t)J.ww * J.wh;
   ws.pend.active = false;
-  MRS_TRY_STATUS(sum_chunk(ws, d_jobs, jobs, ws.pend.sub, ws.pend.used, ws.pend.nwave, acc, st));
+  MRS_TRY_STATUS(sum_chunk(ws, d_jobs, jobs, ws.pend.sub, ws.pend.used, ws.pend.nwave,
+                           ws.pend.direct, acc, st));
+  if (ws.pend.direct) {
+    MRS_TRY_HIP(hipGetLastError());
+    return MRS_OK;
+  }
   prof_begin(KID_RESOLVE, st);
   k_resolve<<<cdiv((size_t)total_pix, 256), 256, 0, st>>>(d_jobs, (int)jobs.size(), total_pix,
                                                            acc);
@@ -2070,10 +2269,10 @@ mrs_status end_batch(Workspace& ws, const DevJob* d_jobs, const std::vector<DevJ
 
 mrs_status launch_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs,
                         const std::vector<DevJob>& jobs, char* acc, size_t acc_bytes,
-                        hipStream_t st) {
+                        hipStream_t st, DevJob* store = nullptr) {
   if (ws.pend.active)
     return fail(MRS_ERR_INVALID_ARGUMENT, "render: a split render of this workspace is not ended");
-  mrs_status rc = begin_batch(ws, tu, d_jobs, jobs, acc, acc_bytes, st);
+  mrs_status rc = begin_batch(ws, tu, d_jobs, jobs, acc, acc_bytes, st, store);
   if (rc != MRS_OK) {
     ws.pend.active = false;
     return rc;
@@ -2159,9 +2358,8 @@ mrs_status render(const mrs_scene* s, const RenderArgs& a, hipStream_t st) {
   if (rc != MRS_OK) return rc;
   const size_t ab = acc_bytes_of(npix, a.fp64, a.out_layers != nullptr);
   if ((rc = ws_ensure_acc(ws, ab)) != MRS_OK) return rc;
-  k_store_job<<<1, 64, 0, st>>>(J, ws.one);
   std::vector<DevJob> jobs{J};
-  return launch_batch(ws, tu, ws.one, jobs, ws.acc, ab, st);
+  return launch_batch(ws, tu, ws.one, jobs, ws.acc, ab, st, ws.one);
 }
 
 // ------------------------------------------------------------ static workspace
@@ -2268,9 +2466,8 @@ mrs_status render_noalloc(const mrs_scene* s, const RenderArgs& a, hipStream_t s
   ProfPause pause;  // kernel timing would create events
   // the counters of this call start at zero and are not added to mrs_get_counters
   k_zero_words<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(ws.stats), 2 * MRS_NUM_COUNTERS);
-  k_store_job<<<1, 64, 0, st>>>(J, ws.one);
   std::vector<DevJob> jobs{J};
-  return launch_batch(ws, tu, ws.one, jobs, ws.acc, ab, st);
+  return launch_batch(ws, tu, ws.one, jobs, ws.acc, ab, st, ws.one);
 }
 
 }  // namespace mrs
@@ -2357,8 +2554,9 @@ mrs_status batch_render_fork(mrs_batch* b, hipStream_t st) {
   int64_t total = 0;
   for (const DevJob& J : b->jobs) total += (int64_t)J.spp * J.ww * J.wh;
   const Plan P = make_plan(b->tune, total);
-  k_zero_words<<<std::min(4096u, cdiv(b->acc_bytes / 4, 256)), 256, 0, st>>>(
-      (uint32_t*)b->d_acc, b->acc_bytes / 4);
+  if (total > P.K * P.Cs)  // the sums in memory of a render of several super-chunks
+    k_zero_words<<<std::min(4096u, cdiv(b->acc_bytes / 4, 256)), 256, 0, st>>>(
+        (uint32_t*)b->d_acc, b->acc_bytes / 4);
   if (P.K > 1) MRS_TRY_HIP(hipEventRecord(b->ws.ev_fork, st));
   MRS_TRY_HIP(hipGetLastError());
   b->ws.forked = true;
