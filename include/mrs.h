@@ -336,9 +336,18 @@ typedef struct mrs_tuning {
   int32_t streams;      /* 1..4 (default 3): a render's resident paths are cut into
                            this many sub-chunks, traced concurrently on internal
                            streams shared by the library (joined back into the
-                           caller's stream before the per-pixel sums) */
+                           caller's stream before the per-pixel sums); renders of
+                           at most 2^18 paths stay on the caller's stream */
   int32_t tail_bounce;  /* 1..65 (default 3): bounces from this one on are traced
-                           path by path in one launch (65: never) */
+                           path by path in one launch (65: never).  A render of
+                           at most 2^19 resident paths starts earlier: at bounce
+                           2, of at most 2^18 at bounce 1, and of at most 2^17
+                           (2^16 in scenes of fewer than 4096 triangles) at
+                           bounce 0, where the whole render is one launch unless
+                           extend, shade or shadow kernels are being recorded
+                           (mrs_profile_*), node visits are counted, or schedule,
+                           wave_extend = 0 or bvh_quantized ask for other kernels.
+                           Same results */
   int32_t bvh_builder;  /* MRS_BVH_PLOC (default) or MRS_BVH_LBVH; applies to
                            scenes built afterwards */
   int32_t conv_small_tiles; /* 0..2^30 (default 128): a 3x3 network conv whose

@@ -210,6 +210,7 @@ struct ProfPause {
   ProfPause(const ProfPause&) = delete;
   ProfPause& operator=(const ProfPause&) = delete;
 };
+bool prof_records(uint32_t ids);  // launches of any of these ids (a mask) are being recorded
 void prof_begin(int id, hipStream_t st);
 void prof_end(int id, hipStream_t st);
 mrs_status prof_enable(bool on);

@@ -190,6 +190,7 @@ struct TraceState {
 // loads.
 typedef float vfloat4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const vfloat4 gfloat4;
+typedef __attribute__((address_space(1))) const float gfloat;
 
 __device__ __forceinline__ float4 ld4(const gfloat4* p) {
   const vfloat4 v = *p;
@@ -499,6 +500,171 @@ __device__ void trace_stream(IO& io, uint32_t first, uint32_t stride, uint32_t n
   }
 }
 
+// ------------------------------------------------------------ quad traversal
+
+// A value of another lane of the quad (lane ^ X).
+template <int X>
+__device__ __forceinline__ uint32_t quad_xor(uint32_t v) {
+  constexpr int ctrl = X == 1 ? 0xB1 : X == 2 ? 0x4E : 0x1B;
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xf, 0xf, true);
+}
+template <int X>
+__device__ __forceinline__ float quad_xor(float v) {
+  return __uint_as_float(quad_xor<X>(__float_as_uint(v)));
+}
+
+constexpr int QUAD_TRIS = 4096;  // scenes of fewer triangles take the rules for small trees
+constexpr int QUAD_STACK = 4 * LDS_STACK;  // entries per ray held in LDS: a quad's four columns
+
+// The traversal of trace_stream with four neighbouring lanes (a quad) per ray: each
+// lane tests one of a node's four children and one of a leaf's triangles, so a visit
+// is ~55 instructions and 7 dword loads of one line instead of ~120 and 7 x 16 bytes,
+// and a wave's 16 rays diverge less than 64 would.  Bound by the latency of a ray's
+// dependent visits; where the launches that take it end and what that gains: quad_rays.  All control flow is the same in
+// the four lanes of a quad (it depends on the ray and on values combined over the
+// quad); each lane keeps the best hit among the triangles that it tested, combined by
+// (distance, primitive id) when the ray ends.  The boxes are tested by the same
+// slab(), the triangles by the same isect_tri, so every hit is bitwise trace_stream's.
+// IO::store runs in the four lanes alike.
+template <int MODE, class IO>
+__device__ void trace_quad(IO& io, uint32_t n, Stack& st) {
+  constexpr int LS = TB / 4;  // LDS stride of a ray's stack entries
+  const uint32_t ql = threadIdx.x & 3u;
+  const uint32_t first = (blockIdx.x * TB + threadIdx.x) >> 2, stride = gridDim.x * LS;
+  // the block's LDS and the launch's spill area, shared out to quads
+  lds_u32* lds = st.lds - threadIdx.x + (threadIdx.x >> 2);
+  uint32_t* spill = st.spill - (blockIdx.x * TB + threadIdx.x) + first;
+  uint32_t qi = first;
+  bool live = qi < n;
+  RayIn r;
+  TraceState ts;     // the lane's best hit
+  float tbest;       // the quad's
+  f3 inv, oi;
+  uint32_t node = EMPTY4, leaf = EMPTY4;
+  int32_t budget = 0;
+  int sp = 0;
+  bool occluded = false;
+  auto push = [&](int at, uint32_t v) {
+    if (at < QUAD_STACK) {
+      lds[at * LS] = v;
+    } else if (at < MAX_STACK4) {
+      spill[(size_t)(at - QUAD_STACK) * stride] = v;
+      ++st.spills;
+    } else {
+      st.overflow = true;
+    }
+  };
+  auto pop = [&]() -> uint32_t {
+    if (sp == 0) return EMPTY4;
+    --sp;
+    const uint32_t top = lds[(sp < QUAD_STACK ? sp : QUAD_STACK - 1) * LS];
+    if (sp < QUAD_STACK) return top;
+    return spill[(size_t)(sp - QUAD_STACK) * stride];
+  };
+  auto begin = [&]() {
+    ts = TraceState{r.tmax, NO_PRIM, 0.0f, 0.0f};
+    tbest = r.tmax;
+    inv = F3(safe_rcp(r.d.x), safe_rcp(r.d.y), safe_rcp(r.d.z));
+    oi = mul(r.o, inv);
+    sp = 0;
+    occluded = false;
+    budget = (int32_t)r.sc.nnodes + r.sc.ntris + 2;
+    node = leaf = EMPTY4;
+    if (r.sc.ntris > 0) {
+      if (r.sc.root & LEAF_BIT) leaf = r.sc.root;
+      else node = r.sc.root;
+    }
+  };
+  if (live) {
+    io.load(qi, r);
+    begin();
+  }
+  while (live) {
+    const bool any = MODE == PER_RAY ? r.any : MODE == ANY_HIT;
+    while (!(node & LEAF_BIT) && --budget > 0) {
+      if (node >= r.sc.nnodes) {  // keeps a corrupt reference harmless
+        node = pop();
+        continue;
+      }
+      const gfloat* nd = (const gfloat*)r.sc.nodes + (32 * (size_t)node + ql);
+      const uint32_t ref = __float_as_uint(nd[24]);
+      float tn;
+      const bool h = slab(nd[0], nd[4], nd[8], nd[12], nd[16], nd[20], oi, inv, tbest, tn) &
+                     (ref != EMPTY4);
+      // entry distances order as integers (tn >= 0); the lane makes keys distinct
+      const uint32_t key = h ? (__float_as_uint(tn) & ~3u) | ql : 0xfffffffcu | ql;
+      const uint32_t k1 = quad_xor<1>(key), k2 = quad_xor<2>(key), k3 = quad_xor<3>(key);
+      const int rank = (int)(k1 < key) + (int)(k2 < key) + (int)(k3 < key);
+      uint32_t cnt = h ? 1u : 0u;
+      cnt += quad_xor<1>(cnt);
+      cnt += quad_xor<2>(cnt);
+      uint32_t near = h && rank == 0 ? ref : 0u;
+      near |= quad_xor<1>(near);
+      near |= quad_xor<2>(near);
+      const int nhit = (int)cnt;
+      if (h && rank > 0) {  // the others onto the stack, far to near
+        const int at = sp + nhit - 1 - rank;
+        if (sp + 3 <= QUAD_STACK) lds[at * LS] = ref;
+        else push(at, ref);
+      }
+      if (nhit > 0) {
+        sp = min(sp + nhit - 1, MAX_STACK4);
+        node = near;
+      } else {
+        node = pop();
+      }
+      if ((node & LEAF_BIT) && node != EMPTY4 && leaf == EMPTY4) {
+        leaf = node;
+        node = pop();
+      }
+      if (__all(leaf != EMPTY4)) break;
+    }
+    // ---- the parked leaf, then leaves that follow on the stack
+    while (leaf != EMPTY4 && --budget > 0) {
+      const uint32_t f = leaf & 0x00ffffffu, cnt = ((leaf >> 24) & 3u) + 1u;
+      bool hit = false;
+      if (f + cnt <= (uint32_t)r.sc.ntris && ql < cnt)  // keeps a corrupt reference harmless
+        hit = isect_leaf(r.sc.leaf_tri, f + ql, r.o, r.d, r.x0, r.x1, r.x2, any, ts);
+      leaf = EMPTY4;
+      if (any) {
+        uint32_t o = hit ? 1u : 0u;
+        o |= quad_xor<1>(o);
+        o |= quad_xor<2>(o);
+        occluded = o != 0;
+        if (occluded) {
+          node = EMPTY4;
+          break;
+        }
+      } else {
+        tbest = fminf(ts.t, quad_xor<1>(ts.t));
+        tbest = fminf(tbest, quad_xor<2>(tbest));
+      }
+      if ((node & LEAF_BIT) && node != EMPTY4) {
+        leaf = node;
+        node = pop();
+      }
+    }
+    if ((node == EMPTY4 && leaf == EMPTY4) || budget <= 0) {  // ray finished
+      if (MODE != ANY_HIT) {
+        auto better = [&](float t, uint32_t prim, float b1, float b2) {
+          if (t < ts.t || (t == ts.t && prim < ts.prim)) ts = TraceState{t, prim, b1, b2};
+        };
+        better(quad_xor<1>(ts.t), quad_xor<1>(ts.prim), quad_xor<1>(ts.b1), quad_xor<1>(ts.b2));
+        better(quad_xor<2>(ts.t), quad_xor<2>(ts.prim), quad_xor<2>(ts.b1), quad_xor<2>(ts.b2));
+      }
+      if (io.store(qi, ts, occluded, r)) {
+        begin();
+      } else {
+        qi += stride;
+        live = qi < n;
+        if (live) {
+          io.load(qi, r);
+          begin();
+        }
+      }
+    }
+  }
+}
 
 // ------------------------------------------------------------ wave traversal
 
@@ -916,9 +1082,11 @@ struct ExtendIO {
 // instantiation per schedule, so that each kernel holds only its own queue code
 // (fewer registers for the static one).
 template <int MODE, bool COUNT, bool Q, int SCHED, class IO>
-__device__ __forceinline__ void trace_queue(IO& io, uint32_t n, uint32_t* fetch, Stack& st,
-                                            WorkCount& wc) {
-  if (SCHED == 0) {
+__device__ __forceinline__ void trace_queue(IO& io, uint32_t n, uint32_t quad, uint32_t* fetch,
+                                            Stack& st, WorkCount& wc) {
+  if (SCHED == 0 && !COUNT && !Q && n <= quad) {
+    trace_quad<MODE>(io, n, st);
+  } else if (SCHED == 0) {
     trace_stream<MODE, COUNT, Q>(io, blockIdx.x * TB + threadIdx.x, gridDim.x * TB, n, st, wc);
   } else {
     WaveQueue wq(fetch, true);
@@ -930,6 +1098,7 @@ __device__ __forceinline__ void trace_queue(IO& io, uint32_t n, uint32_t* fetch,
 
 template <bool COUNT, bool Q, int SCHED>
 __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(7))) void k_extend(const DevJob* __restrict__ jobs, int b,
+                                               uint32_t quad,
                                                const float4* __restrict__ rays,
                                                uint32_t* __restrict__ q,
                                                float4* __restrict__ hits,
@@ -941,7 +1110,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(7))) void k_
   Stack st{(lds_u32*)stk + threadIdx.x, spill + gtid, gridDim.x * TB, 0, 0u, false};
   WorkCount wc;
   ExtendIO<> io{jobs, rays, hits};
-  trace_queue<CLOSEST, COUNT, Q, SCHED>(io, n, q + Q_FETCH_EXT + b, st, wc);
+  trace_queue<CLOSEST, COUNT, Q, SCHED>(io, n, quad, q + Q_FETCH_EXT + b, st, wc);
   if (st.spills) atomicAdd(stats + 3, (unsigned long long)st.spills);
   if (st.overflow) atomicAdd(stats + 5, 1ull);
   if (COUNT && wc.visits) atomicAdd(stats + 6, (unsigned long long)wc.visits);
@@ -1275,13 +1444,14 @@ struct ShadowIO {
     Lv.x += S2.x;
     Lv.y += S2.y;
     Lv.z += S2.z;
-    L_buf[slot] = Lv;
+    L_buf[slot] = Lv;  // (a quad's four lanes load and store the same value together)
     return false;
   }
 };
 
 template <bool COUNT, bool Q, int SCHED>
 __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(7))) void k_shadow(const DevJob* __restrict__ jobs, int b,
+                                               uint32_t quad,
                                                const float4* __restrict__ shadow,
                                                uint32_t* __restrict__ q,
                                                float4* __restrict__ L_buf,
@@ -1293,7 +1463,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(7))) void k_
   Stack st{(lds_u32*)stk + threadIdx.x, spill + gtid, gridDim.x * TB, 0, 0u, false};
   WorkCount wc;
   ShadowIO io{jobs, shadow, L_buf};
-  trace_queue<ANY_HIT, COUNT, Q, SCHED>(io, n, q + Q_FETCH_SHD + b, st, wc);
+  trace_queue<ANY_HIT, COUNT, Q, SCHED>(io, n, quad, q + Q_FETCH_SHD + b, st, wc);
   if (st.spills) atomicAdd(stats + 3, (unsigned long long)st.spills);
   if (st.overflow) atomicAdd(stats + 5, 1ull);
   if (COUNT && wc.visits) atomicAdd(stats + 8, (unsigned long long)wc.visits);
@@ -1341,6 +1511,9 @@ __global__ __launch_bounds__(TB) void k_shadow_wave(const DevJob* __restrict__ j
 // next segment of the same path.  The arithmetic is the wavefront's
 // (shade_vertex; L += c after an unoccluded shadow ray), so results are
 // bitwise those of the wavefront.
+// GEN: whole paths -- queue entry qi is path slot qi, its camera ray is computed
+// here, and the first vertex stores its features and layers.
+template <bool GEN = false>
 struct PathIO {
   const DevJob* __restrict__ jobs;
   const float4* __restrict__ rays;
@@ -1348,6 +1521,9 @@ struct PathIO {
   float4* __restrict__ L_buf;
   int64_t g0;
   int b0;
+  int njobs = 0;
+  float4* __restrict__ aux_buf = nullptr;
+  float4* __restrict__ lay_buf = nullptr;
   uint32_t nrays = 0, nshadow = 0;  // segments traced by this lane
   // the lane's path
   uint32_t slot, j;
@@ -1371,6 +1547,17 @@ struct PathIO {
     ++nrays;
   }
   __device__ __forceinline__ void load(uint32_t qi, RayIn& r) {
+    if (GEN) {
+      f3 ro, rd;
+      slot = qi;
+      camera_ray(jobs, njobs, g0 + qi, j, ro, rd);
+      b = 0;
+      beta = F3(1.0f, 1.0f, 1.0f);
+      L = F3(0.0f, 0.0f, 0.0f);
+      pdf = 0.0f;
+      closest(r, ro, rd, NO_PRIM);
+      return;
+    }
     const float4 R0 = rays[2 * qi], R1 = rays[2 * qi + 1];
     const uint32_t tag = __float_as_uint(R1.w);
     slot = __float_as_uint(R0.w);
@@ -1388,7 +1575,9 @@ struct PathIO {
       Vertex v;
       shade_vertex(jobs[j], g0 + slot, b, o, d,
                    make_float4(ts.t, __uint_as_float(ts.prim), ts.b1, ts.b2), beta, L, pdf,
-                   nullptr, v);
+                   GEN && b == 0 && jobs[j].out_aux ? aux_buf + 2 * slot : nullptr, v);
+      if (GEN && b == 0 && jobs[j].out_layers)
+        lay_buf[slot] = make_float4(v.L.x, v.L.y, v.L.z, (float)v.lobe);
       beta = v.beta;
       pdf = v.pdf;
       L = v.L;
@@ -1429,6 +1618,7 @@ struct PathIO {
 
 template <bool COUNT, bool Q>
 __global__ __launch_bounds__(TB) void k_tail(const DevJob* __restrict__ jobs, int64_t g0, int b0,
+                                             uint32_t quad,
                                              const float4* __restrict__ rays,
                                              const uint32_t* __restrict__ q,
                                              float4* __restrict__ beta_buf,
@@ -1440,14 +1630,19 @@ __global__ __launch_bounds__(TB) void k_tail(const DevJob* __restrict__ jobs, in
   const uint32_t gtid = blockIdx.x * TB + threadIdx.x;
   Stack st{(lds_u32*)stk + threadIdx.x, spill + gtid, gridDim.x * TB, 0, 0u, false};
   WorkCount wc;
-  PathIO io;
+  PathIO<> io;
   io.jobs = jobs;
   io.rays = rays;
   io.beta_buf = beta_buf;
   io.L_buf = L_buf;
   io.g0 = g0;
   io.b0 = b0;
-  trace_stream<PER_RAY, COUNT, Q>(io, gtid, gridDim.x * TB, n, st, wc);
+  if (!COUNT && !Q && n <= quad) {
+    trace_quad<PER_RAY>(io, n, st);
+    if (threadIdx.x & 3) io.nrays = io.nshadow = 0;  // counted by one lane of the quad
+  } else {
+    trace_stream<PER_RAY, COUNT, Q>(io, gtid, gridDim.x * TB, n, st, wc);
+  }
   if (io.nrays) {
     atomicAdd(stats + 1, (unsigned long long)io.nrays);
     atomicAdd(stats + 12, (unsigned long long)io.nrays);
@@ -1461,6 +1656,37 @@ __global__ __launch_bounds__(TB) void k_tail(const DevJob* __restrict__ jobs, in
   if (COUNT && wc.visits) atomicAdd(stats + 14, (unsigned long long)wc.visits);
   if (COUNT && wc.tests) atomicAdd(stats + 15, (unsigned long long)wc.tests);
   if (COUNT && wc.max_steps) atomicMax(stats + 10, (unsigned long long)wc.max_steps);
+}
+
+// Whole paths, four lanes each, in one launch (small renders).
+__global__ __launch_bounds__(TB) void k_path(const DevJob* __restrict__ jobs, int njobs,
+                                             int64_t g0, uint32_t n,
+                                             float4* __restrict__ L_buf,
+                                             float4* __restrict__ aux_buf,
+                                             float4* __restrict__ lay_buf,
+                                             uint32_t* __restrict__ spill,
+                                             unsigned long long* __restrict__ stats) {
+  __shared__ uint32_t stk[LDS_STACK * TB];
+  const uint32_t gtid = blockIdx.x * TB + threadIdx.x;
+  Stack st{(lds_u32*)stk + threadIdx.x, spill + gtid, gridDim.x * TB, 0, 0u, false};
+  PathIO<true> io;
+  io.jobs = jobs;
+  io.njobs = njobs;
+  io.L_buf = L_buf;
+  io.aux_buf = aux_buf;
+  io.lay_buf = lay_buf;
+  io.g0 = g0;
+  trace_quad<PER_RAY>(io, n, st);
+  if ((threadIdx.x & 3) == 0 && io.nrays) {
+    atomicAdd(stats + 1, (unsigned long long)io.nrays);
+    atomicAdd(stats + 12, (unsigned long long)io.nrays);
+  }
+  if ((threadIdx.x & 3) == 0 && io.nshadow) {
+    atomicAdd(stats + 2, (unsigned long long)io.nshadow);
+    atomicAdd(stats + 13, (unsigned long long)io.nshadow);
+  }
+  if (st.spills) atomicAdd(stats + 3, (unsigned long long)st.spills);
+  if (st.overflow) atomicAdd(stats + 5, 1ull);
 }
 
 // ------------------------------------------------------------ per-pixel sums
@@ -1626,8 +1852,8 @@ __global__ __launch_bounds__(256) void k_accumulate(SumArgs A) {
 // lanes load 16 consecutive samples at once (256 bytes of radiance) into LDS, then each
 // lane adds them, in order, to the one or two channels that it holds.  With a thread
 // per pixel, a lane's loads are a pixel apart and few pixels leave the chip idle: 2.8 M
-// paths at 1024 spp are 2730 pixels, 11 blocks of one thread a pixel, 275 us; this
-// kernel, bound by the serial adds of a pixel, takes 35.  The lines (sum_class): with
+// paths at 1024 spp are 2730 pixels, 11 blocks of one thread a pixel, 293 us; this
+// kernel, bound by the serial adds of a pixel, takes 80 (FP64 sums).  The lines (sum_class): with
 // features or layers to sum (thread per pixel / 16 lanes, us) 8 spp 10.6 / 14.8, 16 spp
 // 21 / 15, 32 spp 26 / 21 at 57,600 pixels; radiance alone 16 spp 6.5 / 7.4, 32 spp
 // 10.0 / 9.2, 64 spp 17 / 13 at 16,384 pixels (1,024 pixels: 16 lanes ahead from 16 on;
@@ -1831,7 +2057,8 @@ struct Sub {
   hipStream_t s;
   int64_t lo;
   uint32_t n;
-  unsigned gb;
+  unsigned gb;  // blocks
+  unsigned gq;  // blocks of the launches that may take four lanes per ray
   size_t o;
   float4* rays[2];
   float4 *hits, *shadow, *beta, *L, *aux, *lay;
@@ -1892,7 +2119,10 @@ constexpr int64_t MAX_SUB_PATHS = int64_t(1) << 24;
 
 Plan make_plan(const mrs_tuning& tu, int64_t total) {
   Plan p;
-  p.K = std::max(1, std::min<int>(tu.streams, (int)(total / 65536)));
+  // one stream for few paths (us on one / three): 131,072 paths 850 / 890 (100,000
+  // triangles), 444 / 469 (10,000), 248 / 300 (34); 524,288 paths 1049 / 972, 606 / 582,
+  // 376 / 406
+  p.K = total <= (1 << 18) ? 1 : tu.streams;
   const int64_t C = std::max<int64_t>(1, std::min<int64_t>(tu.chunk_paths, total));
   p.Cs = std::min(MAX_SUB_PATHS, ((C + p.K - 1) / p.K + 255) & ~(int64_t)255);
   p.blocks_k = std::max(1, (tu.trace_blocks + p.K - 1) / p.K);
@@ -2106,6 +2336,44 @@ auto shadow_kernel(int sched) {
   return sched == 1 ? k_shadow<COUNT, Q, 1> : k_shadow<COUNT, Q, 0>;
 }
 
+// How a render of `resident` concurrent paths is cut into launches.  A launch takes at
+// least as long as its slowest ray, so few paths are better off in few launches: every
+// render of whole_paths' sizes runs its paths from camera ray to end in one launch
+// (k_path), up to 2^18 paths the path tail starts at bounce 1, up to 2^19 at bounce 2,
+// and above at tail_bounce.  All routes give bitwise the same results.  Times of one
+// render (us; depth 8, features; the 34-triangle box / 10,000 / 100,000 triangles):
+//   16,384 paths: tail at 3 204 / 517 / 1261, all quads, tail at 1 120 / 260 / 409,
+//     one launch 112 / 214 / 239;
+//   65,536: 279 / 645 / 1548, 231 / 319 / 428, 214 / 276 / 313;
+//   131,072: 332 / 816 / 1596, 243 / 437 / 471, 305 / 364 / 385;
+//   256,000: tail at 1 292 / 510 / 601, one launch 449 / 508 / 600;
+//   524,288: tail at 1 / 2 / 3 454 / 406 / 416, 679 / 582 / 622, 926 / 972 / 1086;
+//   1,024,000: 763 / 700 / 662, 937 / 817 / 782, 1455 / 1312 / 1405.
+int first_tail_bounce(int tail_bounce, int64_t resident) {
+  if (tail_bounce >= MAX_BOUNCE_SLOTS - 1) return tail_bounce;  // never
+  return std::min(tail_bounce, resident <= (1 << 18) ? 1 : resident <= (1 << 19) ? 2 : tail_bounce);
+}
+// One launch for whole paths; not while the kernels that it replaces are being timed.
+bool whole_paths(int tail_bounce, int64_t resident, int tris) {
+  if (tail_bounce >= MAX_BOUNCE_SLOTS - 1 ||
+      prof_records(1u << KID_EXTEND | 1u << KID_SHADE | 1u << KID_SHADOW))
+    return false;
+  return resident <= (tris < QUAD_TRIS ? 1 << 16 : 1 << 17);
+}
+
+// The most rays of a launch that it traces with four lanes each (trace_quad): while the
+// chip has lanes to spare, a ray's time counts, beyond that the instructions of all
+// rays do, which one lane per ray needs fewer of.  A tree of few nodes gains the least
+// per ray.  One render (us) with at most 2^15 / 2^16 / 2^17 / 2^18 rays of a launch on
+// quads: 100,000 triangles, 256,000 paths 1118 / 1123 / 1043 / 962, 524,288 paths on
+// three streams 1142 / 1131 / 972 / 972, 3,686,400 paths 2444 / 2231 / 2106 / 2102, but
+// six 7.4 M path frames, one after the other 21.66 / 21.65 / 22.43 / 22.88 ms; the box,
+// 256,000 paths 324 / 324 / 421 / 428, 524,288 on three streams 416 / 586 / 599 / 596.
+uint32_t quad_rays(int64_t resident, int K, int tris) {
+  if (tris < QUAD_TRIS) return 65536u / (uint32_t)K;
+  return resident <= (1 << 18) ? 1u << 18 : resident <= (1 << 20) ? 1u << 17 : 1u << 16;
+}
+
 // The launch sequence of a batch whose job table is on the device: chunks of at
 // most chunk_paths paths over the concatenated path space; per chunk, generate
 // (unless bounce 0 computes the camera rays itself), then extend / shade /
@@ -2123,14 +2391,20 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
     max_depth = std::max(max_depth, (int)J.max_depth);
   }
   const Plan P = make_plan(tu, total);
-  // wavefront bounces 0 .. nwave-1; the path tail takes bounces nwave .. max_depth
-  const int nwave = std::min(tu.tail_bounce, max_depth + 1);
+  const int64_t resident = std::min<int64_t>(total, P.K * P.Cs);
   const int dyn = tu.schedule;
   const bool qn = tu.bvh_quantized != 0;
   const bool count = g_count_work.load();
   // bounce 0 by the wave traversal: camera rays are computed where they are
   // used (wave traversal, shading) and never stored
   const bool gen_fused = !count && tu.wave_extend > 0;
+  int max_tris = 0;
+  for (const DevJob& J : jobs) max_tris = std::max(max_tris, J.sv.ntris);
+  const uint32_t quad = count || qn || dyn ? 0u : quad_rays(resident, P.K, max_tris);
+  const bool whole = gen_fused && quad > 0 && whole_paths(tu.tail_bounce, resident, max_tris);
+  // wavefront bounces 0 .. nwave-1; the path tail takes bounces nwave .. max_depth
+  const int nwave =
+      whole ? 0 : std::min(first_tail_bounce(tu.tail_bounce, resident), max_depth + 1);
   unsigned long long* stats = ws.stats;
   const size_t spill_k = (size_t)P.blocks_k * TB * (MAX_STACK4 - LDS_STACK);
   const bool forked = ws.forked && ws.fork_st == st;
@@ -2152,6 +2426,8 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
       u.lo = g0 + k * P.Cs;
       u.n = (uint32_t)std::min<int64_t>(P.Cs, total - u.lo);
       u.gb = std::min<unsigned>(P.blocks_k, cdiv(u.n, TB));
+      u.gq = std::max(u.gb, std::min<unsigned>(
+                                P.blocks_k, cdiv((size_t)std::min(u.n, quad) * 4, TB)));
       u.o = (size_t)k * P.Cs;
       u.rays[0] = ws.rays[0] + 2 * u.o;
       u.rays[1] = ws.rays[1] + 2 * u.o;
@@ -2170,7 +2446,7 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
       Sub& u = sub[k];
       if (P.K > 1) MRS_TRY_HIP(hipStreamWaitEvent(u.s, ws.ev_fork, 0));
       if (store && P.K == 1 && g0 == 0) k_begin<<<1, 256, 0, st>>>(jobs[0], store, u.q, u.n);
-      else k_reset<<<1, 256, 0, u.s>>>(u.q, u.n);
+      else if (!whole) k_reset<<<1, 256, 0, u.s>>>(u.q, u.n);
       if (!gen_fused) {
         prof_begin(KID_GENERATE, u.s);
         k_generate<<<cdiv(u.n, 256), 256, 0, u.s>>>(d_jobs, nj, u.lo, u.n, u.rays[0]);
@@ -2187,7 +2463,7 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
         } else {
           auto ext = count ? (qn ? extend_kernel<true, true>(dyn) : extend_kernel<true, false>(dyn))
                            : (qn ? extend_kernel<false, true>(dyn) : extend_kernel<false, false>(dyn));
-          ext<<<u.gb, TB, 0, u.s>>>(d_jobs, b, u.rays[b & 1], u.q, u.hits, u.spill, stats);
+          ext<<<u.gq, TB, 0, u.s>>>(d_jobs, b, quad, u.rays[b & 1], u.q, u.hits, u.spill, stats);
         }
         prof_end(KID_EXTEND, u.s);
       }
@@ -2210,19 +2486,26 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
           } else {
             auto shd = count ? (qn ? shadow_kernel<true, true>(dyn) : shadow_kernel<true, false>(dyn))
                              : (qn ? shadow_kernel<false, true>(dyn) : shadow_kernel<false, false>(dyn));
-            shd<<<u.gb, TB, 0, u.s>>>(d_jobs, b, u.shadow, u.q, u.L, u.spill, stats);
+            shd<<<u.gq, TB, 0, u.s>>>(d_jobs, b, quad, u.shadow, u.q, u.L, u.spill, stats);
           }
           prof_end(KID_SHADOW, u.s);
         }
       }
     }
-    if (nwave <= max_depth) {  // the remaining bounces, path by path
+    if (whole) {
+      for (int k = 0; k < used; ++k) {
+        Sub& u = sub[k];
+        prof_begin(KID_TAIL, u.s);
+        k_path<<<u.gq, TB, 0, u.s>>>(d_jobs, nj, u.lo, u.n, u.L, u.aux, u.lay, u.spill, stats);
+        prof_end(KID_TAIL, u.s);
+      }
+    } else if (nwave <= max_depth) {  // the remaining bounces, path by path
       for (int k = 0; k < used; ++k) {
         Sub& u = sub[k];
         prof_begin(KID_TAIL, u.s);
         auto tail = count ? (qn ? k_tail<true, true> : k_tail<true, false>)
                           : (qn ? k_tail<false, true> : k_tail<false, false>);
-        tail<<<u.gb, TB, 0, u.s>>>(d_jobs, u.lo, nwave, u.rays[nwave & 1], u.q, u.beta, u.L,
+        tail<<<u.gq, TB, 0, u.s>>>(d_jobs, u.lo, nwave, quad, u.rays[nwave & 1], u.q, u.beta, u.L,
                                    u.spill, stats);
         prof_end(KID_TAIL, u.s);
       }
