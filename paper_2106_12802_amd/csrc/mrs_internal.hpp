@@ -119,7 +119,8 @@ struct mrs_scene {
   int32_t nmats = 0;
   int32_t nlights = 0;
   bool bvh_built = false;
-  // device buffers
+  // device buffers; all but the BVH4 (d_nodes4, d_nodes4q) lie in d_slab
+  char* d_slab = nullptr;
   float4* d_tri_src = nullptr;  // ntris*3: v0, v1, v2 in primitive order (w unused)
   float4* d_prim_ng = nullptr;
   float4* d_prim_n = nullptr;
