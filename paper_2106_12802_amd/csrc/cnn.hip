@@ -593,18 +593,25 @@ __device__ __forceinline__ void rw_epilogue(const ConvArgs& p, const RwEpi& e, c
   }
 }
 
+template <int R, int WR, bool MULTI>
+constexpr int rw_lds() {  // BF16 values of LDS that a block takes
+  return (MULTI ? 2 : 1) * rw_tile_px<R, WR>() * RW_PITCH;
+}
+
+// Block (bx, by, bz) of the conv, with rw_lds() values of LDS from `lds` on.
 template <int R, int WR, int WN, bool MULTI, int MODE>
-__global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_p, int nsplit,
-                                                           BwdEpi be) {
+__device__ __forceinline__ void conv3_rw_block(const ConvArgs& p, int cout_p, int nsplit,
+                                               const BwdEpi& be, uint16_t* lds, int bx, int by,
+                                               int bz) {
   constexpr int THREADS = 64 * WR * WN, TH = WR * R, TILE = rw_tile_px<R, WR>();
   constexpr int TCH = TILE * 8, CNT = (TCH + THREADS - 1) / THREADS;
   constexpr int BN = WN * 16;
-  __shared__ __attribute__((aligned(16))) uint16_t tile[MULTI ? 2 : 1][TILE * RW_PITCH];
+  auto tile = reinterpret_cast<uint16_t(*)[TILE * RW_PITCH]>(lds);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kq = lane >> 4, li = lane & 15;
   const int wr = wave % WR, wn = wave / WR;
-  const int x0 = blockIdx.x * C3_W, y0 = blockIdx.y * TH;
-  const int b = blockIdx.z / nsplit, part = blockIdx.z - b * nsplit;
+  const int x0 = bx * C3_W, y0 = by * TH;
+  const int b = bz / nsplit, part = bz - b * nsplit;
   const int nper = cout_p / nsplit;  // output channels of this block (a multiple of BN)
   const int nchunk = MULTI ? p.cin_p >> 6 : 1;
   // this thread's chunks (8 channels of a pixel) of the input tile: byte offsets
@@ -682,12 +689,20 @@ __global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_
   }
 }
 
+template <int R, int WR, int WN, bool MULTI, int MODE>
+__global__ __launch_bounds__(64 * WR * WN) void k_conv3_rw(ConvArgs p, int cout_p, int nsplit,
+                                                           BwdEpi be) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[rw_lds<R, WR, MULTI>()];
+  conv3_rw_block<R, WR, WN, MULTI, MODE>(p, cout_p, nsplit, be, lds, blockIdx.x, blockIdx.y,
+                                         blockIdx.z);
+}
+
 // Runs the conv on k_conv3_rw if it fits: 3x3 over cin_p = 64 n channels of a
 // plain view, or the 64 channels of a shuffle by 2; no padding in K or in the
 // output channels, and channel strides that the epilogue's vectors can take.
 // The output channels are split over nsplit blocks per tile.
 template <int R, int WR, int WN, int MODE>
-bool try_conv3_rw(const ConvArgs& a, int cout_p, int nsplit, hipStream_t st, const BwdEpi* be) {
+bool conv3_rw_fits(const ConvArgs& a, int cout_p, int nsplit, const BwdEpi* be) {
   const bool multi = a.cin_p > 64;
   if (!a.frag || a.taps != 9 || (a.mode == VIEW_PLAIN && a.ca < a.cin_p) || a.cin_p % 64 || a.kp != 9 * a.cin_p ||
       (a.mode != VIEW_PLAIN && (multi || a.c0 != 64 || a.r != 2)) || a.cout != cout_p ||
@@ -701,6 +716,12 @@ bool try_conv3_rw(const ConvArgs& a, int cout_p, int nsplit, hipStream_t st, con
   if (MODE == RW_DG &&
       (be->mode == EPI_PLAIN ? be->stride % 8 != 0 : be->mode != EPI_DENSE))
     return false;
+  return true;
+}
+template <int R, int WR, int WN, int MODE>
+bool try_conv3_rw(const ConvArgs& a, int cout_p, int nsplit, hipStream_t st, const BwdEpi* be) {
+  if (!conv3_rw_fits<R, WR, WN, MODE>(a, cout_p, nsplit, be)) return false;
+  const bool multi = a.cin_p > 64;
   BwdEpi e;
   if (be) e = *be;
   else std::memset(&e, 0, sizeof e);
@@ -1408,18 +1429,24 @@ __device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi, int sh) {
   return ((lo >> sh) & 0xffffu) | ((hi >> sh) << 16);
 }
 
+template <int RN, int QX>
+constexpr int wgrad_lds() {  // floats of LDS that a block takes
+  return 4 * 4 * RN * 16 * QX + 4 * 16 * RN;
+}
+
+// Block (bx, by, bz), with wgrad_lds() floats of LDS from `lds` on.
 template <int RN, int QX, bool FAST>
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
+__device__ __forceinline__ void wgrad_block(const WgradArgs& a, float* lds, int bx, int by, int bz) {
   constexpr int NN = 16 * RN, NC = 16 * QX;
   constexpr int YW = RN == 1 ? 1 : RN / 2, XW = QX / 2;  // dwords per pixel
-  __shared__ __attribute__((aligned(16))) float red[4][NN * NC];
-  __shared__ float bred[4][NN];
+  auto red = reinterpret_cast<float(*)[4 * RN * NC]>(lds);
+  auto bred = reinterpret_cast<float(*)[NN]>(lds + 4 * 4 * RN * NC);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = lane & 15, kq = lane >> 4;
-  const int col0 = blockIdx.x * NC, n0 = blockIdx.y * NN;
+  const int col0 = bx * NC, n0 = by * NN;
   const ConvArgs& x = a.x;
   const int quarter = a.chunk >> 2;
-  const int pw0 = blockIdx.z * a.chunk + wave * quarter;
+  const int pw0 = bz * a.chunk + wave * quarter;
   const int pw1 = min(a.npix, pw0 + quarter);
   // this lane's X columns: QX channels cx.. of tap `tap` (one tap: cin_p % 8 == 0)
   const int colx = col0 + QX * i;
@@ -1430,7 +1457,7 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
   const int ny = RN == 1 ? ((n0 + i) & ~1) : n0 + RN * i;
   const bool yon = (RN == 1 ? n0 + i : ny) < a.dy_stride;
   const int ysh = RN == 1 ? 16 * ((n0 + i) & 1) : 0;
-  const bool bias_blk = blockIdx.x == 0 && a.bpart;
+  const bool bias_blk = bx == 0 && a.bpart;
 
   auto load_step = [&](int pk, Dw<YW>(&yd)[8], Dw<XW>(&xd)[8]) {
     const int pp0 = pk + 8 * kq;
@@ -1519,22 +1546,6 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
       xd[e] = xn[e];
     }
   }
-  // accumulator (c, d) of lane (j, g): rows 4g + v (channel n0 + RN row + c),
-  // column j (col0 + QX j + d)
-  {
-    const int j = lane & 15, g = lane >> 4;
-    float* r = red[wave];
-#pragma unroll
-    for (int c = 0; c < RN; ++c)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float* row = r + (RN * (4 * g + v) + c) * NC + QX * j;
-#pragma unroll
-        for (int d4 = 0; d4 < QX; d4 += 4)
-          *reinterpret_cast<float4*>(row + d4) =
-              make_float4(acc[c][d4][v], acc[c][d4 + 1][v], acc[c][d4 + 2][v], acc[c][d4 + 3][v]);
-      }
-  }
   if (bias_blk) {  // over kq (lanes 16 apart), then per wave into LDS
 #pragma unroll
     for (int c = 0; c < RN; ++c) {
@@ -1546,23 +1557,46 @@ __global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
       for (int c = 0; c < RN; ++c) bred[wave][RN == 1 ? i : RN * i + c] = bs[c];
     }
   }
-  __syncthreads();
+  // accumulator (c, d) of lane (j, g): rows 4g + v (channel n0 + RN row + c), column j
+  // (col0 + QX j + d).  The four waves' tiles are added a quarter (one v) at a time:
+  // 4 RN rows, 16 KB of LDS a block instead of 65, so that three blocks share a CU (168
+  // registers; a training step of the dense groups 3.71 -> 3.64 ms).
   const int t = threadIdx.x;
-  float* out = a.part + ((size_t)blockIdx.z * a.cout_p + n0) * x.kp + col0;
-  for (int f = t; f < NN * NC / 4; f += 256) {
-    const int nl = (4 * f) / NC, cl = (4 * f) % NC;
-    if (col0 + cl >= x.kp) continue;
-    const float4 r0 = reinterpret_cast<const float4*>(red[0])[f];
-    const float4 r1 = reinterpret_cast<const float4*>(red[1])[f];
-    const float4 r2 = reinterpret_cast<const float4*>(red[2])[f];
-    const float4 r3 = reinterpret_cast<const float4*>(red[3])[f];
-    *reinterpret_cast<float4*>(out + (size_t)nl * x.kp + cl) =
-        make_float4(((r0.x + r1.x) + r2.x) + r3.x, ((r0.y + r1.y) + r2.y) + r3.y,
-                    ((r0.z + r1.z) + r2.z) + r3.z, ((r0.w + r1.w) + r2.w) + r3.w);
+  float* out = a.part + ((size_t)bz * a.cout_p + n0) * x.kp + col0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    if (v) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < RN; ++c) {
+      float* row = red[wave] + (RN * kq + c) * NC + QX * i;
+#pragma unroll
+      for (int d4 = 0; d4 < QX; d4 += 4)
+        *reinterpret_cast<float4*>(row + d4) =
+            make_float4(acc[c][d4][v], acc[c][d4 + 1][v], acc[c][d4 + 2][v], acc[c][d4 + 3][v]);
+    }
+    __syncthreads();
+    for (int f = t; f < RN * NC; f += 256) {
+      const int rl = (4 * f) / NC, cl = (4 * f) % NC;
+      if (col0 + cl >= x.kp) continue;
+      const int nl = RN * (4 * (rl / RN) + v) + rl % RN;
+      const float4 r0 = reinterpret_cast<const float4*>(red[0])[f];
+      const float4 r1 = reinterpret_cast<const float4*>(red[1])[f];
+      const float4 r2 = reinterpret_cast<const float4*>(red[2])[f];
+      const float4 r3 = reinterpret_cast<const float4*>(red[3])[f];
+      *reinterpret_cast<float4*>(out + (size_t)nl * x.kp + cl) =
+          make_float4(((r0.x + r1.x) + r2.x) + r3.x, ((r0.y + r1.y) + r2.y) + r3.y,
+                      ((r0.z + r1.z) + r2.z) + r3.z, ((r0.w + r1.w) + r2.w) + r3.w);
+    }
   }
   if (bias_blk && t < NN && n0 + t < a.cout)
-    a.bpart[(size_t)blockIdx.z * a.cout + n0 + t] =
+    a.bpart[(size_t)bz * a.cout + n0 + t] =
         ((bred[0][t] + bred[1][t]) + bred[2][t]) + bred[3][t];
+}
+
+template <int RN, int QX, bool FAST>
+__global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a) {
+  __shared__ __attribute__((aligned(16))) float lds[wgrad_lds<RN, QX>()];
+  wgrad_block<RN, QX, FAST>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Sum of v[sp * stride] over the splits: eight independent partial sums
@@ -1583,22 +1617,52 @@ __device__ __forceinline__ float sum_splits(const float* __restrict__ v, size_t 
 // Sum the split partials in order and scatter into the master gradient layout
 // [cout][cin][k][k] followed by the bias.  Threads walk the packed layout
 // [n][tap cin_p + c], so that the split partials are read coalesced.
-__global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ part,
-                                                     const float* __restrict__ bpart, int splits,
-                                                     int cout, int cin, int ksz, int cin_p, int kp,
-                                                     int cout_p, float* __restrict__ g) {
-  const int64_t np = (int64_t)cout * kp;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void grad_reduce_block(const ReduceArgs& a, int block) {
+  const int64_t np = (int64_t)a.cout * a.kp;
+  const int64_t i = (int64_t)block * 256 + threadIdx.x;
   if (i < np) {
-    const int n = (int)(i / kp), col = (int)(i - (int64_t)n * kp);
-    const int tap = col / cin_p, c = col - tap * cin_p;
-    if (c >= cin || tap >= ksz * ksz) return;
-    const int ky = tap / ksz, kx = tap - ky * ksz;
-    g[((size_t)(n * cin + c) * ksz + ky) * ksz + kx] =
-        sum_splits(part + i, (size_t)cout_p * kp, splits);
-  } else if (i < np + cout) {
+    const int n = (int)(i / a.kp), col = (int)(i - (int64_t)n * a.kp);
+    const int tap = col / a.cin_p, c = col - tap * a.cin_p;
+    if (c >= a.cin || tap >= a.ksz * a.ksz) return;
+    const int ky = tap / a.ksz, kx = tap - ky * a.ksz;
+    a.g[((size_t)(n * a.cin + c) * a.ksz + ky) * a.ksz + kx] =
+        sum_splits(a.part + i, (size_t)a.cout_p * a.kp, a.splits);
+  } else if (i < np + a.cout) {
     const int n = (int)(i - np);
-    g[(size_t)cout * cin * ksz * ksz + n] = sum_splits(bpart + n, (size_t)cout, splits);
+    a.g[(size_t)a.cout * a.cin * a.ksz * a.ksz + n] =
+        sum_splits(a.bpart + n, (size_t)a.cout, a.splits);
+  }
+}
+__global__ __launch_bounds__(256) void k_grad_reduce(ReduceArgs a) {
+  grad_reduce_block(a, blockIdx.x);
+}
+
+// One layer of the backward pass in one launch: the data gradient (conv3_rw_block on
+// 16 x 8 tiles), the weight gradient's partial sums, which need nothing of it, and the
+// sum over the splits of the layer done before, whose partial sums lie in the other half
+// of the scratch.  Each is bound by latency -- a few dependent steps per block and one
+// to four blocks per CU -- so side by side they take little more than the longest.  The
+// blocks of the data gradient come first: the next layer waits for them.  Measured, one
+// training step of 16 images of 128 x 128: 1.58 -> 1.30 ms (16 blocks: 24 -> 15 us a
+// layer), 3.64 -> 3.19 ms (dense groups).  Larger tiles take 512 threads and longer
+// launches, which do not gain: the rule is the small plan's of k_conv3_rw.
+template <bool MULTI>
+__global__ __launch_bounds__(256, 3) void k_layer_bwd(ConvArgs p, int cout_p, int nsplit,
+                                                      BwdEpi be, int gx, int gy, int nd,
+                                                      WgradArgs w, int wx, int wy, int nw,
+                                                      ReduceArgs r) {
+  constexpr int BYTES_D = 2 * rw_lds<4, 2, MULTI>(), BYTES_W = 4 * wgrad_lds<4, 4>();
+  __shared__ __attribute__((aligned(16))) char lds[BYTES_D > BYTES_W ? BYTES_D : BYTES_W];
+  int i = blockIdx.x;
+  if (i < nd) {
+    const int t = i / gx;
+    conv3_rw_block<4, 2, 2, MULTI, RW_DG>(p, cout_p, nsplit, be, reinterpret_cast<uint16_t*>(lds),
+                                          i - t * gx, t % gy, t / gy);
+  } else if ((i -= nd) < nw) {
+    const int t = i / wx;
+    wgrad_block<4, 4, true>(w, reinterpret_cast<float*>(lds), i - t * wx, t % wy, t / wy);
+  } else {
+    grad_reduce_block(r, i - nw);
   }
 }
 
@@ -1750,11 +1814,34 @@ void launch_wgrad(const WgradArgs& a, int splits, hipStream_t st) {
   }
 }
 
-void launch_grad_reduce(const float* part, const float* bpart, int splits, const NetLayer& L,
-                        float* g, hipStream_t st) {
-  const int64_t n = (int64_t)L.cout * L.kp + L.cout;
-  k_grad_reduce<<<cdiv64(n, 256), 256, 0, st>>>(part, bpart, splits, L.cout, L.cin, L.k, L.cin_p,
-                                                 L.kp, L.cout_p, g);
+ReduceArgs reduce_args(const WgradArgs& w, int splits, const NetLayer& L, float* g) {
+  return ReduceArgs{w.part, w.bpart, splits, L.cout, L.cin, L.k, L.cin_p, L.kp, L.cout_p, g};
+}
+
+static unsigned reduce_blocks(const ReduceArgs& r) {
+  return r.part ? cdiv64((int64_t)r.cout * r.kp + r.cout, 256) : 0u;
+}
+
+void launch_grad_reduce(const ReduceArgs& r, hipStream_t st) {
+  if (r.part) k_grad_reduce<<<reduce_blocks(r), 256, 0, st>>>(r);
+}
+
+bool launch_layer_bwd(const ConvArgs& a, const BwdEpi& e, int cout_p, const WgradArgs& w,
+                      int splits, const ReduceArgs& r, hipStream_t st) {
+  const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
+  const int nsplit = cout_p / 32;
+  if (tiles >= conv_small_tiles() || w.cout_p < 64 || w.x.mode != VIEW_PLAIN || w.x.W % 8 ||
+      !conv3_rw_fits<4, 2, 2, RW_DG>(a, cout_p, nsplit, &e))
+    return false;
+  const int gx = (a.W + 15) / 16, gy = (a.H + 7) / 8;
+  const int wx = (int)cdiv64(w.x.kp, 64), wy = w.cout_p / 64;
+  const int64_t nd = (int64_t)gx * gy * a.B * nsplit, nw = (int64_t)wx * wy * splits;
+  const int64_t grid = nd + nw + reduce_blocks(r);
+  if (grid > (1 << 30)) return false;
+  auto kern = a.cin_p > 64 ? k_layer_bwd<true> : k_layer_bwd<false>;
+  kern<<<(unsigned)grid, 256, 0, st>>>(a, cout_p, nsplit, e, gx, gy, (int)nd, w, wx, wy, (int)nw, r);
+  count_conv(8);
+  return true;
 }
 
 void launch_out_grad(const OutGrad& o, const float* y, int64_t npix, uint16_t* g8,

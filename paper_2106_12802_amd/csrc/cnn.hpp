@@ -101,6 +101,14 @@ struct WgradArgs {
   float* bpart;          // [splits][cout]: the bias gradient's partial sums
 };
 
+// The sum of a layer's weight-gradient partials over the splits (part NULL: none).
+struct ReduceArgs {
+  const float* part;
+  const float* bpart;
+  int splits, cout, cin, ksz, cin_p, kp, cout_p;
+  float* g;  // the layer's master gradient
+};
+
 // How a backward pass gets its output gradient dL/dI_SR: from a loss of the
 // output against `tgt` (beta 0: L1, > 0: the robust loss; FP64 value in
 // *loss), or (tgt NULL) as given by the caller in `gout` (FP32 [P][3]).
@@ -169,8 +177,20 @@ ConvArgs base_args(const mrs_net* net, const NetLayer& L, int B, int H, int W);
 ConvArgs tconv_args(const mrs_net* net, const NetLayer& L, int B, int H, int W,
                     const uint16_t* dy);
 BwdEpi plain_epi();
-void wgrad(mrs_net* net, const NetLayer& L, const ConvArgs& x, const uint16_t* dy, int dy_stride,
-           hipStream_t st);
+// A backward pass, layer by layer from the output on.  The partial sums of a layer's
+// weight gradient are added up while the next layer runs, so they alternate between the
+// two halves of the scratch.
+struct BackwardPass {
+  mrs_net* net;
+  hipStream_t st;
+  int half = 0;
+  ReduceArgs pending{};
+  // The data gradient a, e (NULL: none) and the weight gradient of layer L with input
+  // view x and output gradient dy.
+  void layer(const ConvArgs* a, const BwdEpi* e, const NetLayer& L, const ConvArgs& x,
+             const uint16_t* dy, int dy_stride);
+  void finish();  // the last layer's sums
+};
 int wgrad_splits(int64_t npix, int kp, int cout_p, int& chunk);
 // Split-K partial buffers for the weight gradients at P HR pixels.
 mrs_status ensure_wpart(mrs_net* net, int64_t P, hipStream_t st);
@@ -198,8 +218,12 @@ void launch_input(const mrs_net* net, int B, int H, int W, const float* hr, cons
 void launch_init(float* dst, const NetLayer& L, uint64_t seed, hipStream_t st);
 void launch_dgrad(const ConvArgs& a, const BwdEpi& e, int cout_p, hipStream_t st);
 void launch_wgrad(const WgradArgs& a, int splits, hipStream_t st);
-void launch_grad_reduce(const float* part, const float* bpart, int splits, const NetLayer& L,
-                        float* g, hipStream_t st);
+ReduceArgs reduce_args(const WgradArgs& w, int splits, const NetLayer& L, float* g);
+void launch_grad_reduce(const ReduceArgs& r, hipStream_t st);
+// launch_dgrad, launch_wgrad and launch_grad_reduce(r) of an earlier layer in one launch;
+// false if the shapes do not fit it.
+bool launch_layer_bwd(const ConvArgs& a, const BwdEpi& e, int cout_p, const WgradArgs& w,
+                      int splits, const ReduceArgs& r, hipStream_t st);
 void launch_pack_all(const float* wm, const PackJob* jobs, int njobs, int64_t total,
                      uint16_t* packed, uint16_t* packed_t, hipStream_t st);
 void launch_out_grad(const OutGrad& o, const float* y, int64_t npix, uint16_t* g8,

@@ -353,14 +353,15 @@ mrs_status net_refresh_packed(mrs_net* net, hipStream_t st) {
 
 // Split-K partial buffers for the weight gradients of every layer at batch
 // size B x H x W (pixel count per layer from its resolution level).
+constexpr size_t BPART_FLOATS = 256 * 256;  // at most 128 splits of 256 channels
 mrs_status ensure_wpart(mrs_net* net, int64_t P, hipStream_t st) {
-  size_t need_w = 0, need_b = 0;
+  size_t need_w = 0;
   for (const NetLayer& L : net->layers) {
     int chunk;
     const int sp = wgrad_splits(P >> (2 * L.level), L.kp, L.cout_p, chunk);
     need_w = std::max(need_w, (size_t)sp * L.cout_p * L.kp);
-    need_b = std::max(need_b, (size_t)sp * L.cout);
   }
+  need_w = (need_w + 63) & ~(size_t)63;  // the second half is as aligned as the first
   if (need_w > net->wpart_floats) {
     if (net->d_wpart) {
       MRS_TRY_HIP(hipStreamSynchronize(st));
@@ -370,9 +371,8 @@ mrs_status ensure_wpart(mrs_net* net, int64_t P, hipStream_t st) {
     net->d_wpart = nullptr;
     net->d_bpart = nullptr;
     net->wpart_floats = 0;
-    if (hipMalloc(&net->d_wpart, sizeof(float) * need_w) != hipSuccess ||
-        hipMalloc(&net->d_bpart, sizeof(float) * std::max<size_t>(need_b, 256 * 256)) !=
-            hipSuccess) {
+    if (hipMalloc(&net->d_wpart, sizeof(float) * 2 * need_w) != hipSuccess ||
+        hipMalloc(&net->d_bpart, sizeof(float) * 2 * BPART_FLOATS) != hipSuccess) {
       (void)hipGetLastError();
       return fail(MRS_ERR_OUT_OF_MEMORY, "mrs_train_step: gradient scratch allocation failed");
     }
@@ -381,8 +381,8 @@ mrs_status ensure_wpart(mrs_net* net, int64_t P, hipStream_t st) {
   return MRS_OK;
 }
 
-void wgrad(mrs_net* net, const NetLayer& L, const ConvArgs& x, const uint16_t* dy, int dy_stride,
-           hipStream_t st) {
+void BackwardPass::layer(const ConvArgs* a, const BwdEpi* e, const NetLayer& L, const ConvArgs& x,
+                         const uint16_t* dy, int dy_stride) {
   WgradArgs w;
   w.x = x;
   w.dy = dy;
@@ -390,11 +390,21 @@ void wgrad(mrs_net* net, const NetLayer& L, const ConvArgs& x, const uint16_t* d
   w.cout_p = L.cout_p;
   w.npix = x.B * x.H * x.W;
   const int splits = wgrad_splits(w.npix, L.kp, L.cout_p, w.chunk);
-  w.part = net->d_wpart;
+  w.part = net->d_wpart + half * net->wpart_floats;
   w.cout = L.cout;
-  w.bpart = net->d_bpart;
-  launch_wgrad(w, splits, st);
-  launch_grad_reduce(net->d_wpart, net->d_bpart, splits, L, net->d_grad + L.w_off, st);
+  w.bpart = net->d_bpart + half * BPART_FLOATS;
+  if (!a || !launch_layer_bwd(*a, *e, L.coutp_t, w, splits, pending, st)) {
+    launch_grad_reduce(pending, st);
+    if (a) launch_dgrad(*a, *e, L.coutp_t, st);
+    launch_wgrad(w, splits, st);
+  }
+  pending = reduce_args(w, splits, L, net->d_grad + L.w_off);
+  half ^= 1;
+}
+
+void BackwardPass::finish() {
+  launch_grad_reduce(pending, st);
+  pending = ReduceArgs{};
 }
 
 ConvArgs tconv_args(const mrs_net* net, const NetLayer& L, int B, int H, int W,
@@ -559,6 +569,7 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
   const int h = H / NET_SCALE, w = W / NET_SCALE;
   const NetLayer& Lu = Ls[3 + 2 * NET_NRES];
   const NetLayer& Lr = Ls[4 + 2 * NET_NRES];
+  BackwardPass pass{net, st};
   // rec: d[shuffle(U), h0] -> dU (masked by U > 0, LR layout) and dh0a (FP32)
   {
     ConvArgs a = tconv_args(net, Lr, B, H, W, A.g8);
@@ -571,7 +582,6 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
     e.c_split = NET_UPCH;
     e.stride2 = Lu.cout;
     e.r = NET_SCALE;
-    launch_dgrad(a, e, Lr.coutp_t, st);
     ConvArgs x = base_args(net, Lr, B, H, W);
     x.mode = VIEW_SHUFFLE_CONCAT;
     x.a = A.U;
@@ -580,7 +590,7 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
     x.r = NET_SCALE;
     x.b = A.h0;
     x.cb = NET_FEAT;
-    wgrad(net, Lr, x, A.g8, 8, st);
+    pass.layer(&a, &e, Lr, x, A.g8, 8);
   }
   // up: dFDF (FP32) and 0.1 dFDF (BF16) = gradient of the last trunk conv
   {
@@ -589,11 +599,10 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
     e.out_f = A.dfdf;
     e.out_h = A.drh;
     e.out_h_scale = NET_RES_SCALE;
-    launch_dgrad(a, e, Lu.coutp_t, st);
     ConvArgs x = base_args(net, Lu, B, h, w);
     x.a = A.rh[NET_NRES];
     x.ca = NET_FEAT;
-    wgrad(net, Lu, x, A.dU, Lu.cout, st);
+    pass.layer(&a, &e, Lu, x, A.dU, Lu.cout);
   }
   const float* dr = A.dfdf;
   for (int i = NET_NRES - 1; i >= 0; --i) {
@@ -604,11 +613,10 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
       BwdEpi e = plain_epi();
       e.mask = A.th[i];
       e.out_h = A.dth;
-      launch_dgrad(a, e, Lb.coutp_t, st);
       ConvArgs x = base_args(net, Lb, B, h, w);
       x.a = A.th[i];
       x.ca = NET_FEAT;
-      wgrad(net, Lb, x, A.drh, NET_FEAT, st);
+      pass.layer(&a, &e, Lb, x, A.drh, NET_FEAT);
     }
     {  // conv a: dr_i = dr_{i+1} + W_a^T dt; at i = 0 add dFDF and mask by F0 > 0
       ConvArgs a = tconv_args(net, La, B, h, w, A.dth);
@@ -623,11 +631,10 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
         e.mask = A.f0h;
         e.out_h = A.df0h;
       }
-      launch_dgrad(a, e, La.coutp_t, st);
       ConvArgs x = base_args(net, La, B, h, w);
       x.a = A.rh[i];
       x.ca = NET_FEAT;
-      wgrad(net, La, x, A.dth, NET_FEAT, st);
+      pass.layer(&a, &e, La, x, A.dth, NET_FEAT);
       dr = A.drf[i & 1];
     }
   }
@@ -645,7 +652,6 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
     e.mask2 = A.h0;
     e.out_h2 = A.dh0h;
     e.r = NET_SCALE;
-    launch_dgrad(a, e, Lf.coutp_t, st);
     ConvArgs x = base_args(net, Lf, B, h, w);
     x.mode = VIEW_CONCAT_UNSHUFFLE;
     x.a = A.fl;
@@ -653,18 +659,19 @@ void backward(mrs_net* net, const TrainArena& A, int B, int H, int W, hipStream_
     x.b = A.h0;
     x.cb = NET_FEAT;
     x.r = NET_SCALE;
-    wgrad(net, Lf, x, A.df0h, NET_FEAT, st);
+    pass.layer(&a, &e, Lf, x, A.df0h, NET_FEAT);
   }
   {  // encoders: weight gradients only
     ConvArgs x = base_args(net, Ls[1], B, h, w);
     x.a = A.xl;
     x.ca = 8;
-    wgrad(net, Ls[1], x, A.dflh, NET_FEAT, st);
+    pass.layer(nullptr, nullptr, Ls[1], x, A.dflh, NET_FEAT);
     x = base_args(net, Ls[0], B, H, W);
     x.a = A.xh;
     x.ca = 16;
-    wgrad(net, Ls[0], x, A.dh0h, NET_FEAT, st);
+    pass.layer(nullptr, nullptr, Ls[0], x, A.dh0h, NET_FEAT);
   }
+  pass.finish();
 }
 
 mrs_status check_train_args(mrs_net* n, int B, const float* hr, const float* aux,

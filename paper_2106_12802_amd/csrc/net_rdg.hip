@@ -223,6 +223,7 @@ void backward(mrs_net* net, const RdgActs& A, const RdgGrads& G, int B, int H, i
   const std::vector<NetLayer>& Ls = net->layers;
   const int Dn = arch_dsf(net->arch), sc = 1 << Dn;
   const int h = H / sc, w = W / sc;
+  BackwardPass pass{net, st};
   // rec (k = D) and upscaling steps D-1 .. 1: d shuffle2(U_{k-1}) -> dU_{k-1}
   // (masked by U_{k-1} > 0, stored like U_{k-1})
   for (int k = Dn; k >= 1; --k) {
@@ -238,8 +239,7 @@ void backward(mrs_net* net, const RdgActs& A, const RdgGrads& G, int B, int H, i
     e.c_split = NET_FEAT;
     e.stride2 = 4 * NET_FEAT;
     e.r = 2;
-    launch_dgrad(a, e, L.coutp_t, st);
-    wgrad(net, L, shuffle_view(net, L, B, hk, wk, A.U[k - 1]), dy, dy_stride, st);
+    pass.layer(&a, &e, L, shuffle_view(net, L, B, hk, wk, A.U[k - 1]), dy, dy_stride);
   }
   {  // up0: dFDF (FP32 + BF16)
     const NetLayer& Lu0 = Ls[RDG_L_UP];
@@ -247,11 +247,10 @@ void backward(mrs_net* net, const RdgActs& A, const RdgGrads& G, int B, int H, i
     BwdEpi e = plain_epi();
     e.out_f = G.dfdf;
     e.out_h = G.dfdfh;
-    launch_dgrad(a, e, Lu0.coutp_t, st);
     ConvArgs x = base_args(net, Lu0, B, h, w);
     x.a = A.fdfh;
     x.ca = NET_FEAT;
-    wgrad(net, Lu0, x, G.dU[0], Lu0.cout, st);
+    pass.layer(&a, &e, Lu0, x, G.dU[0], Lu0.cout);
   }
   // groups, last to first; dF = gradient of F_g (the group's output)
   const float* dFf = G.dfdf;
@@ -293,8 +292,7 @@ void backward(mrs_net* net, const RdgActs& A, const RdgGrads& G, int B, int H, i
             e.out_h = G.dsh[b & 1];
           }
         }
-        launch_dgrad(a, e, L.coutp_t, st);
-        wgrad(net, L, dense_view(net, L, B, h, w, D), dy, NET_FEAT, st);
+        pass.layer(&a, &e, L, dense_view(net, L, B, h, w, D), dy, NET_FEAT);
       }
       if (b > 0) {
         dsf = G.dsf[b & 1];
@@ -319,7 +317,6 @@ void backward(mrs_net* net, const RdgActs& A, const RdgGrads& G, int B, int H, i
     e.out_h2 = G.dh0h;
     e.r = sc;
     e.dsf = Dn;
-    launch_dgrad(a, e, Lf.coutp_t, st);
     ConvArgs x = base_args(net, Lf, B, h, w);
     x.mode = VIEW_CONCAT_UNSHUFFLE;
     x.a = A.fl;
@@ -328,18 +325,19 @@ void backward(mrs_net* net, const RdgActs& A, const RdgGrads& G, int B, int H, i
     x.cb = NET_FEAT;
     x.r = sc;
     x.dsf = Dn;
-    wgrad(net, Lf, x, G.df0h, NET_FEAT, st);
+    pass.layer(&a, &e, Lf, x, G.df0h, NET_FEAT);
   }
   {  // encoders: weight gradients only
     ConvArgs x = base_args(net, Ls[1], B, h, w);
     x.a = A.xl;
     x.ca = 8;
-    wgrad(net, Ls[1], x, G.dflh, NET_FEAT, st);
+    pass.layer(nullptr, nullptr, Ls[1], x, G.dflh, NET_FEAT);
     x = base_args(net, Ls[0], B, H, W);
     x.a = A.xh;
     x.ca = 16;
-    wgrad(net, Ls[0], x, G.dh0h, NET_FEAT, st);
+    pass.layer(nullptr, nullptr, Ls[0], x, G.dh0h, NET_FEAT);
   }
+  pass.finish();
 }
 
 }  // namespace
