@@ -124,8 +124,11 @@ __device__ __forceinline__ bf16x8 load_chunk(const ConvArgs& p, int b, int y, in
   return view_chunk(p, b, y, x, c);
 }
 
-// Accumulates the 32 x (16 NT) output tile of one wave over the whole K.
-template <int NT>
+// Accumulates the 32 x (16 NT) output tile of one wave over the whole K.  SWAP: the
+// weights are the MFMA's A operand, so that a lane holds 4 channels of one pixel
+// (acc[r][j]: pixel 16 r + lane % 16, channels 16 j + 4 (lane / 16) ..) instead of 4
+// pixels of one channel; bitwise the same sums.
+template <int NT, bool SWAP = false>
 __device__ __forceinline__ void conv_mainloop(const ConvArgs& p, int M, int m0, int n0, int lane,
                                               f32x4 (&acc)[2][NT]) {
   const int kq = lane >> 4, li = lane & 15;
@@ -170,7 +173,8 @@ __device__ __forceinline__ void conv_mainloop(const ConvArgs& p, int M, int m0, 
     for (int r = 0; r < 2; ++r)
 #pragma unroll
       for (int j = 0; j < NT; ++j)
-        acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[r], Bv[j], acc[r][j], 0, 0, 0);
+        acc[r][j] = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(Bv[j], A[r], acc[r][j], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[r], Bv[j], acc[r][j], 0, 0, 0);
 #pragma unroll
     for (int r = 0; r < 2; ++r) A[r] = An[r];
 #pragma unroll
@@ -1063,10 +1067,85 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs p) {
   conv_epilogue<NT>(p, acc, m, n0, li, in);
 }
 
+// What the epilogue of k_dgrad does to 4 channels n .. n + 3 (n a multiple of 4, as are
+// all strides and splits) of pixel m: the tensors to add, the mask, the outputs, with
+// offsets in elements.
+struct DgOut {
+  const float *a1, *a2;
+  const uint16_t* mask;
+  float* out_f;
+  uint16_t* out_h;
+  float h_scale;
+};
+
+// b, y, x: pixel m's place in the conv's image.
+template <int MODE>
+__device__ __forceinline__ DgOut dg_out(const ConvArgs& p, const BwdEpi& e, int64_t m, int b,
+                                        int y, int x, int n) {
+  DgOut o{nullptr, nullptr, nullptr, nullptr, nullptr, 1.0f};
+  if (MODE == EPI_PLAIN) {
+    const int64_t i = m * e.stride + n;
+    o.a1 = e.add1 ? e.add1 + i : nullptr;
+    o.a2 = e.add2 ? e.add2 + i : nullptr;
+    o.mask = e.mask ? e.mask + i : nullptr;
+    o.out_f = e.out_f ? e.out_f + i : nullptr;
+    o.out_h = e.out_h ? e.out_h + i : nullptr;
+    o.h_scale = e.out_h_scale;
+  } else if (MODE == EPI_REC_SPLIT) {  // this conv at HR; [shuffle(U) | h0]
+    if (n < e.c_split) {
+      const int Y = y / e.r, X = x / e.r, hh = p.H / e.r, ww = p.W / e.r;
+      const int64_t i = ((int64_t)(b * hh + Y) * ww + X) * e.stride2 +
+                        ((y - Y * e.r) * e.r + x - X * e.r) * e.c_split + n;
+      o.mask = e.mask + i;
+      o.out_h = e.out_h + i;
+    } else {
+      o.out_f = e.out_f + m * e.stride + (n - e.c_split);
+    }
+  } else if (MODE == EPI_FUSE_SPLIT) {  // this conv at LR; [fl | unshuffle(h0)]
+    if (n < e.c_split) {
+      const int64_t i = m * e.c_split + n;
+      o.mask = e.mask + i;
+      o.out_h = e.out_h + i;
+    } else {
+      const int cc = n - e.c_split, q = cc / e.stride, ch = cc - q * e.stride;
+      int I, J;
+      unshuffle_slot(q, e.r, e.dsf, I, J);
+      const int64_t i =
+          ((int64_t)(b * p.H * e.r + y * e.r + I) * (p.W * e.r) + x * e.r + J) * e.stride + ch;
+      o.a1 = e.add1 ? e.add1 + i : nullptr;
+      o.mask = e.mask2 + i;
+      o.out_h = e.out_h2 + i;
+    }
+  } else {  // EPI_DENSE: input slices 0 .. k-1 of a residual dense block
+    const int sl = n >> 6, ch = n & 63;
+    const int64_t gi = m * RDG_DENSE + n, i64 = m * NET_FEAT + ch;
+    if (e.k == 1) {  // x_0 complete: the gradient of the block input (a third sum: add2)
+      o.a1 = e.ga + gi;
+      o.a2 = e.add1 ? e.add1 + i64 : nullptr;
+      o.mask = e.mask0 ? e.dense + gi : nullptr;
+      o.out_f = e.out_f ? e.out_f + i64 : nullptr;
+      o.out_h = e.out_h + i64;
+    } else if (sl == e.k - 1) {  // x_{k-1} complete: through its ReLU
+      o.a1 = e.fusing ? nullptr : e.ga + gi;
+      o.mask = e.dense + gi;
+      o.out_h = e.dy_next + i64;
+    } else {
+      o.a1 = !e.fusing ? e.ga + gi : sl == 0 ? e.ds + i64 : nullptr;
+      o.out_f = e.ga + gi;
+    }
+  }
+  return o;
+}
+
 // Data gradient of a conv: the same implicit GEMM over dY with the packed
 // transposed, flipped weights; the epilogue applies the backward of what
-// surrounds the conv (ReLU masks, residual sums, the (un)shuffle views).
-template <int NT>
+// surrounds the conv (ReLU masks, residual sums, the (un)shuffle views).  Bound by the
+// epilogue's traffic in the fuse and reconstruction convs that run here; a lane holds 4
+// channels of a pixel, so that it moves 8 and 16 bytes at a time (2 and 4 with the
+// operands' roles exchanged).  16 images of 128 x 128: fuse 113 -> 51 us (136 MB, 28 us
+// at the rate of a copy), reconstruction 64 -> 34 (90 MB, 19 us); with 64 shuffled
+// channels 90 -> 41 and 78 -> 30 us.
+template <int NT, int MODE>
 __global__ __launch_bounds__(256) void k_dgrad(ConvArgs p, BwdEpi e) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -1075,75 +1154,44 @@ __global__ __launch_bounds__(256) void k_dgrad(ConvArgs p, BwdEpi e) {
   if (m0 >= M) return;
   const int n0 = blockIdx.y * (NT * 16);
   f32x4 acc[2][NT];
-  conv_mainloop<NT>(p, M, m0, n0, lane, acc);
+  conv_mainloop<NT, true>(p, M, m0, n0, lane, acc);
   const int kq = lane >> 4, li = lane & 15;
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
+    const int m = m0 + r * 16 + li;
+    if (m >= M) continue;
+    const int x = m % p.W, t = m / p.W, y = t % p.H, b = t / p.H;
+    DgOut o[NT];
+    f32x4 v1[NT], v2[NT], v3[NT];
+    u32x2 mk[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {  // loads before stores
+      const int n = n0 + j * 16 + kq * 4;
+      if (n >= p.cout) continue;
+      o[j] = dg_out<MODE>(p, e, m, b, y, x, n);
+      if (o[j].a1) v1[j] = *reinterpret_cast<const f32x4*>(o[j].a1);
+      if (o[j].a2) v2[j] = *reinterpret_cast<const f32x4*>(o[j].a2);
+      if (MODE == EPI_DENSE && e.k == 1 && e.add2)
+        v3[j] = *reinterpret_cast<const f32x4*>(e.add2 + (int64_t)m * NET_FEAT + (n & 63));
+      if (o[j].mask) mk[j] = *reinterpret_cast<const u32x2*>(o[j].mask);
+    }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const int n = n0 + j * 16 + li;
-      if (n >= p.cout) continue;
+      if (n0 + j * 16 + kq * 4 >= p.cout) continue;
+      f32x4 g = acc[r][j];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int m = m0 + r * 16 + kq * 4 + v;
-        if (m >= M) continue;
-        float y = acc[r][j][v] * e.scale;
-        if (e.mode == EPI_PLAIN) {
-          const size_t idx = (size_t)m * e.stride + n;
-          if (e.add1) y += e.add1[idx];
-          if (e.add2) y += e.add2[idx];
-          if (e.mask && !pos_bf(e.mask[idx])) y = 0.0f;
-          if (e.out_f) e.out_f[idx] = y;
-          if (e.out_h) e.out_h[idx] = f2bf(y * e.out_h_scale);
-        } else if (e.mode == EPI_REC_SPLIT) {  // this conv at HR; [shuffle(U) | h0]
-          const int x = m % p.W, t = m / p.W, yy = t % p.H, b = t / p.H;
-          if (n < e.c_split) {
-            const int hh = p.H / e.r, ww = p.W / e.r;
-            const size_t idx = ((size_t)(b * hh + yy / e.r) * ww + x / e.r) * e.stride2 +
-                               ((yy % e.r) * e.r + (x % e.r)) * e.c_split + n;
-            if (!pos_bf(e.mask[idx])) y = 0.0f;
-            e.out_h[idx] = f2bf(y);
-          } else {
-            e.out_f[(size_t)m * e.stride + (n - e.c_split)] = y;
-          }
-        } else if (e.mode == EPI_FUSE_SPLIT) {  // this conv at LR; [fl | unshuffle(h0)]
-          if (n < e.c_split) {
-            const size_t idx = (size_t)m * e.c_split + n;
-            if (!pos_bf(e.mask[idx])) y = 0.0f;
-            e.out_h[idx] = f2bf(y);
-          } else {
-            const int X = m % p.W, t = m / p.W, Y = t % p.H, b = t / p.H;
-            const int cc = n - e.c_split, q = cc / e.stride, ch = cc - q * e.stride;
-            int I, J;
-            unshuffle_slot(q, e.r, e.dsf, I, J);
-            const int hy = Y * e.r + I, hx = X * e.r + J;
-            const size_t hidx = ((size_t)(b * p.H * e.r + hy) * (p.W * e.r) + hx) * e.stride + ch;
-            float v2 = e.add1 ? y + e.add1[hidx] : y;
-            if (!pos_bf(e.mask2[hidx])) v2 = 0.0f;
-            e.out_h2[hidx] = f2bf(v2);
-          }
-        } else {  // EPI_DENSE: input slices 0 .. k-1 of a residual dense block
-          const int sl = n >> 6, ch = n & 63;
-          const size_t gi = (size_t)m * RDG_DENSE + n, i64 = (size_t)m * NET_FEAT + ch;
-          if (e.k == 1) {  // x_0 complete: the gradient of the block input
-            y += e.ga[gi];
-            if (e.add1) y += e.add1[i64];
-            if (e.add2) y += e.add2[i64];
-            if (e.mask0 && !pos_bf(e.dense[gi])) y = 0.0f;
-            if (e.out_f) e.out_f[i64] = y;
-            e.out_h[i64] = f2bf(y);
-          } else if (sl == e.k - 1) {  // x_{k-1} complete: through its ReLU
-            if (!e.fusing) y += e.ga[gi];
-            if (!pos_bf(e.dense[gi])) y = 0.0f;
-            e.dy_next[i64] = f2bf(y);
-          } else if (e.fusing) {
-            if (sl == 0) y += e.ds[i64];
-            e.ga[gi] = y;
-          } else {
-            e.ga[gi] += y;
-          }
-        }
+      for (int q = 0; q < 4; ++q) {
+        g[q] *= e.scale;
+        if (o[j].a1) g[q] += v1[j][q];
+        if (o[j].a2) g[q] += v2[j][q];
+        if (MODE == EPI_DENSE && e.k == 1 && e.add2) g[q] += v3[j][q];
+        if (o[j].mask && !pos_bf((uint16_t)(mk[j][q >> 1] >> (16 * (q & 1))))) g[q] = 0.0f;
       }
+      if (o[j].out_f) *reinterpret_cast<f32x4*>(o[j].out_f) = g;
+      if (o[j].out_h)
+        *reinterpret_cast<u32x2*>(o[j].out_h) =
+            u32x2{f2bf2(g[0] * o[j].h_scale, g[1] * o[j].h_scale),
+                  f2bf2(g[2] * o[j].h_scale, g[3] * o[j].h_scale)};
     }
   }
 }
@@ -1390,7 +1438,7 @@ __global__ __launch_bounds__(256) void k_init(float* __restrict__ dst, int64_t n
 // this step's MFMAs.  The 4 waves of a workgroup take consecutive quarters of
 // the split's pixels and their tiles are summed in LDS in wave order
 // (deterministic).  The first column block also sums dY, the bias gradient.
-// FAST: plain view and W % 8 == 0, so a lane's 8 pixels share one image row.
+// VIEW: how the lane finds X (WgView).
 template <int W>
 struct Dw {
   uint32_t v[W];
@@ -1429,13 +1477,63 @@ __device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi, int sh) {
   return ((lo >> sh) & 0xffffu) | ((hi >> sh) << 16);
 }
 
+// Input views of the weight gradient: a plain tensor or one shuffled by a power of two,
+// with rows of a multiple of 8 pixels, so that the 8 pixels a lane takes share one image
+// row and a shift or two give their places; any other view, pixel by pixel (view_ptr).
+// Measured, view_ptr against shifts, 16 images of 128 x 128: reconstruction 93 / 52 us
+// (80 channels), 85 / 40 (64), second upscaling step 147 / 117, fuse 32 / 22.
+enum WgView { WG_ANY = 0, WG_PLAIN = 1, WG_POW2 = 2 };
+
+// One channel's place in a view whose shuffle factor is a power of two: pixel (b, y, x)
+// is at base + b sb + (y >> l) sy + (y & msk) sy2 + (x >> l) sx + (x & msk) sx2 (as
+// view_ptr gives it).
+struct LaneView {
+  const uint16_t* base;
+  int64_t sb, sy;
+  int sy2, sx, sx2, l, msk;
+  __device__ __forceinline__ const uint16_t* row(int b, int y) const {
+    return base + b * sb + (y >> l) * sy + (y & msk) * sy2;
+  }
+  __device__ __forceinline__ int col(int x) const { return (x >> l) * sx + (x & msk) * sx2; }
+};
+__device__ __forceinline__ LaneView lane_view(const ConvArgs& p, int c) {
+  LaneView v{p.a + c, 0, 0, 0, p.ca, 0, 0, 0};
+  int rows = p.H, cols = p.W;
+  if (p.mode == VIEW_CONCAT_UNSHUFFLE && c >= p.ca) {
+    const int cc = c - p.ca, q = cc / p.cb;
+    int I, J;
+    unshuffle_slot(q, p.r, p.dsf, I, J);
+    v.base = p.b + ((int64_t)I * p.W * p.r + J) * p.cb + (cc - q * p.cb);
+    v.sx = p.r * p.cb;
+    v.sy = (int64_t)p.W * p.r * p.r * p.cb;
+    v.sb = p.H * v.sy;
+    return v;
+  }
+  if (p.mode == VIEW_SHUFFLE_CONCAT) {
+    if (c < p.c0) {
+      v.l = 31 - __clz(p.r);
+      v.msk = p.r - 1;
+      v.sy2 = p.r * p.c0;
+      v.sx2 = p.c0;
+      rows >>= v.l;
+      cols >>= v.l;
+    } else {
+      v.base = p.b + (c - p.c0);
+      v.sx = p.cb;
+    }
+  }
+  v.sy = (int64_t)cols * v.sx;
+  v.sb = rows * v.sy;
+  return v;
+}
+
 template <int RN, int QX>
 constexpr int wgrad_lds() {  // floats of LDS that a block takes
   return 4 * 4 * RN * 16 * QX + 4 * 16 * RN;
 }
 
 // Block (bx, by, bz), with wgrad_lds() floats of LDS from `lds` on.
-template <int RN, int QX, bool FAST>
+template <int RN, int QX, int VIEW>
 __device__ __forceinline__ void wgrad_block(const WgradArgs& a, float* lds, int bx, int by, int bz) {
   constexpr int NN = 16 * RN, NC = 16 * QX;
   constexpr int YW = RN == 1 ? 1 : RN / 2, XW = QX / 2;  // dwords per pixel
@@ -1459,18 +1557,21 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& a, float* lds, int 
   const int ysh = RN == 1 ? 16 * ((n0 + i) & 1) : 0;
   const bool bias_blk = bx == 0 && a.bpart;
 
+  const LaneView xv = VIEW == WG_POW2 ? lane_view(x, xon ? cx : 0) : LaneView{};
   auto load_step = [&](int pk, Dw<YW>(&yd)[8], Dw<XW>(&xd)[8]) {
     const int pp0 = pk + 8 * kq;
     const uint16_t* yp = a.dy + (int64_t)pp0 * a.dy_stride + ny;
-    if constexpr (FAST) {
+    if constexpr (VIEW != WG_ANY) {
       const bool gv = pp0 < pw1;  // W % 8 == 0: the 8 pixels are valid together
-      const int x0 = pp0 % x.W, y0 = (pp0 / x.W) % x.H;
-      const bool rowv = gv && xon && (unsigned)(y0 + ty) < (unsigned)x.H;
-      const uint16_t* xp = x.a + ((int64_t)pp0 + ty * x.W + tx) * x.ca + cx;
+      const int t = pp0 / x.W, x0 = pp0 - t * x.W + tx, pb = t / x.H, y = t - pb * x.H + ty;
+      const bool rowv = gv && xon && (unsigned)y < (unsigned)x.H;
+      const uint16_t* xp = VIEW == WG_POW2
+                               ? xv.row(pb, y)
+                               : x.a + ((int64_t)pp0 + ty * x.W + tx) * x.ca + cx;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const bool xv = rowv && (unsigned)(x0 + e + tx) < (unsigned)x.W;
-        xd[e] = xv ? ldw<XW>(xp + (int64_t)e * x.ca) : zdw<XW>();
+        const bool in = rowv && (unsigned)(x0 + e) < (unsigned)x.W;
+        xd[e] = in ? ldw<XW>(xp + (VIEW == WG_POW2 ? xv.col(x0 + e) : e * x.ca)) : zdw<XW>();
         yd[e] = (gv && yon) ? ldw<YW>(yp + (int64_t)e * a.dy_stride) : zdw<YW>();
       }
     } else {
@@ -1593,10 +1694,10 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& a, float* lds, int 
         ((bred[0][t] + bred[1][t]) + bred[2][t]) + bred[3][t];
 }
 
-template <int RN, int QX, bool FAST>
+template <int RN, int QX, int VIEW>
 __global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a) {
   __shared__ __attribute__((aligned(16))) float lds[wgrad_lds<RN, QX>()];
-  wgrad_block<RN, QX, FAST>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+  wgrad_block<RN, QX, VIEW>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Sum of v[sp * stride] over the splits: eight independent partial sums
@@ -1660,7 +1761,7 @@ __global__ __launch_bounds__(256, 3) void k_layer_bwd(ConvArgs p, int cout_p, in
                                           i - t * gx, t % gy, t / gy);
   } else if ((i -= nd) < nw) {
     const int t = i / wx;
-    wgrad_block<4, 4, true>(w, reinterpret_cast<float*>(lds), i - t * wx, t % wy, t / wy);
+    wgrad_block<4, 4, WG_PLAIN>(w, reinterpret_cast<float*>(lds), i - t * wx, t % wy, t / wy);
   } else {
     grad_reduce_block(r, i - nw);
   }
@@ -1774,10 +1875,16 @@ void launch_dgrad(const ConvArgs& a, const BwdEpi& e, int cout_p, hipStream_t st
   if (try_conv3_rw<8, 2, 4, RW_DG>(a, cout_p, 1, st, &e)) return count_conv(9);
   const int64_t M = (int64_t)a.B * a.H * a.W;
   const unsigned gx = cdiv64(M, 128);
-  if (cout_p >= 64) {
-    k_dgrad<4><<<dim3(gx, cout_p / 64), 256, 0, st>>>(a, e);
-  } else {
-    k_dgrad<1><<<dim3(gx, cout_p / 16), 256, 0, st>>>(a, e);
+  const dim3 g4(gx, cout_p / 64), g1(gx, cout_p / 16);
+  const auto run = [&](auto k4, auto k1) {
+    if (cout_p >= 64) k4<<<g4, 256, 0, st>>>(a, e);
+    else k1<<<g1, 256, 0, st>>>(a, e);
+  };
+  switch (e.mode) {
+    case EPI_PLAIN: run(k_dgrad<4, EPI_PLAIN>, k_dgrad<1, EPI_PLAIN>); break;
+    case EPI_REC_SPLIT: run(k_dgrad<4, EPI_REC_SPLIT>, k_dgrad<1, EPI_REC_SPLIT>); break;
+    case EPI_FUSE_SPLIT: run(k_dgrad<4, EPI_FUSE_SPLIT>, k_dgrad<1, EPI_FUSE_SPLIT>); break;
+    default: run(k_dgrad<4, EPI_DENSE>, k_dgrad<1, EPI_DENSE>);
   }
 }
 
@@ -1799,19 +1906,17 @@ int wgrad_splits(int64_t npix, int kp, int cout_p, int& chunk) {
 }
 
 void launch_wgrad(const WgradArgs& a, int splits, hipStream_t st) {
-  const bool fast = a.x.mode == VIEW_PLAIN && a.x.W % 8 == 0;
+  const int view = a.x.W % 8 ? WG_ANY
+                   : a.x.mode == VIEW_PLAIN ? WG_PLAIN
+                   : (a.x.r & (a.x.r - 1)) == 0 ? WG_POW2 : WG_ANY;
   const dim3 grid(cdiv64(a.x.kp, wgrad_nc(a.cout_p)), a.cout_p / wgrad_nn(a.cout_p), splits);
-  if (a.cout_p >= 64) {
-    if (fast)
-      k_wgrad<4, 4, true><<<grid, 256, 0, st>>>(a);
-    else
-      k_wgrad<4, 4, false><<<grid, 256, 0, st>>>(a);
-  } else {
-    if (fast)
-      k_wgrad<1, 8, true><<<grid, 256, 0, st>>>(a);
-    else
-      k_wgrad<1, 8, false><<<grid, 256, 0, st>>>(a);
-  }
+  const auto run = [&](auto k44, auto k18) {
+    if (a.cout_p >= 64) k44<<<grid, 256, 0, st>>>(a);
+    else k18<<<grid, 256, 0, st>>>(a);
+  };
+  if (view == WG_PLAIN) run(k_wgrad<4, 4, WG_PLAIN>, k_wgrad<1, 8, WG_PLAIN>);
+  else if (view == WG_POW2) run(k_wgrad<4, 4, WG_POW2>, k_wgrad<1, 8, WG_POW2>);
+  else run(k_wgrad<4, 4, WG_ANY>, k_wgrad<1, 8, WG_ANY>);
 }
 
 ReduceArgs reduce_args(const WgradArgs& w, int splits, const NetLayer& L, float* g) {
