@@ -291,15 +291,9 @@ constexpr int C3_W = 16;  // tile width: one 16-pixel MFMA row tile
 
 __device__ __forceinline__ bool pos_bf(uint16_t h) { return h != 0 && !(h & 0x8000u); }
 
-// Row (channel) and K index of element e of a layer packed in fragment order:
-// 16-row tiles, each as K steps of 32, each as the 64 lanes' 8 weights in the
-// order of the MFMA's A operand (lane l: row l % 16, K 8 (l / 16) ..).
-__device__ __forceinline__ void frag_order(int e, int kp, int& row, int& k) {
-  const int t = e / (16 * kp), f = e - t * 16 * kp;
-  const int ks = f >> 9, lane = (f >> 3) & 63;
-  row = t * 16 + (lane & 15);
-  k = ks * 32 + (lane >> 4) * 8 + (f & 7);
-}
+// Fragment order of packed weights: 16-row tiles, each as K steps of 32, each as the 64
+// lanes' 8 weights in the order of the MFMA's A operand (lane l: row l % 16, K
+// 8 (l / 16) ..), so that a wave loads a step as one run of 1 KB.
 
 // 3x3 convolution of 64-channel slices (cin_p a multiple of 64) with its weights
 // held in registers.  A block owns a tile of 16 columns x WR R rows of one image
@@ -315,7 +309,7 @@ __device__ __forceinline__ void frag_order(int e, int kp, int& row, int& k) {
 // pixel and the epilogue moves 8 and 16 bytes at a time.  The next slice's
 // weights are loaded as the last rows release the registers, and the next tile
 // goes through registers into the other LDS buffer.  The weights are packed in
-// fragment order (frag_order): row-major ones cost 16 half-used lines a load
+// fragment order: row-major ones cost 16 half-used lines a load
 // and 7 us a launch.
 // Every output sums its K in the order slice, tap, channel, whatever the plan.
 // Measured (720p LR image, 64 / 128 / 256 input channels, one launch after the
@@ -1376,41 +1370,80 @@ __global__ __launch_bounds__(256) void k_input(InputArgs p) {
   }
 }
 
+// One tile of k_pack_all: 16 rows x 32 channels (of the padded cinp) x all taps.  The
+// master's weights of a row and consecutive channels (t = 0), or of a column and
+// consecutive rows (t = 1), lie together: they are read in order into LDS and written in
+// the order of the packed layout, 4 bytes a lane.
+constexpr int PK_ROWS = 16, PK_COLS = 32;
+template <int TAPS>
+__device__ __forceinline__ void pack_tile(const PackJob& J, int tile, const float* __restrict__ w,
+                                          uint16_t* __restrict__ out, float* lds) {
+  const int nc = (J.cinp + PK_COLS - 1) / PK_COLS, rt = tile / nc, c0 = (tile - rt * nc) * PK_COLS;
+  const int r0 = rt * PK_ROWS;
+  // runs of consecutive weights in the master, and their pitch in LDS
+  const int runs = J.t ? PK_COLS : PK_ROWS;
+  const int len = (J.t ? PK_ROWS : PK_COLS) * TAPS, pitch = len + 1;
+  const int run0 = J.t ? c0 : r0, in0 = J.t ? r0 : c0;  // first output / input channel
+  const int have = min(len, (J.cin - in0) * TAPS);
+  for (int u = threadIdx.x >> 6; u < runs; u += 4) {
+    const int n = run0 + u;
+    const float* src = w + ((size_t)n * J.cin + in0) * TAPS;
+    const int m = n < J.cout ? have : 0;
+    for (int k = threadIdx.x & 63; k < len; k += 64) lds[u * pitch + k] = k < m ? src[k] : 0.0f;
+  }
+  __syncthreads();
+  // place of K index k (even) of row r0 + row
+  const auto at = [&](int row, int k) {
+    return J.frag ? (size_t)r0 * J.kp + (k >> 5) * 512 + (((k >> 3) & 3) * 16 + row) * 8 + (k & 7)
+                  : (size_t)(r0 + row) * J.kp + k;
+  };
+  const int cols = min(PK_COLS, J.cinp - c0);
+#pragma unroll
+  for (int tap = 0; tap < TAPS; ++tap) {
+    const int f = threadIdx.x;  // two channels of a row
+    const int row = J.frag ? (f >> 2) & 15 : f >> 4;
+    const int col = J.frag ? (f >> 6) * 8 + (f & 3) * 2 : (f & 15) * 2;
+    if (col >= cols) continue;
+    const float* v = lds + (J.t ? col * pitch + row * TAPS + TAPS - 1 - tap
+                                : row * pitch + col * TAPS + tap);
+    *reinterpret_cast<uint32_t*>(out + at(row, tap * J.cinp + c0 + col)) =
+        f2bf2(v[0], v[J.t ? pitch : TAPS]);
+  }
+  if (c0 + PK_COLS >= J.cinp) {  // zeros from the last tap to kp
+    const int pad = (J.kp - TAPS * J.cinp) / 2;
+    for (int f = threadIdx.x; f < PK_ROWS * pad; f += 256) {
+      const int row = f / pad, k = TAPS * J.cinp + 2 * (f - row * pad);
+      *reinterpret_cast<uint32_t*>(out + at(row, k)) = 0u;
+    }
+  }
+}
+
 // BF16 weight packing of every layer in one launch (master layout
-// [cout][cin][k][k]).  Element i belongs to the last job whose begin is <= i.
+// [cout][cin][k][k]), a block per tile; tile i belongs to the last job whose begin is <= i.
 // t = 0: wp[n][tap cin_p + c] = W[n][c][tap], the forward convs' B operand.
 // t = 1: wt[c][tap' cinp_t + n] = W[n][c][taps - 1 - tap'], the data-gradient
 // conv (flipped taps, input and output channels swapped).  Padding is zero.
 // Layers that run on k_conv3_rw are stored in fragment order, the others row by row.
+// Bound by memory, 6 bytes a weight and direction: 2.7 M and 11.8 M packed weights (16
+// blocks, dense groups) 26 -> 13 us and 96 -> 24; a thread per weight read the master in
+// steps of a kernel's taps.
 __global__ __launch_bounds__(256) void k_pack_all(const float* __restrict__ wm,
                                                   const PackJob* __restrict__ jobs, int njobs,
-                                                  int64_t total, uint16_t* __restrict__ packed,
+                                                  uint16_t* __restrict__ packed,
                                                   uint16_t* __restrict__ packed_t) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
+  __shared__ float lds[PK_COLS * (PK_ROWS * 9 + 1)];
+  const int64_t i = blockIdx.x;
   int lo = 0, hi = njobs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (jobs[mid].begin <= i) lo = mid;
     else hi = mid - 1;
   }
-  const PackJob& J = jobs[lo];
-  const int64_t e = i - J.begin;
-  int row = (int)(e / J.kp), k = (int)(e % J.kp);
-  if (J.frag) frag_order((int)e, J.kp, row, k);
-  const int tap = k / J.cinp, col = k % J.cinp;
-  const int taps = J.ksz * J.ksz;
-  const float* w = wm + J.w_off;
-  float v = 0.0f;
-  if (J.t == 0) {  // row = output channel n, col = input channel c
-    if (row < J.cout && col < J.cin && tap < taps)
-      v = w[((size_t)(row * J.cin + col) * taps) + tap];
-    packed[J.out_off + e] = f2bf(v);
-  } else {  // row = input channel c, col = output channel n, flipped tap
-    if (row < J.cin && col < J.cout && tap < taps)
-      v = w[((size_t)(col * J.cin + row) * taps) + (taps - 1 - tap)];
-    packed_t[J.out_off + e] = f2bf(v);
-  }
+  const PackJob J = jobs[lo];
+  uint16_t* out = (J.t ? packed_t : packed) + J.out_off;
+  const int tile = (int)(i - J.begin);
+  if (J.ksz == 3) pack_tile<9>(J, tile, wm + J.w_off, out, lds);
+  else pack_tile<1>(J, tile, wm + J.w_off, out, lds);
 }
 
 // He-uniform initialisation (fan-in), Philox4x32-10 with tag 2; biases 0.
@@ -2055,10 +2088,14 @@ void launch_input(const mrs_net* net, int B, int H, int W, const float* hr, cons
   count_conv(3);
 }
 
-void launch_pack_all(const float* wm, const PackJob* jobs, int njobs, int64_t total,
+int64_t pack_tiles(const PackJob& j) {
+  return (int64_t)((j.coutp + PK_ROWS - 1) / PK_ROWS) * ((j.cinp + PK_COLS - 1) / PK_COLS);
+}
+
+void launch_pack_all(const float* wm, const PackJob* jobs, int njobs, int64_t tiles,
                      uint16_t* packed, uint16_t* packed_t, hipStream_t st) {
-  if (total > 0)
-    k_pack_all<<<cdiv64(total, 256), 256, 0, st>>>(wm, jobs, njobs, total, packed, packed_t);
+  if (tiles > 0)
+    k_pack_all<<<(unsigned)tiles, 256, 0, st>>>(wm, jobs, njobs, packed, packed_t);
 }
 
 void launch_init(float* dst, const NetLayer& L, uint64_t seed, hipStream_t st) {

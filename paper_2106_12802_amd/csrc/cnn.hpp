@@ -139,7 +139,7 @@ struct NetLayer {
 // One layer's BF16 packing job of k_pack_all: the forward layout (t = 0) or
 // the transposed layout of its data-gradient conv (t = 1).
 struct PackJob {
-  int64_t begin;    // index of the job's first element in the launch
+  int64_t begin;    // index of the job's first tile in the launch
   int64_t w_off;    // the layer's FP32 master weights
   int64_t out_off;  // offset in d_packed (t = 0) or d_packed_t (t = 1)
   int cout, cin, ksz;
@@ -224,7 +224,8 @@ void launch_grad_reduce(const ReduceArgs& r, hipStream_t st);
 // false if the shapes do not fit it.
 bool launch_layer_bwd(const ConvArgs& a, const BwdEpi& e, int cout_p, const WgradArgs& w,
                       int splits, const ReduceArgs& r, hipStream_t st);
-void launch_pack_all(const float* wm, const PackJob* jobs, int njobs, int64_t total,
+int64_t pack_tiles(const PackJob& j);
+void launch_pack_all(const float* wm, const PackJob* jobs, int njobs, int64_t tiles,
                      uint16_t* packed, uint16_t* packed_t, hipStream_t st);
 void launch_out_grad(const OutGrad& o, const float* y, int64_t npix, uint16_t* g8,
                      hipStream_t st);

@@ -319,7 +319,7 @@ mrs_status ensure_pack_jobs(mrs_net* net) {
       j.t = t;
       j.frag = t ? L.frag_t() : L.frag();
       jobs.push_back(j);
-      at += (int64_t)j.coutp * j.kp;
+      at += pack_tiles(j);
     }
     if (t == 0) {
       net->packjobs_fwd = (int)jobs.size();
