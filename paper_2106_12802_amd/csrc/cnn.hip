@@ -1140,13 +1140,13 @@ __device__ __forceinline__ DgOut dg_out(const ConvArgs& p, const BwdEpi& e, int6
 // at the rate of a copy), reconstruction 64 -> 34 (90 MB, 19 us); with 64 shuffled
 // channels 90 -> 41 and 78 -> 30 us.
 template <int NT, int MODE>
-__global__ __launch_bounds__(256) void k_dgrad(ConvArgs p, BwdEpi e) {
+__device__ __forceinline__ void dgrad_block(const ConvArgs& p, const BwdEpi& e, int bx, int by) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int M = p.B * p.H * p.W;
-  const int m0 = (blockIdx.x * 4 + wave) * 32;
+  const int m0 = (bx * 4 + wave) * 32;
   if (m0 >= M) return;
-  const int n0 = blockIdx.y * (NT * 16);
+  const int n0 = by * (NT * 16);
   f32x4 acc[2][NT];
   conv_mainloop<NT, true>(p, M, m0, n0, lane, acc);
   const int kq = lane >> 4, li = lane & 15;
@@ -1188,6 +1188,11 @@ __global__ __launch_bounds__(256) void k_dgrad(ConvArgs p, BwdEpi e) {
                   f2bf2(g[2] * o[j].h_scale, g[3] * o[j].h_scale)};
     }
   }
+}
+
+template <int NT, int MODE>
+__global__ __launch_bounds__(256) void k_dgrad(ConvArgs p, BwdEpi e) {
+  dgrad_block<NT, MODE>(p, e, blockIdx.x, blockIdx.y);
 }
 
 // Network input channels of one HRLS pixel: 16 BF16 values (log1p of clipped RGB,
@@ -1727,12 +1732,6 @@ __device__ __forceinline__ void wgrad_block(const WgradArgs& a, float* lds, int 
         ((bred[0][t] + bred[1][t]) + bred[2][t]) + bred[3][t];
 }
 
-template <int RN, int QX, int VIEW>
-__global__ __launch_bounds__(256, 3) void k_wgrad(WgradArgs a) {
-  __shared__ __attribute__((aligned(16))) float lds[wgrad_lds<RN, QX>()];
-  wgrad_block<RN, QX, VIEW>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
 // Sum of v[sp * stride] over the splits: eight independent partial sums
 // (split sp into sum sp % 8), so that eight loads are in flight, then added in a
 // fixed order.
@@ -1771,32 +1770,74 @@ __global__ __launch_bounds__(256) void k_grad_reduce(ReduceArgs a) {
   grad_reduce_block(a, blockIdx.x);
 }
 
+// The blocks of a launch that are a weight gradient's: wx x wy x splits of them.
+struct WgradGrid {
+  WgradArgs w;
+  int wx, wy, n;
+};
+template <int RN, int QX, int VIEW>
+__device__ __forceinline__ void wgrad_block(const WgradGrid& g, float* lds, int i) {
+  const int t = i / g.wx;
+  wgrad_block<RN, QX, VIEW>(g.w, lds, i - t * g.wx, t % g.wy, t / g.wy);
+}
+
+// A weight gradient's partial sums, and the sum of an earlier layer's.
+template <int RN, int QX, int VIEW>
+__global__ __launch_bounds__(256, 3) void k_wgrad(WgradGrid g, ReduceArgs r) {
+  __shared__ __attribute__((aligned(16))) float lds[wgrad_lds<RN, QX>()];
+  const int i = blockIdx.x;
+  if (i < g.n) wgrad_block<RN, QX, VIEW>(g, lds, i);
+  else grad_reduce_block(r, i - g.n);
+}
+
+// k_layer_bwd for the layers whose data gradient is a direct conv through a view (the
+// reconstruction, the later upscaling steps, the fuse conv): gx column blocks, nd in all.
+// Measured (16 images of 128 x 128) against the launches one by one: fuse 63 against
+// 51 + 22 + 5 us, reconstruction 82 against 34 + 52 (80 channels; both fill the chip),
+// 60 against 30 + 40 (64), second upscaling step 178 against 78 + 117.
+template <int MODE, int RN, int QX>
+__global__ __launch_bounds__(256, 3) void k_layer_bwd_view(ConvArgs p, BwdEpi e, int gx, int nd,
+                                                           WgradGrid g, ReduceArgs r) {
+  __shared__ __attribute__((aligned(16))) float lds[wgrad_lds<RN, QX>()];
+  int i = blockIdx.x;
+  // the longer blocks first: a later upscaling step's data gradient sums K = 2304
+  constexpr bool DG_FIRST = MODE == EPI_REC_SPLIT && RN == 4;
+  const int wg0 = DG_FIRST ? nd : 0, dg0 = DG_FIRST ? 0 : g.n;
+  if (i >= nd + g.n) {
+    grad_reduce_block(r, i - nd - g.n);
+  } else if ((unsigned)(i - wg0) < (unsigned)g.n) {
+    wgrad_block<RN, QX, WG_POW2>(g, lds, i - wg0);
+  } else {
+    i -= dg0;
+    const int t = i / gx;
+    dgrad_block<4, MODE>(p, e, i - t * gx, t);
+  }
+}
+
 // One layer of the backward pass in one launch: the data gradient (conv3_rw_block on
 // 16 x 8 tiles), the weight gradient's partial sums, which need nothing of it, and the
 // sum over the splits of the layer done before, whose partial sums lie in the other half
 // of the scratch.  Each is bound by latency -- a few dependent steps per block and one
 // to four blocks per CU -- so side by side they take little more than the longest.  The
-// blocks of the data gradient come first: the next layer waits for them.  Measured, one
-// training step of 16 images of 128 x 128: 1.58 -> 1.30 ms (16 blocks: 24 -> 15 us a
-// layer), 3.64 -> 3.19 ms (dense groups).  Larger tiles take 512 threads and longer
+// weight gradient's blocks, the longest, come first (a layer of 64 channels 15.1 -> 14.3
+// us, of 256 31 -> 27.7).  Measured, one training step of 16 images of 128 x 128: 1.58 ->
+// 1.30 ms (16 blocks: 24 -> 15 us a layer), 3.64 -> 3.19 ms (dense groups).  Larger tiles take 512 threads and longer
 // launches, which do not gain: the rule is the small plan's of k_conv3_rw.
 template <bool MULTI>
 __global__ __launch_bounds__(256, 3) void k_layer_bwd(ConvArgs p, int cout_p, int nsplit,
                                                       BwdEpi be, int gx, int gy, int nd,
-                                                      WgradArgs w, int wx, int wy, int nw,
-                                                      ReduceArgs r) {
+                                                      WgradGrid g, ReduceArgs r) {
   constexpr int BYTES_D = 2 * rw_lds<4, 2, MULTI>(), BYTES_W = 4 * wgrad_lds<4, 4>();
   __shared__ __attribute__((aligned(16))) char lds[BYTES_D > BYTES_W ? BYTES_D : BYTES_W];
   int i = blockIdx.x;
-  if (i < nd) {
+  if (i < g.n) {
+    wgrad_block<4, 4, WG_PLAIN>(g, reinterpret_cast<float*>(lds), i);
+  } else if ((i -= g.n) < nd) {
     const int t = i / gx;
     conv3_rw_block<4, 2, 2, MULTI, RW_DG>(p, cout_p, nsplit, be, reinterpret_cast<uint16_t*>(lds),
                                           i - t * gx, t % gy, t / gy);
-  } else if ((i -= nd) < nw) {
-    const int t = i / wx;
-    wgrad_block<4, 4, WG_PLAIN>(w, reinterpret_cast<float*>(lds), i - t * wx, t % wy, t / wy);
   } else {
-    grad_reduce_block(r, i - nw);
+    grad_reduce_block(r, i - nd);
   }
 }
 
@@ -1938,48 +1979,64 @@ int wgrad_splits(int64_t npix, int kp, int cout_p, int& chunk) {
   return (int)std::max<int64_t>(1, (npix + chunk - 1) / chunk);
 }
 
-void launch_wgrad(const WgradArgs& a, int splits, hipStream_t st) {
-  const int view = a.x.W % 8 ? WG_ANY
-                   : a.x.mode == VIEW_PLAIN ? WG_PLAIN
-                   : (a.x.r & (a.x.r - 1)) == 0 ? WG_POW2 : WG_ANY;
-  const dim3 grid(cdiv64(a.x.kp, wgrad_nc(a.cout_p)), a.cout_p / wgrad_nn(a.cout_p), splits);
-  const auto run = [&](auto k44, auto k18) {
-    if (a.cout_p >= 64) k44<<<grid, 256, 0, st>>>(a);
-    else k18<<<grid, 256, 0, st>>>(a);
-  };
-  if (view == WG_PLAIN) run(k_wgrad<4, 4, WG_PLAIN>, k_wgrad<1, 8, WG_PLAIN>);
-  else if (view == WG_POW2) run(k_wgrad<4, 4, WG_POW2>, k_wgrad<1, 8, WG_POW2>);
-  else run(k_wgrad<4, 4, WG_ANY>, k_wgrad<1, 8, WG_ANY>);
-}
-
 ReduceArgs reduce_args(const WgradArgs& w, int splits, const NetLayer& L, float* g) {
   return ReduceArgs{w.part, w.bpart, splits, L.cout, L.cin, L.k, L.cin_p, L.kp, L.cout_p, g};
 }
 
-static unsigned reduce_blocks(const ReduceArgs& r) {
+namespace {
+unsigned reduce_blocks(const ReduceArgs& r) {
   return r.part ? cdiv64((int64_t)r.cout * r.kp + r.cout, 256) : 0u;
 }
+WgradGrid wgrad_grid(const WgradArgs& w, int splits) {
+  const int wx = (int)cdiv64(w.x.kp, wgrad_nc(w.cout_p)), wy = w.cout_p / wgrad_nn(w.cout_p);
+  return WgradGrid{w, wx, wy, wx * wy * splits};
+}
+int wgrad_view(const ConvArgs& x) {
+  return x.W % 8 ? WG_ANY
+         : x.mode == VIEW_PLAIN ? WG_PLAIN
+         : (x.r & (x.r - 1)) == 0 ? WG_POW2 : WG_ANY;
+}
+}  // namespace
 
 void launch_grad_reduce(const ReduceArgs& r, hipStream_t st) {
   if (r.part) k_grad_reduce<<<reduce_blocks(r), 256, 0, st>>>(r);
 }
 
+void launch_wgrad(const WgradArgs& w, int splits, const ReduceArgs& r, hipStream_t st) {
+  const WgradGrid g = wgrad_grid(w, splits);
+  const auto run = [&](auto k44, auto k18) {
+    (w.cout_p >= 64 ? k44 : k18)<<<g.n + reduce_blocks(r), 256, 0, st>>>(g, r);
+  };
+  switch (wgrad_view(w.x)) {
+    case WG_PLAIN: run(k_wgrad<4, 4, WG_PLAIN>, k_wgrad<1, 8, WG_PLAIN>); break;
+    case WG_POW2: run(k_wgrad<4, 4, WG_POW2>, k_wgrad<1, 8, WG_POW2>); break;
+    default: run(k_wgrad<4, 4, WG_ANY>, k_wgrad<1, 8, WG_ANY>);
+  }
+}
+
 bool launch_layer_bwd(const ConvArgs& a, const BwdEpi& e, int cout_p, const WgradArgs& w,
                       int splits, const ReduceArgs& r, hipStream_t st) {
   const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
-  const int nsplit = cout_p / 32;
-  if (tiles >= conv_small_tiles() || w.cout_p < 64 || w.x.mode != VIEW_PLAIN || w.x.W % 8 ||
-      !conv3_rw_fits<4, 2, 2, RW_DG>(a, cout_p, nsplit, &e))
-    return false;
-  const int gx = (a.W + 15) / 16, gy = (a.H + 7) / 8;
-  const int wx = (int)cdiv64(w.x.kp, 64), wy = w.cout_p / 64;
-  const int64_t nd = (int64_t)gx * gy * a.B * nsplit, nw = (int64_t)wx * wy * splits;
-  const int64_t grid = nd + nw + reduce_blocks(r);
-  if (grid > (1 << 30)) return false;
-  auto kern = a.cin_p > 64 ? k_layer_bwd<true> : k_layer_bwd<false>;
-  kern<<<(unsigned)grid, 256, 0, st>>>(a, cout_p, nsplit, e, gx, gy, (int)nd, w, wx, wy, (int)nw, r);
-  count_conv(8);
-  return true;
+  const int nsplit = cout_p / 32, view = wgrad_view(w.x);
+  const WgradGrid g = wgrad_grid(w, splits);
+  if (tiles < conv_small_tiles() && w.cout_p >= 64 && view == WG_PLAIN &&
+      conv3_rw_fits<4, 2, 2, RW_DG>(a, cout_p, nsplit, &e)) {
+    const int gx = (a.W + 15) / 16, gy = (a.H + 7) / 8, nd = gx * gy * a.B * nsplit;
+    auto kern = a.cin_p > 64 ? k_layer_bwd<true> : k_layer_bwd<false>;
+    kern<<<nd + g.n + reduce_blocks(r), 256, 0, st>>>(a, cout_p, nsplit, e, gx, gy, nd, g, r);
+    count_conv(8);
+    return true;
+  }
+  if (view == WG_POW2 && cout_p >= 64 &&
+      (e.mode == EPI_REC_SPLIT || (e.mode == EPI_FUSE_SPLIT && w.cout_p >= 64))) {
+    const int gx = (int)cdiv64((int64_t)a.B * a.H * a.W, 128), nd = gx * (cout_p / 64);
+    auto kern = e.mode == EPI_FUSE_SPLIT ? k_layer_bwd_view<EPI_FUSE_SPLIT, 4, 4>
+                : w.cout_p >= 64 ? k_layer_bwd_view<EPI_REC_SPLIT, 4, 4>
+                                 : k_layer_bwd_view<EPI_REC_SPLIT, 1, 8>;
+    kern<<<nd + g.n + reduce_blocks(r), 256, 0, st>>>(a, e, gx, nd, g, r);
+    return true;
+  }
+  return false;
 }
 
 void launch_out_grad(const OutGrad& o, const float* y, int64_t npix, uint16_t* g8,

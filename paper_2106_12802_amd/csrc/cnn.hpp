@@ -217,7 +217,8 @@ void launch_input(const mrs_net* net, int B, int H, int W, const float* hr, cons
                   hipStream_t st);
 void launch_init(float* dst, const NetLayer& L, uint64_t seed, hipStream_t st);
 void launch_dgrad(const ConvArgs& a, const BwdEpi& e, int cout_p, hipStream_t st);
-void launch_wgrad(const WgradArgs& a, int splits, hipStream_t st);
+// A weight gradient's partial sums, and launch_grad_reduce(r) in the same launch.
+void launch_wgrad(const WgradArgs& w, int splits, const ReduceArgs& r, hipStream_t st);
 ReduceArgs reduce_args(const WgradArgs& w, int splits, const NetLayer& L, float* g);
 void launch_grad_reduce(const ReduceArgs& r, hipStream_t st);
 // launch_dgrad, launch_wgrad and launch_grad_reduce(r) of an earlier layer in one launch;

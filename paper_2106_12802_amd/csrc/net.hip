@@ -394,9 +394,8 @@ void BackwardPass::layer(const ConvArgs* a, const BwdEpi* e, const NetLayer& L, 
   w.cout = L.cout;
   w.bpart = net->d_bpart + half * BPART_FLOATS;
   if (!a || !launch_layer_bwd(*a, *e, L.coutp_t, w, splits, pending, st)) {
-    launch_grad_reduce(pending, st);
     if (a) launch_dgrad(*a, *e, L.coutp_t, st);
-    launch_wgrad(w, splits, st);
+    launch_wgrad(w, splits, pending, st);
   }
   pending = reduce_args(w, splits, L, net->d_grad + L.w_off);
   half ^= 1;
