@@ -347,7 +347,9 @@ typedef struct mrs_tuning {
                            extend, shade or shadow kernels are being recorded
                            (mrs_profile_*), node visits are counted, or schedule,
                            wave_extend = 0 or bvh_quantized ask for other kernels.
-                           Same results */
+                           Starts one bounce later in renders of several jobs of
+                           more than 2^22 resident paths, in small scenes of more
+                           than 2^20.  Same results */
   int32_t bvh_builder;  /* MRS_BVH_PLOC (default) or MRS_BVH_LBVH; applies to
                            scenes built afterwards */
   int32_t conv_small_tiles; /* 0..2^30 (default 128): a 3x3 network conv whose

@@ -24,6 +24,16 @@ __device__ __forceinline__ f3 normalize(f3 a) { return a * (1.0f / sqrtf(dot(a, 
 __device__ __forceinline__ float maxc(f3 a) { return fmaxf(a.x, fmaxf(a.y, a.z)); }
 
 // ------------------------------------------------------------------ Philox4x32-10
+
+// The 64-bit product in one quarter-rate instruction; the compiler takes two, for the
+// halves (a vertex spends 80 of them on its random numbers: six hybrid frames of 7.4 M
+// paths 20.22 -> 20.06 ms).
+__device__ __forceinline__ uint64_t mul_wide(uint32_t a, uint32_t b) {
+  uint64_t p;
+  asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p) : "s"(a), "v"(b) : "vcc");
+  return p;
+}
+
 // Counter-based generator of Salmon et al. (SC'11).  One S-box round maps the
 // counter (c0, c1, c2, c3) with key (k0, k1) to
 //   (hi(M1*c2) ^ c1 ^ k0, lo(M1*c2), hi(M0*c0) ^ c3 ^ k1, lo(M0*c0));
@@ -33,8 +43,9 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
   constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(M0, c.x), lo0 = M0 * c.x;
-    const uint32_t hi1 = __umulhi(M1, c.z), lo1 = M1 * c.z;
+    const uint64_t p0 = mul_wide(M0, c.x), p1 = mul_wide(M1, c.z);
+    const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
+    const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
     c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
     k0 += W0;
     k1 += W1;

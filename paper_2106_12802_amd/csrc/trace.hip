@@ -2356,9 +2356,16 @@ auto shadow_kernel(int sched) {
 //   256,000: tail at 1 292 / 510 / 601, one launch 449 / 508 / 600;
 //   524,288: tail at 1 / 2 / 3 454 / 406 / 416, 679 / 582 / 622, 926 / 972 / 1086;
 //   1,024,000: 763 / 700 / 662, 937 / 817 / 782, 1455 / 1312 / 1405.
-int first_tail_bounce(int tail_bounce, int64_t resident) {
+// Where the chip is full the bounces' own launches are the better use of it: one more of
+// them in large renders of several jobs and, from 2^20 paths on, in small scenes.  Tail
+// at 3 / 4: six hybrid frames of 7.4 M paths 20.92 / 20.20 ms, four uneven pairs of frames
+// 3.94 / 3.74; the box, 1.8 M paths 955 / 799 us, 8.3 M 3621 / 2979; but one image among
+// 100,000 triangles, 3.7 M paths 2109 / 2224, 8.3 M 3612 / 3637 (10,000: 1602 / 1552,
+// 3029 / 2954).
+int first_tail_bounce(int tail_bounce, int64_t resident, int tris, size_t jobs) {
   if (tail_bounce >= MAX_BOUNCE_SLOTS - 1) return tail_bounce;  // never
-  return std::min(tail_bounce, resident <= (1 << 18) ? 1 : resident <= (1 << 19) ? 2 : tail_bounce);
+  if (resident <= (1 << 19)) return std::min(tail_bounce, resident <= (1 << 18) ? 1 : 2);
+  return tail_bounce + (tris < QUAD_TRIS ? resident > (1 << 20) : jobs > 1 && resident > (1 << 22));
 }
 // One launch for whole paths; not while the kernels that it replaces are being timed.
 bool whole_paths(int tail_bounce, int64_t resident, int tris) {
@@ -2411,7 +2418,8 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
   const bool whole = gen_fused && quad > 0 && whole_paths(tu.tail_bounce, resident, max_tris);
   // wavefront bounces 0 .. nwave-1; the path tail takes bounces nwave .. max_depth
   const int nwave =
-      whole ? 0 : std::min(first_tail_bounce(tu.tail_bounce, resident), max_depth + 1);
+      whole ? 0 : std::min(first_tail_bounce(tu.tail_bounce, resident, max_tris, jobs.size()),
+                             max_depth + 1);
   unsigned long long* stats = ws.stats;
   const size_t spill_k = (size_t)P.blocks_k * TB * (MAX_STACK4 - LDS_STACK);
   const bool forked = ws.forked && ws.fork_st == st;
