@@ -848,6 +848,8 @@ __global__ __launch_bounds__(RB_THREADS) void k_res_block(ConvArgs pa, ConvArgs 
 // channels and has the operands of all these K steps in flight at once, straight
 // from memory into registers (a K step is 32 channels of one HR pixel per LR
 // pixel, so its place in the block is uniform).  K steps ascend, as in k_conv.
+// Measured at 720p: 57 us as k_conv<4>, 32 here (51 MB read once: 11 us at the rate of a
+// copy); 17 K steps a batch instead of 12 spill.
 constexpr int FU_KS = 12, FU_WAVES = 8;
 
 __global__ __launch_bounds__(64 * FU_WAVES, 4) void k_fuse(ConvArgs p) {
@@ -947,6 +949,8 @@ bool try_fuse(const ConvArgs& a, int cout_p, hipStream_t st) {
 // weights in registers (only the 3 rows of the MFMA's A operand that hold output
 // channels are read from memory).  Bound by reading its input (147 MB at 720p,
 // 31 us at the rate of a copy).  K index tap (C0 + CB) + c: a K step may span taps.
+// Measured at 720p: 79 -> 47 us (80 channels), 60 -> 37 (64).  Ten-odd dependent LDS reads
+// and three blocks a CU lie between that and the floor.
 template <int C0, int CB, int RS>
 __global__ __launch_bounds__(256, 3) void k_rec(ConvArgs p) {
   constexpr int CIN = C0 + CB, KS = (9 * CIN + 31) / 32, TW = C3_W + 2, NPX = TW * TW;
