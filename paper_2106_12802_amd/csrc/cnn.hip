@@ -321,7 +321,9 @@ template <int R, int WR>
 constexpr int rw_tile_px() {
   return (WR * R + 2) * (C3_W + 2);
 }
-constexpr int RW_PITCH = 64 + 8;  // BF16 per tile pixel: 16-byte reads of 8 lanes hit all banks
+// BF16 per tile pixel.  A wave's operand read takes 8 clocks at this pitch (16 without the
+// padding; 5 with 16 of padding, which changes no conv's time: they wait on latency).
+constexpr int RW_PITCH = 64 + 8;
 
 // What the epilogue of a conv adds and where it stores: y = relu?(acc + bias),
 // y = a1 + s1 y, y += a2, y += a3, zero where mask <= 0, to out_f (FP32) and
