@@ -509,6 +509,14 @@ __device__ void trace_stream(IO& io, uint32_t first, uint32_t stride, uint32_t n
 
 // ------------------------------------------------------------ quad traversal
 
+// Orders a wave's memory accesses (LDS and global) before and after it, across its lanes:
+// for the compiler only, the hardware does them in the wave's order anyway.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A value of another lane of the quad (lane ^ X).
 template <int X>
 __device__ __forceinline__ uint32_t quad_xor(uint32_t v) {
@@ -532,7 +540,8 @@ constexpr int QUAD_STACK = 4 * LDS_STACK;  // entries per ray held in LDS: a qua
 // quad); each lane keeps the best hit among the triangles that it tested, combined by
 // (distance, primitive id) when the ray ends.  The boxes are tested by the same
 // slab(), the triangles by the same isect_tri, so every hit is bitwise trace_stream's.
-// IO::store runs in the four lanes alike.
+// IO::store runs in the four lanes alike (they write the same values), for shadow rays in
+// the first.
 template <int MODE, class IO>
 __device__ void trace_quad(IO& io, uint32_t n, Stack& st) {
   constexpr int LS = TB / 4;  // LDS stride of a ray's stack entries
@@ -609,11 +618,15 @@ __device__ void trace_quad(IO& io, uint32_t n, Stack& st) {
       near |= quad_xor<1>(near);
       near |= quad_xor<2>(near);
       const int nhit = (int)cnt;
+      // A lane's pushes are popped by all four lanes: ordered after the pops of the slots
+      // that they reuse, and before the pops to come.
+      wave_sync();
       if (h && rank > 0) {  // the others onto the stack, far to near
         const int at = sp + nhit - 1 - rank;
         if (sp + 3 <= QUAD_STACK) lds[at * LS] = ref;
         else push(at, ref);
       }
+      wave_sync();
       if (nhit > 0) {
         sp = min(sp + nhit - 1, MAX_STACK4);
         node = near;
@@ -659,7 +672,9 @@ __device__ void trace_quad(IO& io, uint32_t n, Stack& st) {
         better(quad_xor<1>(ts.t), quad_xor<1>(ts.prim), quad_xor<1>(ts.b1), quad_xor<1>(ts.b2));
         better(quad_xor<2>(ts.t), quad_xor<2>(ts.prim), quad_xor<2>(ts.b1), quad_xor<2>(ts.b2));
       }
-      if (io.store(qi, ts, occluded, r)) {
+      // a shadow ray's store adds to the path's radiance and starts no new ray: one lane's
+      const bool more = (MODE != ANY_HIT || ql == 0) && io.store(qi, ts, occluded, r);
+      if (more) {
         begin();
       } else {
         qi += stride;
@@ -1451,7 +1466,7 @@ struct ShadowIO {
     Lv.x += S2.x;
     Lv.y += S2.y;
     Lv.z += S2.z;
-    L_buf[slot] = Lv;  // (a quad's four lanes load and store the same value together)
+    L_buf[slot] = Lv;
     return false;
   }
 };
@@ -1870,13 +1885,6 @@ constexpr int WIDE_SPP_RGB = 32;         // radiance alone
 constexpr int WIDE_PIX = 16;             // pixels per block
 constexpr int WIDE_ROWS = 16 * 4 + 4;    // float4 per pixel: 16 samples x 4, and padding
 
-// Orders a wave's LDS accesses before and after it, across its lanes.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <typename T, bool DIRECT>
 __global__ __launch_bounds__(256) void k_accumulate_wide(SumArgs A) {
   __shared__ float4 lds[WIDE_PIX * WIDE_ROWS];
@@ -1931,7 +1939,7 @@ __global__ __launch_bounds__(256) void k_accumulate_wide(SumArgs A) {
     rows[4 * c + 1] = A0;
     rows[4 * c + 2] = A1;
     rows[4 * c + 3] = E;
-    wave_lds_sync();  // a pixel's rows are its wave's own
+    wave_sync();  // a pixel's rows are its wave's own
     if (k0 + 16 < most) load(k0 + 16);
     const float* w = reinterpret_cast<const float*>(rows);
     const int m = min(16, cnt - k0);
@@ -1950,7 +1958,7 @@ __global__ __launch_bounds__(256) void k_accumulate_wide(SumArgs A) {
         if (k < m && (c < 3 || lobe == c / 3)) a2 += c < 3 ? e : l - e;
       }
     }
-    wave_lds_sync();
+    wave_sync();
   }
   if (DIRECT) {
     const T inv = (T)1 / (T)J.spp;
