@@ -98,6 +98,7 @@ struct DevJob {
   uint32_t rows_full, row_mul, row_inv, pad1;
   uint32_t seed_lo, seed_hi;
   int64_t first, pix_first, acc_off;
+  int64_t sum_first[3];  // pixels of each class of per-pixel sums in the jobs before this one
   float* out_rgb;
   float* out_aux;
   float* out_sq;
