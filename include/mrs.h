@@ -333,23 +333,25 @@ typedef struct mrs_tuning {
                            dynamic fetch from a device counter */
   int32_t bvh_leaf_max; /* triangles a BVH4 leaf may group, 1..4 (default 3);
                            applies to scenes built afterwards */
-  int32_t streams;      /* 1..4 (default 3): a render's resident paths are cut into
-                           this many sub-chunks, traced concurrently on internal
-                           streams shared by the library (joined back into the
-                           caller's stream before the per-pixel sums); renders of
-                           at most 2^18 paths stay on the caller's stream */
-  int32_t tail_bounce;  /* 1..65 (default 3): bounces from this one on are traced
-                           path by path in one launch (65: never).  A render of
-                           at most 2^19 resident paths starts earlier: at bounce
+  int32_t streams;      /* 1..4: a render's resident paths are cut into this many
+                           sub-chunks (of at least 2^16 paths), traced
+                           concurrently on internal streams shared by the
+                           library (joined back into the caller's stream before
+                           the per-pixel sums).  3, the default, leaves renders
+                           of at most 2^18 paths on the caller's stream */
+  int32_t tail_bounce;  /* 1..65: bounces from this one on are traced path by
+                           path in one launch (65: never), whatever the render.
+                           3, the default, leaves it to the render's size: a
+                           render of at most 2^19 resident paths starts at bounce
                            2, of at most 2^18 at bounce 1, and of at most 2^17
                            (2^16 in scenes of fewer than 4096 triangles) at
                            bounce 0, where the whole render is one launch unless
                            extend, shade or shadow kernels are being recorded
                            (mrs_profile_*), node visits are counted, or schedule,
-                           wave_extend = 0 or bvh_quantized ask for other kernels.
-                           Starts one bounce later in renders of several jobs of
-                           more than 2^22 resident paths, in small scenes of more
-                           than 2^20.  Same results */
+                           wave_extend = 0 or bvh_quantized ask for other kernels;
+                           renders of several jobs of more than 2^22 resident
+                           paths, and in small scenes of more than 2^20, start at
+                           bounce 4, all others at 3.  Same results */
   int32_t bvh_builder;  /* MRS_BVH_PLOC (default) or MRS_BVH_LBVH; applies to
                            scenes built afterwards */
   int32_t conv_small_tiles; /* 0..2^30 (default 128): a 3x3 network conv whose

@@ -2145,12 +2145,18 @@ struct Plan {
 // chunk_paths values take more super-chunks instead.
 constexpr int64_t MAX_SUB_PATHS = int64_t(1) << 24;
 
+// The defaults of two tuning fields leave the choice to a rule (make_plan,
+// first_tail_bounce); any other value is what every render takes.
+constexpr int RULE_STREAMS = 3, RULE_TAIL = 3;
+
 Plan make_plan(const mrs_tuning& tu, int64_t total) {
   Plan p;
   // one stream for few paths (us on one / three): 131,072 paths 850 / 890 (100,000
   // triangles), 444 / 469 (10,000), 248 / 300 (34); 524,288 paths 1049 / 972, 606 / 582,
   // 376 / 406
-  p.K = total <= (1 << 18) ? 1 : tu.streams;
+  p.K = tu.streams != RULE_STREAMS ? (int)std::max<int64_t>(1, std::min<int64_t>(tu.streams, total / 65536))
+        : total <= (1 << 18)       ? 1
+                                   : tu.streams;
   const int64_t C = std::max<int64_t>(1, std::min<int64_t>(tu.chunk_paths, total));
   p.Cs = std::min(MAX_SUB_PATHS, ((C + p.K - 1) / p.K + 255) & ~(int64_t)255);
   p.blocks_k = std::max(1, (tu.trace_blocks + p.K - 1) / p.K);
@@ -2166,7 +2172,7 @@ hipStream_t g_sub[MAX_SUB] = {};
 int g_nsub = 0;
 unsigned long long* g_stats = nullptr;  // device counters shared by every stream
 // defaults: the fastest hybrid 720p frame measured with the clustered BVH
-mrs_tuning g_tune = {1 << 23, 8192, 0, 3, 3, 3, MRS_BVH_PLOC, 128, 1, 0, 1, 0, 1};
+mrs_tuning g_tune = {1 << 23, 8192, 0, 3, RULE_STREAMS, RULE_TAIL, MRS_BVH_PLOC, 128, 1, 0, 1, 0, 1};
 std::atomic<int> g_conv_small{128};  // g_tune.conv_small_tiles, read without the lock
 std::atomic<int> g_net_fused{1};      // g_tune.net_fused_blocks, read without the lock
 std::atomic<bool> g_count_work{false};
@@ -2377,8 +2383,8 @@ auto shadow_kernel(int sched) {
 // least as long as its slowest ray, so few paths are better off in few launches: every
 // render of whole_paths' sizes runs its paths from camera ray to end in one launch
 // (k_path), up to 2^18 paths the path tail starts at bounce 1, up to 2^19 at bounce 2,
-// and above at tail_bounce.  All routes give bitwise the same results.  Times of one
-// render (us; depth 8, features; the 34-triangle box / 10,000 / 100,000 triangles):
+// and above at bounce 3; a tail_bounce other than the default starts it there in every
+// render.  All routes give bitwise the same results.  Times of one render (us; depth 8, features; the 34-triangle box / 10,000 / 100,000 triangles):
 //   16,384 paths: tail at 3 204 / 517 / 1261, all quads, tail at 1 120 / 260 / 409,
 //     one launch 112 / 214 / 239;
 //   65,536: 279 / 645 / 1548, 231 / 319 / 428, 214 / 276 / 313;
@@ -2389,17 +2395,18 @@ auto shadow_kernel(int sched) {
 // Where the chip is full the bounces' own launches are the better use of it: one more of
 // them in large renders of several jobs and, from 2^20 paths on, in small scenes.  Tail
 // at 3 / 4: six hybrid frames of 7.4 M paths 20.92 / 20.20 ms, four uneven pairs of frames
-// 3.94 / 3.74; the box, 1.8 M paths 955 / 799 us, 8.3 M 3621 / 2979; but one image among
-// 100,000 triangles, 3.7 M paths 2109 / 2224, 8.3 M 3612 / 3637 (10,000: 1602 / 1552,
-// 3029 / 2954).
+// 3.94 / 3.74, one frame by itself 3590 / 3553 us among 100,000 triangles, 3080 / 3021
+// among 10,000, of 4.9 M paths 2824 / 2797 and 2378 / 2386; the box, 1.8 M paths 955 /
+// 799 us, 8.3 M 3621 / 2979; but one image among 100,000 triangles, 3.7 M paths 2109 /
+// 2224, 8.3 M 3612 / 3637 (10,000: 1602 / 1552, 3029 / 2954).
 int first_tail_bounce(int tail_bounce, int64_t resident, int tris, size_t jobs) {
-  if (tail_bounce >= MAX_BOUNCE_SLOTS - 1) return tail_bounce;  // never
-  if (resident <= (1 << 19)) return std::min(tail_bounce, resident <= (1 << 18) ? 1 : 2);
+  if (tail_bounce != RULE_TAIL) return tail_bounce;
+  if (resident <= (1 << 19)) return resident <= (1 << 18) ? 1 : 2;
   return tail_bounce + (tris < QUAD_TRIS ? resident > (1 << 20) : jobs > 1 && resident > (1 << 22));
 }
 // One launch for whole paths; not while the kernels that it replaces are being timed.
 bool whole_paths(int tail_bounce, int64_t resident, int tris) {
-  if (tail_bounce >= MAX_BOUNCE_SLOTS - 1 ||
+  if (tail_bounce != RULE_TAIL ||
       prof_records(1u << KID_EXTEND | 1u << KID_SHADE | 1u << KID_SHADOW))
     return false;
   return resident <= (tris < QUAD_TRIS ? 1 << 16 : 1 << 17);
