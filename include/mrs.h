@@ -338,7 +338,9 @@ typedef struct mrs_tuning {
                            concurrently on internal streams shared by the
                            library (joined back into the caller's stream before
                            the per-pixel sums).  3, the default, leaves renders
-                           of at most 2^18 paths on the caller's stream */
+                           of at most 2^18 paths on the caller's stream, but
+                           split and forked ones (mrs_batch_render_begin,
+                           _fork), which other work runs beside */
   int32_t tail_bounce;  /* 1..65: bounces from this one on are traced path by
                            path in one launch (65: never), whatever the render.
                            3, the default, leaves it to the render's size: a

@@ -2149,14 +2149,19 @@ constexpr int64_t MAX_SUB_PATHS = int64_t(1) << 24;
 // first_tail_bounce); any other value is what every render takes.
 constexpr int RULE_STREAMS = 3, RULE_TAIL = 3;
 
-Plan make_plan(const mrs_tuning& tu, int64_t total) {
+// split: a render begun and ended by separate calls, or forked ahead of its launches, so
+// that other work on the caller's stream may run beside it.
+Plan make_plan(const mrs_tuning& tu, int64_t total, bool split = false) {
   Plan p;
-  // one stream for few paths (us on one / three): 131,072 paths 850 / 890 (100,000
-  // triangles), 444 / 469 (10,000), 248 / 300 (34); 524,288 paths 1049 / 972, 606 / 582,
-  // 376 / 406
-  p.K = tu.streams != RULE_STREAMS ? (int)std::max<int64_t>(1, std::min<int64_t>(tu.streams, total / 65536))
-        : total <= (1 << 18)       ? 1
-                                   : tu.streams;
+  p.K = (int)std::max<int64_t>(1, std::min<int64_t>(tu.streams, total / 65536));
+  // A render by itself: one stream for few paths (us on one / three): 131,072 paths 850 /
+  // 890 (100,000 triangles), 444 / 469 (10,000), 248 / 300 (34); 524,288 paths 1049 / 972,
+  // 606 / 582, 376 / 406.  A split render keeps the streams, on which the next frame's
+  // paths run beside this frame's sums and network (eight hybrid frames, two in flight, on
+  // one stream / on theirs: 139,264 paths 6.12 / 4.28 ms, 256,000 6.98 / 4.75 among 100,000
+  // triangles, 5.02 / 3.21 and 6.08 / 4.11 among 10,000, 3.85 / 2.61 and 4.28 / 3.44 in a
+  // box).
+  if (!split && tu.streams == RULE_STREAMS && total <= (1 << 18)) p.K = 1;
   const int64_t C = std::max<int64_t>(1, std::min<int64_t>(tu.chunk_paths, total));
   p.Cs = std::min(MAX_SUB_PATHS, ((C + p.K - 1) / p.K + 255) & ~(int64_t)255);
   p.blocks_k = std::max(1, (tu.trace_blocks + p.K - 1) / p.K);
@@ -2271,8 +2276,11 @@ mrs_status ws_ensure(Workspace& w, size_t paths, int threads, int nsub) {
   return MRS_OK;
 }
 
-mrs_status ws_ensure_plan(Workspace& w, const Plan& p) {
-  return ws_ensure(w, (size_t)p.K * p.Cs, p.K * p.blocks_k * TB, p.K > 1 ? p.K : 0);
+// For either of two plans (a batch may be rendered in one call or split).
+mrs_status ws_ensure_plan(Workspace& w, const Plan& p, const Plan& q) {
+  const int K = std::max(p.K, q.K);
+  return ws_ensure(w, (size_t)std::max(p.K * p.Cs, q.K * q.Cs),
+                   std::max(p.K * p.blocks_k, q.K * q.blocks_k) * TB, K > 1 ? K : 0);
 }
 
 mrs_status ws_ensure_acc(Workspace& w, size_t bytes) {
@@ -2433,7 +2441,7 @@ uint32_t quad_rays(int64_t resident, int K, int tris) {
 // which end_batch enqueues (render_batch does both).
 mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs,
                        const std::vector<DevJob>& jobs, char* acc, size_t acc_bytes,
-                       hipStream_t st, DevJob* store = nullptr) {
+                       hipStream_t st, bool split, DevJob* store = nullptr) {
   const int nj = (int)jobs.size();
   int64_t total = 0;
   int max_depth = 0;
@@ -2441,7 +2449,9 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
     total += (int64_t)J.spp * J.ww * J.wh;
     max_depth = std::max(max_depth, (int)J.max_depth);
   }
-  const Plan P = make_plan(tu, total);
+  const bool forked = ws.forked && ws.fork_st == st;
+  ws.forked = false;
+  const Plan P = make_plan(tu, total, split || forked);
   const int64_t resident = std::min<int64_t>(total, P.K * P.Cs);
   const int dyn = tu.schedule;
   const bool qn = tu.bvh_quantized != 0;
@@ -2459,8 +2469,6 @@ mrs_status begin_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_jobs
                              max_depth + 1);
   unsigned long long* stats = ws.stats;
   const size_t spill_k = (size_t)P.blocks_k * TB * (MAX_STACK4 - LDS_STACK);
-  const bool forked = ws.forked && ws.fork_st == st;
-  ws.forked = false;
   const bool direct = total <= P.K * P.Cs;  // every path resident: no sums in memory
   if (store && P.K > 1) k_store_job<<<1, 64, 0, st>>>(jobs[0], store);
   if (!forked) {
@@ -2607,7 +2615,7 @@ mrs_status launch_batch(Workspace& ws, const mrs_tuning& tu, const DevJob* d_job
                         hipStream_t st, DevJob* store = nullptr) {
   if (ws.pend.active)
     return fail(MRS_ERR_INVALID_ARGUMENT, "render: a split render of this workspace is not ended");
-  mrs_status rc = begin_batch(ws, tu, d_jobs, jobs, acc, acc_bytes, st, store);
+  mrs_status rc = begin_batch(ws, tu, d_jobs, jobs, acc, acc_bytes, st, false, store);
   if (rc != MRS_OK) {
     ws.pend.active = false;
     return rc;
@@ -2689,7 +2697,8 @@ mrs_status render(const mrs_scene* s, const RenderArgs& a, hipStream_t st) {
   const int64_t npix = (int64_t)a.ww * a.wh;
   const mrs_tuning tu = tuning_snapshot();
   Workspace& ws = *stream_workspace(st);
-  mrs_status rc = ws_ensure_plan(ws, make_plan(tu, npix * a.spp));
+  const Plan P = make_plan(tu, npix * a.spp);
+  mrs_status rc = ws_ensure_plan(ws, P, P);
   if (rc != MRS_OK) return rc;
   const size_t ab = acc_bytes_of(npix, a.fp64, a.out_layers != nullptr);
   if ((rc = ws_ensure_acc(ws, ab)) != MRS_OK) return rc;
@@ -2851,7 +2860,8 @@ mrs_status batch_create(const std::vector<DevJob>& jobs, mrs_batch** out) {
     off += acc_bytes_of(npix, J.fp64 != 0, J.out_layers != nullptr);
   }
   b->acc_bytes = off;
-  mrs_status rc = ws_ensure_plan(b->ws, make_plan(b->tune, first));
+  mrs_status rc =
+      ws_ensure_plan(b->ws, make_plan(b->tune, first), make_plan(b->tune, first, true));
   if (rc == MRS_OK && (hipMalloc(&b->d_jobs, sizeof(DevJob) * b->jobs.size()) != hipSuccess ||
                        hipMalloc(&b->d_acc, b->acc_bytes) != hipSuccess)) {
     (void)hipGetLastError();
@@ -2878,7 +2888,7 @@ mrs_status batch_render_begin(mrs_batch* b, hipStream_t st) {
   if (b->ws.pend.active)
     return fail(MRS_ERR_INVALID_ARGUMENT,
                 "mrs_batch_render_begin: the batch's previous render is not ended");
-  mrs_status rc = begin_batch(b->ws, b->tune, b->d_jobs, b->jobs, b->d_acc, b->acc_bytes, st);
+  mrs_status rc = begin_batch(b->ws, b->tune, b->d_jobs, b->jobs, b->d_acc, b->acc_bytes, st, true);
   if (rc != MRS_OK) b->ws.pend.active = false;
   return rc;
 }
@@ -2891,7 +2901,7 @@ mrs_status batch_render_fork(mrs_batch* b, hipStream_t st) {
                 "mrs_batch_render_fork: the batch's previous render is not ended");
   int64_t total = 0;
   for (const DevJob& J : b->jobs) total += (int64_t)J.spp * J.ww * J.wh;
-  const Plan P = make_plan(b->tune, total);
+  const Plan P = make_plan(b->tune, total, true);  // the forked render's
   if (total > P.K * P.Cs)  // the sums in memory of a render of several super-chunks
     k_zero_words<<<std::min(4096u, cdiv(b->acc_bytes / 4, 256)), 256, 0, st>>>(
         (uint32_t*)b->d_acc, b->acc_bytes / 4);
