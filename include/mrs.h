@@ -307,8 +307,9 @@ mrs_status mrs_set_count_work(int32_t on);
 /* Kernel timing with HIP events recorded on the launch stream around every
  * launch of the library's kernels, by kernel id:
  * 0 generate, 1 extend (closest hit), 2 shade, 3 shadow (any hit),
- * 4 accumulate, 5 resolve (of a render whose paths are all resident at once: its
- * last accumulate launch, which is recorded under both ids), 6 reserved,
+ * 4 accumulate, 5 resolve (a render whose paths are all resident at once has no
+ * such launch: its last accumulate launch is counted here too, without its time),
+ * 6 reserved,
  * 7 network input preparation and input convs,
  * 8 network LR convs (fuse, trunk, up), 9 network HR output conv,
  * 10 training forward, 11 training backward, 12 Adam + weight refresh,

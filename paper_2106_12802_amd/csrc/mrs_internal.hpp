@@ -215,6 +215,7 @@ struct ProfPause {
 bool prof_records(uint32_t ids);  // launches of any of these ids (a mask) are being recorded
 void prof_begin(int id, hipStream_t st);
 void prof_end(int id, hipStream_t st);
+void prof_count(int id);  // a launch that is recorded, with its time, under another id
 mrs_status prof_enable(bool on);
 mrs_status prof_select(uint32_t mask);
 mrs_status prof_read(double* ms, int64_t* launches);

@@ -57,6 +57,10 @@ ProfPause::~ProfPause() { --t_paused; }
 
 bool prof_records(uint32_t ids) { return g_on && !t_paused && (g_mask & ids) != 0; }
 
+void prof_count(int id) {
+  if (prof_records(1u << id)) ++g_count[id];
+}
+
 void prof_begin(int id, hipStream_t st) {
   if (!g_on || t_paused || id < 0 || id >= MRS_NUM_KERNEL_IDS || !((g_mask >> id) & 1u)) return;
   hipEvent_t e = take();

@@ -2363,13 +2363,12 @@ mrs_status sum_chunk(Workspace& ws, const DevJob* d_jobs, const std::vector<DevJ
       auto kern = cls == 0 ? (direct ? k_accumulate<true> : k_accumulate<false>)
                   : cls == 1 ? (direct ? k_accumulate_wide<float, true> : k_accumulate_wide<float, false>)
                              : (direct ? k_accumulate_wide<double, true> : k_accumulate_wide<double, false>);
-      // the launch that writes the render's last outputs is its resolve as well
-      const bool resolves = direct && k == used - 1 && cls == last;
       prof_begin(KID_ACCUMULATE, st);
-      if (resolves) prof_begin(KID_RESOLVE, st);
       kern<<<blocks, 256, 0, st>>>(A);
-      if (resolves) prof_end(KID_RESOLVE, st);
       prof_end(KID_ACCUMULATE, st);
+      // the launch that writes the render's last outputs is its resolve as well; its time
+      // is the sums'
+      if (direct && k == used - 1 && cls == last) prof_count(KID_RESOLVE);
     }
   }
   // the next super-chunk (or render) reuses the slices once these sums have read them

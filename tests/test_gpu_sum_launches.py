@@ -1,5 +1,5 @@
 """The launches of the per-pixel sums: one for each kernel class among the jobs of a batch,
-whatever their order."""
+whatever their order; each launch's time is recorded once."""
 import pytest
 
 from mrs_inputs import scenes as S
@@ -51,3 +51,25 @@ def test_one_launch_per_class_for_alternating_jobs(mrs, chunk):
         assert torch.equal(rgb, r1)
         assert not j["want_aux"] or torch.equal(aux, a1)
     b.close()
+
+
+def test_resolve_without_a_launch_has_no_time(mrs):
+    """A render whose paths are all resident writes its outputs from the sums' kernel: counted
+    as its resolve, timed as sums; one in super-chunks has a resolve launch of its own."""
+    from paper_2106_12802_amd import tracer as R
+    gs = mrs.GpuScene(S.cornell(2))
+    got = {}
+    for chunk in (mrs.get_tuning()["chunk_paths"], 1000):
+        mrs.set_tuning(chunk_paths=chunk)
+        try:
+            R.profile_select(["accumulate", "resolve"])
+            R.profile_enable(True)
+            mrs.render(gs, 64, 64, 2, 3, 1)
+            got[chunk] = R.profile_read()
+        finally:
+            R.profile_enable(False)
+            R.profile_select(None)
+    direct, chunked = got.values()
+    assert direct["accumulate"][0] > 0.0 and direct["accumulate"][1] == 1
+    assert direct["resolve"] == (0.0, 1)
+    assert chunked["resolve"][0] > 0.0 and chunked["resolve"][1] == 1
