@@ -29,7 +29,7 @@
 // the smallest surface area; mutual nearest neighbours merge; the survivors are
 // compacted in order; repeat until one cluster is left.  Ties are broken by a
 // total order on cluster pairs, so some pair is always mutual and every round
-// merges (identical boxes pair up with their neighbours, see pair_before).
+// merges (identical boxes pair up with their neighbours, see ploc_nearest).
 // The tree is then laid out depth first: internal nodes numbered in
 // preorder (root 0) and leaf records in leaf order, so every subtree's leaves
 // are a contiguous range as the BVH4 collapse needs.  Its trees have a lower
@@ -363,8 +363,9 @@ __global__ __launch_bounds__(256) void k_leaves_refit(const float4* __restrict__
 // ---------------------------------------------------------------- PLOC
 constexpr uint32_t NO_PARENT = 0xffffffffu;
 // Device words of a clustering build: merges so far, 1 once one cluster is left
-// and every merge is made, deepest leaf or node, malformed tree, root.
+// and every merge is made, deepest leaf or node, a fault (below), root.
 enum { PC_MERGES = 0, PC_DONE, PC_DEPTH, PC_BAD, PC_ROOT, PLOC_CTR };
+enum { BAD_TREE = 1, BAD_STUCK = 2 };  // PC_BAD: malformed, a round without a merge
 
 __device__ __forceinline__ float box_half_area(float4 lo, float4 hi) {
   const float dx = hi.x - lo.x, dy = hi.y - lo.y, dz = hi.z - lo.z;
@@ -400,7 +401,9 @@ __global__ __launch_bounds__(256) void k_ploc_init(const float4* __restrict__ tr
 // grids) clusters thus pair up as (0, 1), (2, 3), ...: every cluster merges and
 // the tree stays balanced, where a plain index order would merge one pair per
 // round.  Candidates come by distance, left before right, so an equal one replaces
-// the best only where it is the right one of the same odd distance and c is even.
+// the best only where it is the right one of the same odd distance and c is even; the
+// first of infinite cost is equal to no pair yet and taken, one that is not a number
+// (boxes beyond FP32's range) is no candidate.
 // No branches: the boxes of several candidates are in flight at once (one after
 // the other the LDS latency bounds it).
 template <class L, class H>
@@ -428,9 +431,8 @@ __device__ __forceinline__ int ploc_nearest(int c, int m, L l, H h) {
                                           fminf(lo.z, cl[u].z), 0.0f),
                               make_float4(fmaxf(hi.x, ch[u].x), fmaxf(hi.y, ch[u].y),
                                           fmaxf(hi.z, ch[u].z), 0.0f));
-      const bool tie = (u & 1) ? (a == best) & (bj == c - d) & ((d & 1) != 0) & even
-                               : (a == best) & (bj < 0);
-      const bool take = in & ((a < best) | tie);
+      const bool tie = (bj < 0) | ((u & 1) ? (bj == c - d) & ((d & 1) != 0) & even : false);
+      const bool take = in & ((a < best) | ((a == best) & tie));
       best = take ? a : best;
       bj = take ? j : bj;
     }
@@ -576,6 +578,7 @@ __global__ __launch_bounds__(1024) void k_ploc_small(const uint32_t* __restrict_
   int m = (int)*mcount;
   if (m > PLOC_SMALL || m < 1) return;
   uint32_t merges = ctr[PC_MERGES];
+  bool stuck = false;
   auto put = [&](int c, uint32_t ref, float4 lo, float4 hi) {
     slo[c] = lo;
     shi[c] = make_float4(hi.x, hi.y, hi.z, __uint_as_float(ref));
@@ -647,7 +650,8 @@ __global__ __launch_bounds__(1024) void k_ploc_small(const uint32_t* __restrict_
     for (int q = 0; q < PER; ++q)
       if (kept[q]) put((int)pos[q], ref[q], lo[q], hi[q]);
     merges += nm;
-    if (nm == 0) break;  // cannot happen: some pair is always mutual
+    stuck = nm == 0;  // some pair is mutual unless costs are not numbers
+    if (stuck) break;
     m = (int)nk;
     __syncthreads();
   }
@@ -658,7 +662,8 @@ __global__ __launch_bounds__(1024) void k_ploc_small(const uint32_t* __restrict_
     ctr[PC_MERGES] = merges;
     ctr[PC_ROOT] = root;
     ctr[PC_DONE] = ok ? 1u : 0u;
-    if (m == 1 && !ok) ctr[PC_BAD] = 1u;
+    if (m == 1 && !ok) ctr[PC_BAD] = BAD_TREE;
+    if (stuck) ctr[PC_BAD] = BAD_STUCK;
   }
 }
 
@@ -683,7 +688,7 @@ __global__ __launch_bounds__(256) void k_ploc_order(int n, int nint,
       if (depth >= 4 * MAX_STACK) break;  // too deep (the caller falls back)
       const uint32_t p = x >> 1;
       if (p >= (uint32_t)nint) {  // cannot happen for a tree
-        atomicOr(ctr + PC_BAD, 1u);
+        atomicOr(ctr + PC_BAD, (uint32_t)BAD_TREE);
         break;
       }
       const uint32_t L = sz2[2 * (size_t)p], up = par_int[p];
@@ -1169,6 +1174,8 @@ mrs_status ploc_build(mrs_scene* s, hipStream_t st, const uint32_t* code, const 
   uint32_t h[PLOC_CTR];
   MRS_TRY_HIP(hipMemcpyAsync(h, c.ctr, sizeof h, hipMemcpyDeviceToHost, st));
   MRS_TRY_HIP(hipStreamSynchronize(st));
+  if (h[PC_BAD] & BAD_STUCK)
+    return fail(MRS_ERR_DEVICE, "mrs_build_bvh: a clustering round merged nothing");
   if (h[PC_BAD]) return fail(MRS_ERR_DEVICE, "mrs_build_bvh: clustered tree is malformed");
   // not done in PLOC_MAX_ROUNDS, or too deep: the caller falls back
   *used = h[PC_DONE] && h[PC_DEPTH] <= (uint32_t)MAX_STACK;
