@@ -20,6 +20,7 @@ STATUS_NAMES = {0: "OK", 1: "INVALID_ARGUMENT", 2: "OUT_OF_MEMORY", 3: "DEVICE",
                 5: "UNSUPPORTED"}
 NUM_COUNTERS = 16
 NUM_KERNEL_IDS = 16
+# "cnn_prep" is no longer recorded: the preprocessing runs in cnn_hr_in's launch
 KERNEL_NAMES = ["generate", "extend", "shade", "shadow", "accumulate", "resolve", "cnn_prep",
                 "cnn_hr_in", "cnn_lr", "cnn_hr_out", "train_fwd", "train_bwd", "train_adam", "tail"]
 

@@ -48,11 +48,6 @@ D3 nrm(D3 a) {
   double l = len(a);
   return {a.x / l, a.y / l, a.z / l};
 }
-float bits_to_float(uint32_t u) {
-  float f;
-  std::memcpy(&f, &u, sizeof f);
-  return f;
-}
 bool finite3(const float* p) { return std::isfinite(p[0]) && std::isfinite(p[1]) && std::isfinite(p[2]); }
 
 // Pinned memory that small uploads pass through, one buffer for the process until
