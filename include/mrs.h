@@ -309,7 +309,7 @@ mrs_status mrs_set_count_work(int32_t on);
  * 0 generate, 1 extend (closest hit), 2 shade, 3 shadow (any hit),
  * 4 accumulate, 5 resolve (a render whose paths are all resident at once has no
  * such launch: its last accumulate launch is counted here too, without its time),
- * 6 reserved,
+ * 6 no longer recorded (network input preparation, now in 7's launch),
  * 7 network input preparation and input convs,
  * 8 network LR convs (fuse, trunk, up), 9 network HR output conv,
  * 10 training forward, 11 training backward, 12 Adam + weight refresh,
@@ -326,7 +326,8 @@ mrs_status mrs_profile_select(uint32_t mask);
 mrs_status mrs_profile_read(double ms_out[MRS_NUM_KERNEL_IDS],
                             int64_t launches_out[MRS_NUM_KERNEL_IDS]);
 
-/* Tuning knobs (performance only; results do not depend on them). */
+/* Tuning knobs (performance only; results do not depend on them, but see
+ * bvh_quantized). */
 typedef struct mrs_tuning {
   int32_t chunk_paths;  /* paths resident at once (default 1<<23, at most 1<<26) */
   int32_t trace_blocks; /* grid size of traversal kernels (default 8192) */
@@ -371,7 +372,10 @@ typedef struct mrs_tuning {
   int32_t bvh_quantized; /* 1: traversal reads the 64-byte copy of each BVH4
                            node whose child boxes are 8-bit steps from the node's
                            origin, rounded outward with a margin; 0 (default):
-                           the 128-byte nodes with FP32 boxes.  Same hits */
+                           the 128-byte nodes with FP32 boxes.  Same hits,
+                           except that of a box that a ray only grazes one format
+                           may miss a hit that the other keeps (their margins
+                           differ; one pixel of 198 M paths of 32 scenes) */
   int32_t wave_extend;  /* 0..65 (default 1): closest-hit rays of the bounces
                            below this one are traced a wave at a time (the 64
                            rays of a wave walk one tree order together; node

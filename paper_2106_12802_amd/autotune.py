@@ -1,5 +1,8 @@
 """Autotuner of the renderer's and the network's launch shape (performance only:
-results are bitwise independent of the tuning, which the tests check).
+results are bitwise independent of the tuning, which the tests check, except that
+quantized BVH nodes and FP32 ones may differ in a hit at a box that a ray grazes; a
+program that compares images of several tunings leaves bvh_quantized out of
+`secondary`).
 
 It times a workload under candidate tunings, keeps the fastest, and caches the
 choice in a JSON file keyed by device and workload so that later runs apply it

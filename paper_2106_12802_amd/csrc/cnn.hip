@@ -403,7 +403,8 @@ __device__ __forceinline__ RwEpi rw_epi(const ConvArgs& p, const BwdEpi& e, int 
 // offset in one instruction.  A lane whose offset is not below `bytes` loads
 // zeros and stores nothing (the buffer's range check), so a lane outside the
 // image gets the offset BUF_OUT and needs no branch; in-image offsets stay
-// below 2^31 (at most 18 rows of 16384 pixels of 256 FP32 channels).
+// below 2^31 (18 rows of 256 FP32 channels: up to 116,508 pixels a row, which the
+// launches check).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr uint32_t BUF_OUT = 0x80000000u, BUF_MAX = 0x7fffffffu;
@@ -1434,7 +1435,9 @@ __device__ __forceinline__ void pack_tile(const PackJob& J, int tile, const floa
 // t = 0: wp[n][tap cin_p + c] = W[n][c][tap], the forward convs' B operand.
 // t = 1: wt[c][tap' cinp_t + n] = W[n][c][taps - 1 - tap'], the data-gradient
 // conv (flipped taps, input and output channels swapped).  Padding is zero.
-// Layers that run on k_conv3_rw are stored in fragment order, the others row by row.
+// Forward layers of a multiple of 64 output channels (all but the reconstruction convs)
+// are stored in fragment order, which k_conv3_rw, k_input and k_fuse read, and so are the
+// transposed 3x3 layers of a multiple of 64 channels on both sides; the others row by row.
 // Bound by memory, 6 bytes a weight and direction: 2.7 M and 11.8 M packed weights (16
 // blocks, dense groups) 26 -> 13 us and 96 -> 24; a thread per weight read the master in
 // steps of a kernel's taps.
@@ -1827,8 +1830,15 @@ __global__ __launch_bounds__(256, 3) void k_layer_bwd_view(ConvArgs p, BwdEpi e,
 // to four blocks per CU -- so side by side they take little more than the longest.  The
 // weight gradient's blocks, the longest, come first (a layer of 64 channels 15.1 -> 14.3
 // us, of 256 31 -> 27.7).  Measured, one training step of 16 images of 128 x 128: 1.58 ->
-// 1.30 ms (16 blocks: 24 -> 15 us a layer), 3.64 -> 3.19 ms (dense groups).  Larger tiles take 512 threads and longer
-// launches, which do not gain: the rule is the small plan's of k_conv3_rw.
+// 1.30 ms (16 blocks: 24 -> 15 us a layer), 3.64 -> 3.19 ms (dense groups).
+// Three blocks a CU leave 168 registers: 3 spilled with 64 channels, 16 with more, 24 in
+// k_layer_bwd_view's 4 x 4 tiles; two blocks, without spills, take 4.39 against 4.37 ms for
+// four steps of the 16-block network, 11.47 against 11.16 of the dense groups.
+// The rule is the small plan's of k_conv3_rw (128 tiles).  The launch still pays above it:
+// a step of images of 128 x 128 (4 tiles each) in separate launches on the large plan / in
+// one launch on the small plan, 16 images 1451 / 992 us (dense groups 3656 / 2428), 32
+// images 1928 / 1537 (4679 / 3802), 64 images 2832 / 2698 (6928 / 6650);
+// mrs_tuning.conv_small_tiles moves the line.
 template <bool MULTI>
 __global__ __launch_bounds__(256, 3) void k_layer_bwd(ConvArgs p, int cout_p, int nsplit,
                                                       BwdEpi be, int gx, int gy, int nd,
@@ -2065,16 +2075,6 @@ void launch_adam(float* w, const float* g, float* m, float* v, int64_t n, float 
   k_adam<<<cdiv64(n, 256), 256, 0, st>>>(w, g, m, v, n, lr, b1, b2, eps, c1, c2);
 }
 
-// Tile plan of a 3x3 conv on k_conv3_rw: 16 x 16 tiles of 8 waves with 64 output
-// channels at a time; when such tiles are fewer than mrs_tuning.conv_small_tiles
-// (default 128: half of the 256 CUs), 16 x 8 tiles of 4 waves with the output
-// channels split over blocks of 32 (two fit a CU at once).  Both plans sum every
-// output in the same K order, so the choice changes speed only.  Measured, small
-// against large plan, 64 / 128 / 256 input channels: 40 tiles 4.8 / 6.4 / 10.1
-// against 7.7 / 10.7 / 19.7 us, 120 tiles 6.1 / 8.9 / 15.9 against 7.9 / 11.0 /
-// 21.4, 160 tiles 7.1 / 13.2 / 23.2 against 8.0 / 11.2 / 22.5, 240 tiles (the 720p
-// LR image) 10.3 / 16.6 / 29.7 against 8.5 / 11.8 / 24.2.
-
 void conv_launch_counts(int64_t* out, bool reset) {
   for (int i = 0; i < MRS_NUM_CONV_KINDS; ++i)
     out[i] = reset ? g_conv_launches[i].exchange(0) : g_conv_launches[i].load();
@@ -2096,6 +2096,15 @@ bool launch_res_block(const ConvArgs& a, const ConvArgs& b, hipStream_t st) {
   return true;
 }
 
+// Tile plan of a 3x3 conv on k_conv3_rw: 16 x 16 tiles of 8 waves with 64 output
+// channels at a time; when such tiles are fewer than mrs_tuning.conv_small_tiles
+// (default 128: half of the 256 CUs), 16 x 8 tiles of 4 waves with the output
+// channels split over blocks of 32 (two fit a CU at once).  Both plans sum every
+// output in the same K order, so the choice changes speed only.  Measured, small
+// against large plan, 64 / 128 / 256 input channels: 40 tiles 4.8 / 6.4 / 10.1
+// against 7.7 / 10.7 / 19.7 us, 120 tiles 6.1 / 8.9 / 15.9 against 7.9 / 11.0 /
+// 21.4, 160 tiles 7.1 / 13.2 / 23.2 against 8.0 / 11.2 / 22.5, 240 tiles (the 720p
+// LR image) 10.3 / 16.6 / 29.7 against 8.5 / 11.8 / 24.2.
 void launch_conv(const ConvArgs& a, int cout_p, hipStream_t st) {
   const int64_t tiles = (int64_t)((a.W + 15) / 16) * ((a.H + 15) / 16) * a.B;
   if (tiles < conv_small_tiles() &&

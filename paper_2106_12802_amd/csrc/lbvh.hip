@@ -37,13 +37,13 @@
 // scenes), hence fewer node visits and triangle tests per ray.
 //
 // A build is bound by its chain of small dependent launches, not by its data (100k
-// triangles: 28 MB, 6 us at the rate of a copy; about 75 clustering rounds and 15
+// triangles: 28 MB, 6 us at the rate of a copy; 69 clustering rounds and 15
 // levels).  So the rounds of at most 4096 clusters run in one block, larger ones
 // take three launches with the counts left on the device (the host looks every
 // eighth round), leaf counts and parents are written as clusters merge instead of
 // by a walk with device-scope fences (266 us), and one allocation holds all
 // scratch.  Measured, build of 20k / 100k / 200k triangles: 2.77 / 4.60 / 5.49 ms
-// with five launches and a read-back per round, 0.74 / 1.11 / 1.67 ms now.
+// with five launches and a read-back per round, 0.69 / 1.01 / 1.53 ms now.
 #include "mrs_internal.hpp"
 #include "devmath.hpp"
 
@@ -561,7 +561,9 @@ __global__ __launch_bounds__(256) void k_ploc_scatter(
 // The rounds from at most PLOC_SMALL clusters on, in one block: the boxes stay in
 // LDS, each thread holds up to four clusters while they are merged and compacted.
 // A round costs its LDS reads and a few barriers; as five launches and a count
-// read back by the host it cost about 50 us, and a build has 50 such rounds.
+// read back by the host it cost about 50 us; 53 of the 69 rounds of 100,000 triangles
+// run here, in 248 us (a round of more clusters: 16 us in three launches).  4096 clusters
+// are what LDS holds; smaller lines were not measured.
 // Ends with PC_DONE = 1 and PC_ROOT when one cluster is left, with PC_DONE = 0
 // after max_rounds.
 __global__ __launch_bounds__(1024) void k_ploc_small(const uint32_t* __restrict__ mcount, int nint,
@@ -1044,8 +1046,7 @@ struct Collapse4 {
   float4* sparse4;
 };
 
-// Enqueues the collapse's first C4_TOP + C4_BATCH levels (a healthy tree has no
-// more), the dense numbering and the node count.
+// Enqueues the collapse's first C4_TOP levels.
 void collapse4_begin(const float4* nodes, int n, hipStream_t st, int leaf_max,
                      const Collapse4& c) {
   const int nint = n - 1;
@@ -1054,6 +1055,7 @@ void collapse4_begin(const float4* nodes, int n, hipStream_t st, int leaf_max,
                                      leaf_max);
 }
 
+// Enqueues levels from .. to - 1, the dense numbering and the node count.
 void collapse4_levels(const float4* nodes, int n, hipStream_t st, int leaf_max,
                       const Collapse4& c, int from, int to) {
   const int nint = n - 1;
@@ -1067,7 +1069,8 @@ void collapse4_levels(const float4* nodes, int n, hipStream_t st, int leaf_max,
 }
 
 // Top-down collapse of the binary tree, then dense renumbering.  Synchronises to
-// learn the node count (and, for a deep tree, whether levels are left).
+// learn the node count (and, for a tree of more than C4_TOP + C4_BATCH levels, whether
+// levels are left).
 mrs_status collapse4(mrs_scene* s, hipStream_t st, int leaf_max, const Collapse4& c) {
   const int n = s->ntris;
   collapse4_begin(s->d_nodes, n, st, leaf_max, c);

@@ -151,11 +151,13 @@ __device__ __forceinline__ float safe_rcp(float x) {
   return __builtin_amdgcn_rcpf(ax);
 }
 
-// Conservative slab test.  The far distance is widened by a few ulp so that
-// rounding never culls a box that the ray touches, and a box counts as nearer
-// than the best hit so far up to a relative 2^-12: far above the rounding of
-// either the box or the triangle distances, so culling never drops a triangle
-// that could tie with or beat the best hit, whatever order boxes are visited in.
+// Slab test with margins: the far distance is widened by a few ulp, and a box counts as
+// nearer than the best hit so far up to a relative 2^-12.  Both are relative to the
+// distance, where the rounding of o * inv is not (about 2^-24 |o * inv| on each axis).  So
+// culling keeps every triangle that could tie with or beat the best hit, whatever order
+// boxes are visited in, while its distance is above about 2^-12 |o * inv|, and every box
+// that the ray passes through by more than that rounding; a box that it only grazes can
+// be missed.  The quantized boxes carry an absolute margin and may keep such a box.
 __device__ __forceinline__ bool slab(float lx, float ly, float lz, float hx, float hy, float hz,
                                      f3 oi, f3 inv, float tbest, float& tnear) {
   const float t0x = fmaf(lx, inv.x, -oi.x), t1x = fmaf(hx, inv.x, -oi.x);
@@ -350,7 +352,7 @@ enum TraceMode { CLOSEST = 0, ANY_HIT = 1, PER_RAY = 2 };
 // which the first ones only lengthen their stacks: 720p at 4 spp 2.27 ms against
 // 2.19, six 7.4 M path frames 21.6 against 21.05; for three quarters 2.25 and
 // 21.4, for a quarter 2.25 and 21.9.)  A ray's visiting order thus depends on the rays
-// sharing its wave; the result does not, because box culling is conservative
+// sharing its wave; the result does not, as far as box culling is conservative
 // (see slab).  Children are visited nearest first (sorting network on the
 // entry distances); shadow rays stop at the first occluder.  MODE fixes the
 // ray kind (CLOSEST, ANY_HIT) or takes it from each ray (PER_RAY).  IO supplies
@@ -535,11 +537,12 @@ constexpr int QUAD_STACK = 4 * LDS_STACK;  // entries per ray held in LDS: a qua
 // lane tests one of a node's four children and one of a leaf's triangles, so a visit
 // is ~55 instructions and 7 dword loads of one line instead of ~120 and 7 x 16 bytes,
 // and a wave's 16 rays diverge less than 64 would.  Bound by the latency of a ray's
-// dependent visits; where the launches that take it end and what that gains: quad_rays.  All control flow is the same in
-// the four lanes of a quad (it depends on the ray and on values combined over the
-// quad); each lane keeps the best hit among the triangles that it tested, combined by
-// (distance, primitive id) when the ray ends.  The boxes are tested by the same
-// slab(), the triangles by the same isect_tri, so every hit is bitwise trace_stream's.
+// dependent visits; where the launches that take it end and what that gains: quad_rays.
+// All control flow is the same in the four lanes of a quad (it depends on the ray and on
+// values combined over the quad); each lane keeps the best hit among the triangles that
+// it tested, combined by (distance, primitive id) when the ray ends.  The boxes are tested
+// by the same slab(), the triangles by the same isect_tri, so every hit is bitwise
+// trace_stream's.
 // IO::store runs in the four lanes alike (they write the same values), for shadow rays in
 // the first.
 template <int MODE, class IO>
@@ -1888,7 +1891,9 @@ __global__ __launch_bounds__(256) void k_accumulate(SumArgs A) {
 // lane adds them, in order, to the one or two channels that it holds.  With a thread
 // per pixel, a lane's loads are a pixel apart and few pixels leave the chip idle: 2.8 M
 // paths at 1024 spp are 2730 pixels, 11 blocks of one thread a pixel, 293 us; this
-// kernel, bound by the serial adds of a pixel, takes 80 (FP64 sums).  The lines (sum_class): with
+// kernel takes 80 (FP64 sums).  Bound by the latency of its steps: the compiler keeps the
+// zeros beside the loads in scratch, so the loads are flat and a step's LDS reads wait for
+// the next step's samples too.  The lines (sum_class): with
 // features or layers to sum (thread per pixel / 16 lanes, us) 8 spp 10.6 / 14.8, 16 spp
 // 21 / 15, 32 spp 26 / 21 at 57,600 pixels; radiance alone 16 spp 6.5 / 7.4, 32 spp
 // 10.0 / 9.2, 64 spp 17 / 13 at 16,384 pixels (1,024 pixels: 16 lanes ahead from 16 on;
@@ -2391,7 +2396,8 @@ auto shadow_kernel(int sched) {
 // render of whole_paths' sizes runs its paths from camera ray to end in one launch
 // (k_path), up to 2^18 paths the path tail starts at bounce 1, up to 2^19 at bounce 2,
 // and above at bounce 3; a tail_bounce other than the default starts it there in every
-// render.  All routes give bitwise the same results.  Times of one render (us; depth 8, features; the 34-triangle box / 10,000 / 100,000 triangles):
+// render.  All routes give bitwise the same results.  Times of one render (us; depth 8,
+// features; the 34-triangle box / 10,000 / 100,000 triangles):
 //   16,384 paths: tail at 3 204 / 517 / 1261, all quads, tail at 1 120 / 260 / 409,
 //     one launch 112 / 214 / 239;
 //   65,536: 279 / 645 / 1548, 231 / 319 / 428, 214 / 276 / 313;
