@@ -1,17 +1,16 @@
 """Autotuner of the renderer's and the network's launch shape (performance only:
-results are bitwise independent of the tuning, which the tests check, except that
-quantized BVH nodes and FP32 ones may differ in a hit at a box that a ray grazes; a
-program that compares images of several tunings leaves bvh_quantized out of
-`secondary`).
+results are bitwise independent of what it searches by default, which the tests
+check).
 
 It times a workload under candidate tunings, keeps the fastest, and caches the
 choice in a JSON file keyed by device and workload so that later runs apply it
 without measuring.  The search is a grid over the primary launch shape
 (resident paths x traversal grid x queue schedule) followed by one pass over
 each secondary knob with the rest held at the best so far: sub-chunk streams,
-the first bounce traced path by path, the ordering of appended rays, the BVH
-node format, the bounces traced a wave at a time, the network conv tile plan
-and the fused residual blocks.
+the first bounce traced path by path, the ordering of appended rays, the
+bounces traced a wave at a time, the network conv tile plan and the fused
+residual blocks.  The BVH node format (bvh_quantized) is searched only where a
+caller lists it: the two formats may differ in a hit at a box that a ray grazes.
 """
 from __future__ import annotations
 
@@ -25,8 +24,7 @@ CHUNKS = (1 << 21, 1 << 22, 1 << 23, 1 << 24, 1 << 25)
 BLOCKS = (1024, 2048, 4096, 8192)
 SCHEDULES = (0, 1)
 SECONDARY = (("streams", (1, 2, 3, 4)), ("tail_bounce", (2, 3, 4, 5)),
-             ("queue_sort", (0, 1)), ("bvh_quantized", (0, 1)),
-             ("wave_extend", (0, 1, 2)), ("wave_shadow", (0, 1, 2)),
+             ("queue_sort", (0, 1)), ("wave_extend", (0, 1, 2)), ("wave_shadow", (0, 1, 2)),
              ("conv_small_tiles", (0, 64, 128, 256)), ("net_fused_blocks", (0, 1)))
 KEYS = ("chunk_paths", "trace_blocks", "schedule", "streams", "tail_bounce", "queue_sort",
         "bvh_quantized", "wave_extend", "wave_shadow", "conv_small_tiles", "net_fused_blocks")
