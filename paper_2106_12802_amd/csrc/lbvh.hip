@@ -63,6 +63,13 @@ __device__ __forceinline__ f3 centroid(const float4* tri, int i) {
   return (a + b + c) * (1.0f / 3.0f);
 }
 
+// Half the surface area of a box of sides dx, dy, dz, in a fixed order of roundings: areas
+// of nearly equal boxes decide which clusters merge and which child is opened, and the
+// compiler contracts the plain sum in one way here and in another there.
+__device__ __forceinline__ float half_area(float dx, float dy, float dz) {
+  return fmaf(dx, dz, fmaf(dx, dy, dy * dz));
+}
+
 __global__ __launch_bounds__(256) void k_bounds_partial(const float4* __restrict__ tri, int n,
                                                         float* __restrict__ part) {
   __shared__ float s[6][256];
@@ -368,8 +375,7 @@ enum { PC_MERGES = 0, PC_DONE, PC_DEPTH, PC_BAD, PC_ROOT, PLOC_CTR };
 enum { BAD_TREE = 1, BAD_STUCK = 2 };  // PC_BAD: malformed, a round without a merge
 
 __device__ __forceinline__ float box_half_area(float4 lo, float4 hi) {
-  const float dx = hi.x - lo.x, dy = hi.y - lo.y, dz = hi.z - lo.z;
-  return dx * dy + dy * dz + dz * dx;
+  return half_area(hi.x - lo.x, hi.y - lo.y, hi.z - lo.z);
 }
 
 // Clusters start as the leaves in Morton order: reference LEAF_BIT | k, lo.w = the
@@ -777,8 +783,7 @@ __device__ __forceinline__ void binary_children(const float* __restrict__ nf, Ca
 }
 
 __device__ __forceinline__ float half_area(const Cand& c) {
-  const float dx = c.hi[0] - c.lo[0], dy = c.hi[1] - c.lo[1], dz = c.hi[2] - c.lo[2];
-  return dx * dy + dy * dz + dz * dx;
+  return half_area(c.hi[0] - c.lo[0], c.hi[1] - c.lo[1], c.hi[2] - c.lo[2]);
 }
 
 // leaf-record range of a binary reference
